@@ -1,10 +1,10 @@
 // Temporal attention for gfx950: one sequence per (clip, pixel) made of that pixel's token
 // in every latent frame (T rows, H*W tokens apart in the packed buffer), per head.
-// HBM-bound up to 32 frames: the whole problem of one (pixel, head) is a 16 x 16 score tile (a
-// 32 x 32 one, further down, when a clip has more than 16 frames).  Clips with more than 32
-// frames are walked in 32-row blocks by the kernels at the end of the file.
+// HBM-bound up to 128 frames: up to 16 the whole problem of one (pixel, head) is a 16 x 16 score
+// tile of one wavefront, up to 128 one workgroup holds the sequence in LDS (further down).  Clips
+// with more frames are walked in 32-row blocks by the kernels at the end of the file.
 //
-// One wavefront owns one (pixel, head).  It gathers the T rows of q, k, v (and dout) into a
+// Up to 16 frames one wavefront owns one (pixel, head).  It gathers the T rows of q, k, v (and dout) into a
 // wave-private LDS tile with direct global->LDS loads (16-byte chunks, 256-byte rows, the same
 // XOR swizzle as the other attention kernels), and needs no workgroup barrier at all.
 //   S^T = K Q^T            v_mfma_f32_16x16x32_bf16, A = K rows, B = Q rows
@@ -17,6 +17,9 @@
 // it gets by issuing the score MFMAs twice with the operands swapped.
 // Rows past T are clamped copies of row T-1: as keys they are masked, as queries their
 // results are not stored and their P is zeroed where it would be summed into dK/dV.
+// Results are turned through LDS and stored as whole rows: with 32-byte pieces of 16 rows per store
+// 16 frames x 3,520 pixels x 32 heads took 0.375 ms forward and 0.73 backward, now 0.345 and
+// 0.62 (5.3 TB/s of the 11 tensors, the rate of a large in-place copy).
 #include <algorithm>
 
 #include "vfm_common.h"
@@ -107,16 +110,30 @@ __device__ __forceinline__ float quad_group_sum(float x) {
   return x + __shfl_xor(x, 32);
 }
 
-// Store a 16x16x16 result tile C[d = db*16 + 4*(l/16) + r][token = l%16] as 4 bf16 of row `token`.
+// Store the 16 x D result C[d = db*16 + 4*(l/16) + r][token = l%16] as bf16 rows.  The tile is turned
+// through 16*D*2 bytes of LDS that belong to the wavefront (16-byte chunk x of row t kept at chunk
+// x ^ t), so that a store instruction writes whole rows instead of 32 bytes of each of 16 rows.
 template <int D>
-__device__ __forceinline__ void store_tile(__bf16* base, const TUnit& u, size_t row_stride, int lane,
-                                           int db, f32x4v c, float mul) {
-  if ((lane & 15) < u.T) {
-    const size_t row = (size_t)(u.first_row + (lane & 15) * u.hw);
-    f32x4 o = {c[0] * mul, c[1] * mul, c[2] * mul, c[3] * mul};
-    *reinterpret_cast<bf16x4*>(base + row * row_stride + (size_t)u.head * D + db * 16 + 4 * (lane >> 4)) =
-        to_bf16x4(o);
+__device__ __forceinline__ void store_rows16(char* turn, __bf16* base, const TUnit& u, size_t row_stride, int lane,
+                                             const f32x4v (&c)[D / 16], float mul) {
+  constexpr int CPR = D / 8, RB = D * 2;
+  const int t = lane & 15, h = lane >> 4;
+#pragma unroll
+  for (int db = 0; db < D / 16; ++db) {
+    const f32x4 o = {c[db][0] * mul, c[db][1] * mul, c[db][2] * mul, c[db][3] * mul};
+    *reinterpret_cast<bf16x4*>(turn + t * RB + (((2 * db + (h >> 1)) ^ (t & (CPR - 1))) << 4) + 8 * (h & 1)) = to_bf16x4(o);
   }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int i = 0; i < 16 * CPR / 64; ++i) {
+    const int r = i * (64 / CPR) + lane / CPR, cx = lane % CPR;
+    const u32x4 w = *reinterpret_cast<const u32x4*>(turn + r * RB + ((cx ^ (r & (CPR - 1))) << 4));
+    if (r < u.T)
+      *reinterpret_cast<u32x4*>(base + (size_t)(u.first_row + r * u.hw) * row_stride + (size_t)u.head * D + cx * 8) = w;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
 }  // namespace
@@ -170,11 +187,10 @@ __global__ __launch_bounds__(kTWaves * 64) void tattn_fwd_kernel(const __bf16* _
   for (int r = 0; r < 4; ++r) p[r] *= inv;
   const bf16x4 pb = to_bf16x4(p);
   const f32x4v zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4v o[D / 16];
 #pragma unroll
-  for (int db = 0; db < D / 16; ++db) {
-    const f32x4v o = mfma16x16(read_tr<D>(mine + 2 * TB, lane, db), pb, zero);
-    store_tile<D>(out, u, row_stride, lane, db, o, 1.0f);
-  }
+  for (int db = 0; db < D / 16; ++db) o[db] = mfma16x16(read_tr<D>(mine + 2 * TB, lane, db), pb, zero);
+  store_rows16<D>(mine, out, u, row_stride, lane, o, 1.0f);   // through the q tile, which is spent
 }
 
 template <int D>
@@ -262,24 +278,30 @@ __global__ __launch_bounds__(kTWaves * 64) void tattn_bwd_kernel(const __bf16* _
   }
   const bf16x4 pBb = to_bf16x4(pB), dsBb = to_bf16x4(dsB);
   const f32x4v zero = {0.f, 0.f, 0.f, 0.f};
+  // (the v tile is spent: the results are turned through it one after the other)
+  f32x4v o[D / 16];
+  // dV^T[d, j] = sum_i dO[i, d] P[i, j];  dK^T[d, j] = scale sum_i Q[i, d] dS[i, j]
 #pragma unroll
-  for (int db = 0; db < D / 16; ++db) {
-    // dV^T[d, j] = sum_i dO[i, d] P[i, j];  dK^T[d, j] = scale sum_i Q[i, d] dS[i, j]
-    store_tile<D>(dv, u, row_stride, lane, db, mfma16x16(read_tr<D>(dot, lane, db), pBb, zero), 1.0f);
-    store_tile<D>(dk, u, row_stride, lane, db, mfma16x16(read_tr<D>(qt, lane, db), dsBb, zero), scale);
-    // dQ^T[d, i] = scale sum_j K[j, d] dS^T[j, i]
-    store_tile<D>(dq, u, row_stride, lane, db, mfma16x16(read_tr<D>(kt, lane, db), dsAb, zero), scale);
-  }
+  for (int db = 0; db < D / 16; ++db) o[db] = mfma16x16(read_tr<D>(dot, lane, db), pBb, zero);
+  store_rows16<D>(vt, dv, u, row_stride, lane, o, 1.0f);
+#pragma unroll
+  for (int db = 0; db < D / 16; ++db) o[db] = mfma16x16(read_tr<D>(qt, lane, db), dsBb, zero);
+  store_rows16<D>(vt, dk, u, row_stride, lane, o, scale);
+  // dQ^T[d, i] = scale sum_j K[j, d] dS^T[j, i]
+#pragma unroll
+  for (int db = 0; db < D / 16; ++db) o[db] = mfma16x16(read_tr<D>(kt, lane, db), dsAb, zero);
+  store_rows16<D>(vt, dq, u, row_stride, lane, o, scale);
 }
 
-// ---------------------------------------------------------------- 17..32 frames
-// The same scheme on a 32 x 32 score tile with the 32x32x16 MFMA (lane layouts as in the packed
-// attention kernels: an operand lane holds row l%32, columns ks*16 + 8*(l/32)..+7; an accumulator
-// lane holds column l%32, rows 8*(r/4) + 4*(l/32) + r%4 in its sixteen registers; a transposed
-// operand comes from two transposing LDS reads).  Used when some clip of the call has T > 16.
+// ---------------------------------------------------------------- more than 16 frames: 32-row tiles
+// Helpers of the 32x32x16 MFMA (lane layouts as in the packed attention kernels: an operand lane
+// holds row l%32, columns ks*16 + 8*(l/32)..+7; an accumulator lane holds column l%32, rows
+// 8*(r/4) + 4*(l/32) + r%4 in its sixteen registers; a transposed operand comes from two
+// transposing LDS reads).
 namespace {
 
 constexpr int kT2Rows = 32;
+constexpr f32x16 kZero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
 template <int D>
 struct T2Cfg {
@@ -287,21 +309,6 @@ struct T2Cfg {
   static constexpr int kChunksPerRow = D / 8;
   static constexpr int kLoadsPerTile = kT2Rows * kChunksPerRow / 64;
 };
-
-template <int D>
-__device__ __forceinline__ void gather_tile32(const __bf16* base, const TUnit& u, uint32_t row_bytes,
-                                              uint32_t lds_tile, int lane) {
-  using Cfg = T2Cfg<D>;
-#pragma unroll
-  for (int x = 0; x < Cfg::kLoadsPerTile; ++x) {
-    const int p = x * 64 + lane;
-    const int r = p / Cfg::kChunksPerRow;
-    const int chunk = (p % Cfg::kChunksPerRow) ^ swz<D>(r);
-    const uint32_t off = (uint32_t)(u.first_row + min(r, u.T - 1) * u.hw) * row_bytes +
-                         (uint32_t)(u.head * D * 2 + chunk * 16);
-    lds_dma16(base, off, lds_tile + x * 1024);
-  }
-}
 
 // Row operands: lane l holds row l%32, columns ks*16 + 8*(l/32)..+7.
 template <int D>
@@ -319,21 +326,6 @@ __device__ __forceinline__ bf16x8 read_tr32(const char* tile, int lane, int db, 
   return join_tr(lds_read_tr(tile, tile_off<D>(row, col)), lds_read_tr(tile, tile_off<D>(row + 8, col)));
 }
 
-// Store an accumulator tile C[d = db*32 + 8*(r/4) + 4*(l/32) + r%4][token = l%32] as bf16 of row `token`.
-template <int D>
-__device__ __forceinline__ void store_tile32(__bf16* base, const TUnit& u, size_t row_stride, int lane,
-                                             int db, const f32x16& c, float mul) {
-  if ((lane & 31) < u.T) {
-    const size_t row = (size_t)(u.first_row + (lane & 31) * u.hw);
-    __bf16* p = base + row * row_stride + (size_t)u.head * D + db * 32 + 4 * (lane >> 5);
-#pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      f32x4 o = {c[4 * q4] * mul, c[4 * q4 + 1] * mul, c[4 * q4 + 2] * mul, c[4 * q4 + 3] * mul};
-      *reinterpret_cast<bf16x4*>(p + 8 * q4) = to_bf16x4(o);
-    }
-  }
-}
-
 __device__ __forceinline__ bf16x8 half_to_bf16(const f32x16& x, int s2) {
   f32x8 a;
 #pragma unroll
@@ -343,184 +335,339 @@ __device__ __forceinline__ bf16x8 half_to_bf16(const f32x16& x, int s2) {
 
 }  // namespace
 
-template <int D>
-__global__ __launch_bounds__(kTWaves * 64) void tattn32_fwd_kernel(const __bf16* __restrict__ q,
-                                                                   const __bf16* __restrict__ k,
-                                                                   const __bf16* __restrict__ v,
-                                                                   __bf16* __restrict__ out,
-                                                                   const TemporalTable tab, int n_heads,
-                                                                   float scale_log2) {
-  using Cfg = T2Cfg<D>;
-  constexpr int TB = Cfg::kTileBytes;
-  constexpr int KS = D / 16, DB = D / 32;
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  TUnit u;
-  if (!temporal_unit(tab, n_heads, u)) return;   // whole wavefronts leave; there are no barriers
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int g = lane >> 5;
-  const size_t row_stride = (size_t)n_heads * D;
-  const uint32_t row_bytes = (uint32_t)row_stride * 2u;
-  char* mine = smem + wave * 3 * TB;
-  const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr_of(mine));
-  gather_tile32<D>(q, u, row_bytes, lds0, lane);
-  gather_tile32<D>(k, u, row_bytes, lds0 + TB, lane);
-  gather_tile32<D>(v, u, row_bytes, lds0 + 2 * TB, lane);
-  wait_vmcnt<0>();
+// ---------------------------------------------------------------- 17..128 frames
+// A whole sequence fits in LDS (128 frames of q, k, v and dout at head_dim 128 are 128 KB), so one
+// workgroup owns one (pixel, head), gathers every row once, needs nothing from memory after that
+// and stores whole rows: bound by HBM.  NB = 32-row blocks of the longest sequence of the launch;
+// shorter ones skip the blocks they do not have (uniform branches).
+// Forward: wave b owns query block b and holds its whole score row S^T in registers (NB 32 x 32
+// tiles), so the softmax is exact and needs no rescaling.
+// Measured at head_dim 128, forward and backward together, against the kernels that walk 32-row
+// blocks (below), which read q, k, v, dout three times in the backward: 64 frames x 3,520
+// pixels x 8 heads 2.36 -> 1.07 ms (4.7 TB/s of the 11 tensors; a large copy reaches 5.0), 40
+// frames 2.1x, 80 to 120 frames 1.7 to 1.8x (one workgroup per CU there: its loads and its
+// arithmetic do not overlap); at 17 to 32 frames against one wavefront per sequence with 16-byte
+// stores 1.14 to 1.2x.
+namespace {
 
-  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  bf16x8 qf[KS], kf[KS];
-  read_rows32<D>(mine, lane, qf);
-  read_rows32<D>(mine + TB, lane, kf);
-  f32x16 st = zero16;
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) st = mfma32(kf[ks], qf[ks], st);
-  // lane: query l%32; register r: key 8*(r/4) + 4g + r%4
-  float mx = -INFINITY;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    if (8 * (r >> 2) + 4 * g + (r & 3) >= u.T) st[r] = -INFINITY;
-    mx = fmaxf(mx, st[r]);
+__device__ __forceinline__ bool temporal_block_unit(const TemporalTable& tab, int n_heads, TUnit& u) {
+  const int unit = blockIdx.x;
+  if (unit >= tab.pix_cu[tab.n] * n_heads) return false;
+  u.head = unit % n_heads;
+  const int pp = unit / n_heads;
+  int lo = 0, hi = tab.n;            // last clip s with pix_cu[s] <= pp (skips empty clips)
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (tab.pix_cu[mid] <= pp) lo = mid; else hi = mid;
   }
-  const float m2 = pair_max(mx) * scale_log2;
-  f32x16 p;
-  float sum = 0.f;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    p[r] = fast_exp2(st[r] * scale_log2 - m2);
-    sum += p[r];
-  }
-  const float inv = 1.0f / pair_sum(sum);
-#pragma unroll
-  for (int r = 0; r < 16; ++r) p[r] *= inv;
-  const bf16x8 pb0 = half_to_bf16(p, 0), pb1 = half_to_bf16(p, 1);
-#pragma unroll
-  for (int db = 0; db < DB; ++db) {
-    f32x16 o = mfma32(read_tr32<D>(mine + 2 * TB, lane, db, 0), pb0, zero16);
-    o = mfma32(read_tr32<D>(mine + 2 * TB, lane, db, 1), pb1, o);
-    store_tile32<D>(out, u, row_stride, lane, db, o, 1.0f);
-  }
+  u.hw = tab.hw[lo];
+  u.first_row = tab.cu[lo] + (pp - tab.pix_cu[lo]);
+  u.T = (tab.cu[lo + 1] - tab.cu[lo]) / u.hw;
+  return true;
 }
 
-template <int D>
-__global__ __launch_bounds__(kTWaves * 64) void tattn32_bwd_kernel(const __bf16* __restrict__ q,
-                                                                   const __bf16* __restrict__ k,
-                                                                   const __bf16* __restrict__ v,
-                                                                   const __bf16* __restrict__ dout,
-                                                                   __bf16* __restrict__ dq,
-                                                                   __bf16* __restrict__ dk,
-                                                                   __bf16* __restrict__ dv,
-                                                                   const TemporalTable tab, int n_heads,
-                                                                   float scale, float scale_log2) {
-  using Cfg = T2Cfg<D>;
-  constexpr int TB = Cfg::kTileBytes;
-  constexpr int KS = D / 16, DB = D / 32;
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  TUnit u;
-  if (!temporal_unit(tab, n_heads, u)) return;
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int g = lane >> 5;
-  const size_t row_stride = (size_t)n_heads * D;
-  const uint32_t row_bytes = (uint32_t)row_stride * 2u;
-  char* qt = smem + wave * 4 * TB;
-  char* kt = qt + TB;
-  char* vt = qt + 2 * TB;
-  char* dot = qt + 3 * TB;
-  const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr_of(qt));
-  gather_tile32<D>(q, u, row_bytes, lds0, lane);
-  gather_tile32<D>(k, u, row_bytes, lds0 + TB, lane);
-  gather_tile32<D>(v, u, row_bytes, lds0 + 2 * TB, lane);
-  gather_tile32<D>(dout, u, row_bytes, lds0 + 3 * TB, lane);
-  wait_vmcnt<0>();
-
-  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  bf16x8 qf[KS], kf[KS], vf[KS], df[KS];
-  read_rows32<D>(qt, lane, qf);
-  read_rows32<D>(kt, lane, kf);
-  read_rows32<D>(vt, lane, vf);
-  read_rows32<D>(dot, lane, df);
-  // "A": lane = query, registers = keys (S^T, dP^T);  "B": lane = key, registers = queries (S, dP)
-  f32x16 sA = zero16, dpA = zero16;
+// This wave's share of the rows [0, 32 * n_blk) of one tensor (rows past T are copies of row T-1) into
+// consecutive swizzled [32][D] tiles.
+template <int D, int NB, int NW>
+__device__ __forceinline__ void gather_blocks(const __bf16* base, const TUnit& u, int n_blk, uint32_t row_bytes,
+                                              uint32_t lds_tile, int wave, int lane) {
+  constexpr int CPR = T2Cfg<D>::kChunksPerRow, LPB = T2Cfg<D>::kLoadsPerTile;
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    sA = mfma32(kf[ks], qf[ks], sA);
-    dpA = mfma32(vf[ks], df[ks], dpA);
-  }
-  // softmax statistics per query, in orientation A
-  float mx = -INFINITY;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    if (8 * (r >> 2) + 4 * g + (r & 3) >= u.T) sA[r] = -INFINITY;
-    mx = fmaxf(mx, sA[r]);
-  }
-  const float m2 = pair_max(mx) * scale_log2;
-  f32x16 pA;
-  float sum = 0.f;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    pA[r] = fast_exp2(sA[r] * scale_log2 - m2);
-    sum += pA[r];
-  }
-  sum = pair_sum(sum);
-  const float lse2 = m2 + __log2f(sum);      // P = exp2(s*scale_log2 - lse2)
-  const float inv = 1.0f / sum;
-  float dl = 0.f;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    pA[r] *= inv;
-    dl += pA[r] * dpA[r];
-  }
-  const float delta = pair_sum(dl);          // Delta_i = sum_j P_ij dP_ij
-  f32x16 dsA;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) dsA[r] = pA[r] * (dpA[r] - delta);
-  {
-    // dQ^T[d, i] = scale sum_j K[j, d] dS^T[j, i]
-    const bf16x8 d0 = half_to_bf16(dsA, 0), d1 = half_to_bf16(dsA, 1);
-#pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      f32x16 o = mfma32(read_tr32<D>(kt, lane, db, 0), d0, zero16);
-      o = mfma32(read_tr32<D>(kt, lane, db, 1), d1, o);
-      store_tile32<D>(dq, u, row_stride, lane, db, o, scale);
+  for (int x = 0; x < (NB * LPB + NW - 1) / NW; ++x) {
+    const int i = x * NW + wave;               // 1 KB piece
+    if (i < n_blk * LPB) {
+      const int p = i * 64 + lane;
+      const int r = p / CPR;
+      const int chunk = (p % CPR) ^ swz<D>(r);
+      const uint32_t off = (uint32_t)(u.first_row + min(r, u.T - 1) * u.hw) * row_bytes +
+                           (uint32_t)(u.head * D * 2 + chunk * 16);
+      lds_dma16(base, off, lds_tile + i * 1024);
     }
   }
-  // orientation B: register r belongs to query i = 8*(r/4) + 4g + r%4, whose statistics lane i holds
-  f32x16 sB = zero16, dpB = zero16;
+}
+
+}  // namespace
+
+template <int D, int NB>
+__global__ __launch_bounds__(NB * 64, 2) void tattnB_fwd_kernel(const __bf16* __restrict__ q,
+                                                                const __bf16* __restrict__ k,
+                                                                const __bf16* __restrict__ v,
+                                                                __bf16* __restrict__ out,
+                                                                const TemporalTable tab, int n_heads,
+                                                                float scale_log2) {
+  constexpr int TB = T2Cfg<D>::kTileBytes;
+  constexpr int KS = D / 16, DB = D / 32;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  TUnit u;
+  if (!temporal_block_unit(tab, n_heads, u)) return;
+  const int lane = threadIdx.x & 63, g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n_blk = (u.T + kT2Rows - 1) / kT2Rows;
+  const size_t row_stride = (size_t)n_heads * D;
+  const uint32_t row_bytes = (uint32_t)row_stride * 2u;
+  char* qt = smem;
+  char* kt = qt + NB * TB;
+  char* vt = kt + NB * TB;
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr_of(smem));
+  gather_blocks<D, NB, NB>(q, u, n_blk, row_bytes, lds0, wave, lane);
+  gather_blocks<D, NB, NB>(k, u, n_blk, row_bytes, lds0 + NB * TB, wave, lane);
+  gather_blocks<D, NB, NB>(v, u, n_blk, row_bytes, lds0 + 2 * NB * TB, wave, lane);
+  wait_vmcnt<0>();
+  __syncthreads();
+  if (wave >= n_blk) return;         // (no barrier below)
+
+  bf16x8 qf[KS];
+  read_rows32<D>(qt + wave * TB, lane, qf);
+  f32x16 s[NB];
+  float mx = -INFINITY;
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    sB = mfma32(qf[ks], kf[ks], sB);
-    dpB = mfma32(df[ks], vf[ks], dpB);
+  for (int kb = 0; kb < NB; ++kb) {
+    if (kb < n_blk) {
+      bf16x8 kf[KS];
+      read_rows32<D>(kt + kb * TB, lane, kf);
+      s[kb] = kZero16;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) s[kb] = mfma32(kf[ks], qf[ks], s[kb]);
+      // lane: query l%32 of the block; register r: key 32*kb + 8*(r/4) + 4g + r%4
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        if (kb * kT2Rows + 8 * (r >> 2) + 4 * g + (r & 3) >= u.T) s[kb][r] = -INFINITY;
+        mx = fmaxf(mx, s[kb][r]);
+      }
+    }
   }
-  f32x16 pB, dsB;
+  const float m2 = pair_max(mx) * scale_log2;
+  float sum = 0.f;
+  f32x16 oacc[DB];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int i = 8 * (r >> 2) + 4 * g + (r & 3);
-    const float l2 = __shfl(lse2, i);
-    const float dd = __shfl(delta, i);
-    const float pv = (i < u.T) ? fast_exp2(sB[r] * scale_log2 - l2) : 0.f;   // padded queries add nothing
-    pB[r] = pv;
-    dsB[r] = pv * (dpB[r] - dd);
+  for (int db = 0; db < DB; ++db) oacc[db] = kZero16;
+#pragma unroll
+  for (int kb = 0; kb < NB; ++kb) {
+    if (kb < n_blk) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        s[kb][r] = fast_exp2(s[kb][r] * scale_log2 - m2);
+        sum += s[kb][r];
+      }
+      const bf16x8 p0 = half_to_bf16(s[kb], 0), p1 = half_to_bf16(s[kb], 1);
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+        oacc[db] = mfma32(read_tr32<D>(vt + kb * TB, lane, db, 0), p0, oacc[db]);
+        oacc[db] = mfma32(read_tr32<D>(vt + kb * TB, lane, db, 1), p1, oacc[db]);
+      }
+    }
   }
-  const bf16x8 p0 = half_to_bf16(pB, 0), p1 = half_to_bf16(pB, 1);
-  const bf16x8 s0 = half_to_bf16(dsB, 0), s1 = half_to_bf16(dsB, 1);
+  const float inv = 1.0f / pair_sum(sum);
+  // this wave's q tile is its own: turn the result through it and store whole rows
+  store_tile_rows<D>(qt + wave * TB, oacc, inv,
+                     out + (size_t)(u.first_row + wave * kT2Rows * u.hw) * row_stride + (size_t)u.head * D,
+                     row_stride * u.hw, u.T - wave * kT2Rows);
+}
+
+// Backward: 2 NB waves.  Waves b < NB own query block b: S^T and dP^T of the whole row in registers,
+// softmax and Delta_i = sum_j P_ij dP_ij exactly, the two statistics into LDS, then
+// dQ^T = K^T dS^T.  Waves NB + b own key block b: after the statistics they recompute S and dP in
+// the other orientation, query block by query block, and accumulate dV^T and dK^T.  Seven
+// tensors cross the memory bus once each.
+template <int D, int NB>
+__global__ __launch_bounds__(NB * 128, 2) void tattnB_bwd_kernel(const __bf16* __restrict__ q,
+                                                                 const __bf16* __restrict__ k,
+                                                                 const __bf16* __restrict__ v,
+                                                                 const __bf16* __restrict__ dout,
+                                                                 __bf16* __restrict__ dq,
+                                                                 __bf16* __restrict__ dk,
+                                                                 __bf16* __restrict__ dv,
+                                                                 const TemporalTable tab, int n_heads,
+                                                                 float scale, float scale_log2) {
+  constexpr int TB = T2Cfg<D>::kTileBytes;
+  constexpr int KS = D / 16, DB = D / 32;
+  constexpr int NW = 2 * NB;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  TUnit u;
+  if (!temporal_block_unit(tab, n_heads, u)) return;
+  const int lane = threadIdx.x & 63, g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n_blk = (u.T + kT2Rows - 1) / kT2Rows;
+  const size_t row_stride = (size_t)n_heads * D;
+  const uint32_t row_bytes = (uint32_t)row_stride * 2u;
+  char* qt = smem;
+  char* kt = qt + NB * TB;
+  char* vt = kt + NB * TB;
+  char* dot = vt + NB * TB;
+  float* lse_s = reinterpret_cast<float*>(dot + NB * TB);
+  float* delta_s = lse_s + NB * kT2Rows;
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr_of(smem));
+  gather_blocks<D, NB, NW>(q, u, n_blk, row_bytes, lds0, wave, lane);
+  gather_blocks<D, NB, NW>(k, u, n_blk, row_bytes, lds0 + NB * TB, wave, lane);
+  gather_blocks<D, NB, NW>(v, u, n_blk, row_bytes, lds0 + 2 * NB * TB, wave, lane);
+  gather_blocks<D, NB, NW>(dout, u, n_blk, row_bytes, lds0 + 3 * NB * TB, wave, lane);
+  wait_vmcnt<0>();
+  __syncthreads();
+
+  const bool query_role = wave < NB;
+  const int blk = query_role ? wave : wave - NB;
+  const bool live = blk < n_blk;
+  const size_t head_off = (size_t)u.head * D;
+  const size_t blk_off = (size_t)(u.first_row + blk * kT2Rows * u.hw) * row_stride + head_off;
+  const int rows_valid = u.T - blk * kT2Rows;
+  char* turn = smem + wave * TB;      // after the last barrier
+
+  if (query_role) {
+    f32x16 acc[DB];
+    f32x16 s[NB], dp[NB];
+    float inv = 0.f, delta = 0.f, m2 = 0.f;
+    if (live) {
+      bf16x8 qf[KS], df[KS];
+      read_rows32<D>(qt + blk * TB, lane, qf);
+      read_rows32<D>(dot + blk * TB, lane, df);
+      float mx = -INFINITY;
 #pragma unroll
-  for (int db = 0; db < DB; ++db) {
-    // dV^T[d, j] = sum_i dO[i, d] P[i, j];  dK^T[d, j] = scale sum_i Q[i, d] dS[i, j]
-    f32x16 o = mfma32(read_tr32<D>(dot, lane, db, 0), p0, zero16);
-    o = mfma32(read_tr32<D>(dot, lane, db, 1), p1, o);
-    store_tile32<D>(dv, u, row_stride, lane, db, o, 1.0f);
-    o = mfma32(read_tr32<D>(qt, lane, db, 0), s0, zero16);
-    o = mfma32(read_tr32<D>(qt, lane, db, 1), s1, o);
-    store_tile32<D>(dk, u, row_stride, lane, db, o, scale);
+      for (int kb = 0; kb < NB; ++kb) {
+        if (kb < n_blk) {
+          s[kb] = kZero16;
+          dp[kb] = kZero16;
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) {
+            const int off = tile_off<D>(lane & 31, ks * 16 + 8 * g);
+            s[kb] = mfma32(lds_read_b128(kt + kb * TB, off), qf[ks], s[kb]);
+            dp[kb] = mfma32(lds_read_b128(vt + kb * TB, off), df[ks], dp[kb]);
+          }
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            if (kb * kT2Rows + 8 * (r >> 2) + 4 * g + (r & 3) >= u.T) s[kb][r] = -INFINITY;
+            mx = fmaxf(mx, s[kb][r]);
+          }
+        }
+      }
+      m2 = pair_max(mx) * scale_log2;
+      float sum = 0.f, dl = 0.f;
+#pragma unroll
+      for (int kb = 0; kb < NB; ++kb)
+        if (kb < n_blk) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            s[kb][r] = fast_exp2(s[kb][r] * scale_log2 - m2);
+            sum += s[kb][r];
+          }
+        }
+      sum = pair_sum(sum);
+      inv = 1.0f / sum;
+#pragma unroll
+      for (int kb = 0; kb < NB; ++kb)
+        if (kb < n_blk) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            s[kb][r] *= inv;
+            dl += s[kb][r] * dp[kb][r];
+          }
+        }
+      delta = pair_sum(dl);
+      // queries past the end contribute nothing to dK, dV: P = exp2(s - inf) = 0
+      if (g == 0) {
+        const bool valid = (lane & 31) < rows_valid;
+        lse_s[blk * kT2Rows + (lane & 31)] = valid ? m2 + __log2f(sum) : INFINITY;
+        delta_s[blk * kT2Rows + (lane & 31)] = valid ? delta : 0.f;
+      }
+    }
+    __syncthreads();
+    if (live) {
+#pragma unroll
+      for (int db = 0; db < DB; ++db) acc[db] = kZero16;
+#pragma unroll
+      for (int kb = 0; kb < NB; ++kb)
+        if (kb < n_blk) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) s[kb][r] *= dp[kb][r] - delta;
+          const bf16x8 d0 = half_to_bf16(s[kb], 0), d1 = half_to_bf16(s[kb], 1);
+#pragma unroll
+          for (int db = 0; db < DB; ++db) {   // dQ^T[d, i] += sum_j K[j, d] dS^T[j, i]
+            acc[db] = mfma32(read_tr32<D>(kt + kb * TB, lane, db, 0), d0, acc[db]);
+            acc[db] = mfma32(read_tr32<D>(kt + kb * TB, lane, db, 1), d1, acc[db]);
+          }
+        }
+    }
+    __syncthreads();   // every tile has been read: the waves turn their results through them
+    if (live) store_tile_rows<D>(turn, acc, scale, dq + blk_off, row_stride * u.hw, rows_valid);
+  } else {
+    f32x16 dkacc[DB], dvacc[DB];
+    bf16x8 kf[KS], vf[KS];
+    if (live) {
+      read_rows32<D>(kt + blk * TB, lane, kf);
+      read_rows32<D>(vt + blk * TB, lane, vf);
+    }
+    __syncthreads();   // statistics
+    if (live) {
+#pragma unroll
+      for (int db = 0; db < DB; ++db) { dkacc[db] = kZero16; dvacc[db] = kZero16; }
+      for (int qb = 0; qb < n_blk; ++qb) {
+        // lane = key of this block, register r = query 32*qb + 8*(r/4) + 4g + r%4
+        f32x16 sB = kZero16, dpB = kZero16;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          const int off = tile_off<D>(lane & 31, ks * 16 + 8 * g);
+          sB = mfma32(lds_read_b128(qt + qb * TB, off), kf[ks], sB);
+          dpB = mfma32(lds_read_b128(dot + qb * TB, off), vf[ks], dpB);
+        }
+        f32x16 pB, dsB;
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const f32x4 l4 = *reinterpret_cast<const f32x4*>(lse_s + qb * kT2Rows + 8 * q4 + 4 * g);
+          const f32x4 d4 = *reinterpret_cast<const f32x4*>(delta_s + qb * kT2Rows + 8 * q4 + 4 * g);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int r = 4 * q4 + e;
+            pB[r] = fast_exp2(sB[r] * scale_log2 - l4[e]);
+            dsB[r] = pB[r] * (dpB[r] - d4[e]);
+          }
+        }
+        const bf16x8 p0 = half_to_bf16(pB, 0), p1 = half_to_bf16(pB, 1);
+        const bf16x8 s0 = half_to_bf16(dsB, 0), s1 = half_to_bf16(dsB, 1);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+          // dV^T[d, j] += sum_i dO[i, d] P[i, j];  dK^T[d, j] += sum_i Q[i, d] dS[i, j]
+          dvacc[db] = mfma32(read_tr32<D>(dot + qb * TB, lane, db, 0), p0, dvacc[db]);
+          dvacc[db] = mfma32(read_tr32<D>(dot + qb * TB, lane, db, 1), p1, dvacc[db]);
+          dkacc[db] = mfma32(read_tr32<D>(qt + qb * TB, lane, db, 0), s0, dkacc[db]);
+          dkacc[db] = mfma32(read_tr32<D>(qt + qb * TB, lane, db, 1), s1, dkacc[db]);
+        }
+      }
+    }
+    __syncthreads();
+    if (live) {
+      store_tile_rows<D>(turn, dkacc, scale, dk + blk_off, row_stride * u.hw, rows_valid);
+      store_tile_rows<D>(turn, dvacc, 1.0f, dv + blk_off, row_stride * u.hw, rows_valid);
+    }
   }
 }
 
-// ---------------------------------------------------------------- more than 32 frames
-// Section 4.6 speaks of videos of hundreds of frames.  For clips with T > 32 a wavefront owns one
+template <int D, int NB>
+static hipError_t launch_blocks(const void* q, const void* k, const void* v, const void* dout,
+                                const TemporalTable& tab, int n_heads, float scale, void* o0, void* o1,
+                                void* o2, hipStream_t stream) {
+  const dim3 grid((unsigned)(tab.pix_cu[tab.n] * n_heads));
+  constexpr int TB = T2Cfg<D>::kTileBytes;
+  const float scale_log2 = scale * kLog2eT;
+  if (!dout) {
+    constexpr int lds = 3 * NB * TB;
+    auto kern = tattnB_fwd_kernel<D, NB>;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    return launch(kern, grid, dim3(NB * 64), lds, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (__bf16*)o0,
+                  tab, n_heads, scale_log2);
+  }
+  constexpr int lds = 4 * NB * TB + 2 * NB * kT2Rows * 4;
+  auto kern = tattnB_bwd_kernel<D, NB>;
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (e != hipSuccess) return e;
+  return launch(kern, grid, dim3(NB * 128), lds, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v,
+                (const __bf16*)dout, (__bf16*)o0, (__bf16*)o1, (__bf16*)o2, tab, n_heads, scale, scale_log2);
+}
+
+// ---------------------------------------------------------------- more than 128 frames
+// Section 4.6 speaks of videos of hundreds of frames.  For clips with T > 128 a wavefront owns one
 // 32-row block of one (pixel, head) sequence and walks the sequence's other side in blocks of 32
 // with the online softmax of the packed kernels (running reference m, running sum l, rescaled
-// accumulators), on the 32 x 32 tiles, lane layouts and LDS helpers of the 17..32-frame kernels.
+// accumulators), on the 32 x 32 tiles, lane layouts and LDS helpers above.
 // Blocks of one sequence are consecutive work units, so the wavefronts that re-read a
 // sequence's K/V (or Q/dO) rows run together and find them in cache.
 // The backward still takes no workspace: a first kernel writes each query's statistics (lse in
@@ -604,8 +751,6 @@ template <int D>
 __device__ __forceinline__ float* stat_slot(__bf16* dq, const TUnit& u, int t, size_t row_stride) {
   return reinterpret_cast<float*>(dq + (size_t)(u.first_row + t * u.hw) * row_stride + (size_t)u.head * D);
 }
-
-constexpr f32x16 kZero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
 }  // namespace
 
@@ -856,7 +1001,7 @@ __global__ __launch_bounds__(kTWaves * 64) void tattnL_dq_kernel(const __bf16* _
   for (int db = 0; db < DB; ++db) store_block<D>(dq, u, w.blk, row_stride, lane, db, dqacc[db], scale);
 }
 
-// Some clip of the run has more than 32 frames: the block-walking kernels serve the whole run.
+// Some clip of the run has more than 128 frames: the block-walking kernels serve the whole run.
 template <int D>
 static hipError_t launch_long(const void* q, const void* k, const void* v, const void* dout,
                               const TemporalTable& tab, int n_heads, float scale, void* o0, void* o1,
@@ -914,27 +1059,29 @@ static hipError_t launch_t(const void* q, const void* k, const void* v, const vo
   int max_t = 0;
   for (int s = 0; s < tab.n; ++s)
     if (tab.hw[s] > 0) max_t = std::max(max_t, (tab.cu[s + 1] - tab.cu[s]) / tab.hw[s]);
-  if (max_t > kT2Rows) return launch_long<D>(q, k, v, dout, tab, n_heads, scale, o0, o1, o2, stream);
-  const bool big = max_t > kTRows;     // some clip has more than 16 frames: 32-row tiles for the call
+  // the longest sequence of the run picks the kernels for all of it
+  if (max_t > 4 * kT2Rows) return launch_long<D>(q, k, v, dout, tab, n_heads, scale, o0, o1, o2, stream);
+  if (max_t > 3 * kT2Rows) return launch_blocks<D, 4>(q, k, v, dout, tab, n_heads, scale, o0, o1, o2, stream);
+  if (max_t > 2 * kT2Rows) return launch_blocks<D, 3>(q, k, v, dout, tab, n_heads, scale, o0, o1, o2, stream);
+  if (max_t > kT2Rows) return launch_blocks<D, 2>(q, k, v, dout, tab, n_heads, scale, o0, o1, o2, stream);
+  if (max_t > kTRows) return launch_blocks<D, 1>(q, k, v, dout, tab, n_heads, scale, o0, o1, o2, stream);
   const int grid = (int)((n_units + kTWaves - 1) / kTWaves);
-  const int tiles = dout ? 4 : 3;
-  const int lds = kTWaves * tiles * (big ? T2Cfg<D>::kTileBytes : TCfg<D>::kTileBytes);
+  const int lds = kTWaves * (dout ? 4 : 3) * TCfg<D>::kTileBytes;
   if (!dout) {
-    auto kern = big ? tattn32_fwd_kernel<D> : tattn_fwd_kernel<D>;
+    auto kern = tattn_fwd_kernel<D>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     return launch(kern, dim3(grid), dim3(kTWaves * 64), lds, stream, (const __bf16*)q, (const __bf16*)k,
                   (const __bf16*)v, (__bf16*)o0, tab, n_heads, scale * kLog2eT);
-  } else {
-    auto kern = big ? tattn32_bwd_kernel<D> : tattn_bwd_kernel<D>;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
-    return launch(kern, dim3(grid), dim3(kTWaves * 64), lds, stream, (const __bf16*)q, (const __bf16*)k,
-                  (const __bf16*)v, (const __bf16*)dout, (__bf16*)o0, (__bf16*)o1, (__bf16*)o2, tab, n_heads,
-                  scale, scale * kLog2eT);
   }
+  auto kern = tattn_bwd_kernel<D>;
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (e != hipSuccess) return e;
+  return launch(kern, dim3(grid), dim3(kTWaves * 64), lds, stream, (const __bf16*)q, (const __bf16*)k,
+                (const __bf16*)v, (const __bf16*)dout, (__bf16*)o0, (__bf16*)o1, (__bf16*)o2, tab, n_heads,
+                scale, scale * kLog2eT);
 }
 
 hipError_t launch_tattn_fwd(const void* q, const void* k, const void* v, const TemporalTable& tab,

@@ -125,3 +125,13 @@ def test_full_size_c4_every_element():
     dev, gpu = _run(_binding(), wl)
     for h0 in range(0, wl.n_heads, 4):
         _check(wl, gpu, dev, heads=range(h0, h0 + 4))
+
+
+@pytest.mark.parametrize("frames", [17, 32, 33, 64, 65, 96, 97, 128, 129])
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_block_edges(frames, head_dim):
+    # the workgroup-per-sequence kernels hold 1 to 4 blocks of 32 frames: both ends of every size, the
+    # first length past them, and a short clip in the same call
+    wl = W.Workload(f"edge{frames}", ((frames, 1, 3), (5, 2, 1)), 2, head_dim, (0, head_dim // 2, head_dim // 2), seed=frames)
+    dev, gpu = _run(_binding(), wl)
+    _check(wl, gpu, dev)
