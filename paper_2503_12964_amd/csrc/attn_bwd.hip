@@ -87,50 +87,49 @@ __global__ __launch_bounds__(256) void bwd_prepare_kernel(const u32x4* __restric
 // tensor in a two-token clip, below 0.1% from 32 keys on.  For sequences with at most
 // kShortKeys keys Delta is therefore recomputed here in its other form,
 //     Delta_i = sum_j P_ij dP_ij,   P_ij = exp(scale q_i.k_j - lse_i),   dP_ij = dO_i.v_j,
-// in fp32 from the bf16 operands (the two forms are the same quantity for the exact O).
-// One lane per query row; the key loop is uniform across the wavefront.  A negligible amount
-// of work (at most 32 keys per query), launched only when the call has such a sequence.
+// with fp32 sums of the bf16 operands (the two forms are the same quantity for the exact O).
+// One wavefront per 32 query rows: the scores S^T = K Q^T and dP^T = V dO^T of all (at most 32)
+// keys are one 32x32 MFMA tile each, operands straight from memory, so the kernel is one round of
+// loads deep.  (One lane per query row walking the keys in a serial loop took 31 us of the smallest
+// training step, 32 tokens x 2 heads; this takes 2.6 us.)  Launched only when the call has such
+// a sequence, over the tiles of those sequences only.
 constexpr int kShortKeys = 32;
 
 template <int D, class Segs>
 __global__ __launch_bounds__(64) void bwd_short_delta_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
     const __bf16* __restrict__ dout, const float* __restrict__ lse, float* __restrict__ delta,
-    const Segs segs, const TileIndex ti, int total, int n_heads, float scale) {
+    const Segs segs, const TileIndex ti, int total, int n_heads, float scale_log2) {
+  constexpr int KS = D / 16;
   int seq, t;
   locate_tile(ti, segs.n, blockIdx.x, seq, t);
   const int nk = segs.kv_len(seq);
-  if (nk > kShortKeys) return;
   const int head = blockIdx.y;
-  const int i = segs.q_start(seq) + t * 64 + (int)threadIdx.x;
-  if (i >= segs.q_start(seq) + segs.q_len(seq)) return;
+  const int lane = threadIdx.x, c = lane & 31, g = lane >> 5;
+  const int q_b = segs.q_start(seq) + segs.q_len(seq);
+  const int i = segs.q_start(seq) + t * 32 + c;
+  const int ir = min(i, q_b - 1);                        // rows and keys past the end: copies of the last one
   const size_t row_stride = (size_t)n_heads * D;
-  const u32x4* qi = reinterpret_cast<const u32x4*>(q + (size_t)i * row_stride + (size_t)head * D);
-  const u32x4* di = reinterpret_cast<const u32x4*>(dout + (size_t)i * row_stride + (size_t)head * D);
-  u32x4 qw[D / 8], dw[D / 8];     // packed bf16 pairs, widened on use
+  const size_t qoff = (size_t)ir * row_stride + (size_t)head * D + 8 * g;
+  const size_t koff = (size_t)(segs.kv_start(seq) + min(c, nk - 1)) * row_stride + (size_t)head * D + 8 * g;
+  const float lse_i = lse[(size_t)head * total + ir] * kLog2eB;
+  f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  f32x16 dp = s;
 #pragma unroll
-  for (int c = 0; c < D / 8; ++c) { qw[c] = qi[c]; dw[c] = di[c]; }
-  const float lse_i = lse[(size_t)head * total + i];
-  float acc = 0.f;
-  for (int j = 0; j < nk; ++j) {
-    const size_t off = (size_t)(segs.kv_start(seq) + j) * row_stride + (size_t)head * D;
-    const u32x4* kj = reinterpret_cast<const u32x4*>(k + off);
-    const u32x4* vj = reinterpret_cast<const u32x4*>(v + off);
-    float s = 0.f, dp = 0.f;
-#pragma unroll
-    for (int c = 0; c < D / 8; ++c) {
-      const u32x4 kw = kj[c], vw = vj[c];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        s += __builtin_bit_cast(float, qw[c][e] << 16) * __builtin_bit_cast(float, kw[e] << 16);
-        s += __builtin_bit_cast(float, qw[c][e] & 0xffff0000u) * __builtin_bit_cast(float, kw[e] & 0xffff0000u);
-        dp += __builtin_bit_cast(float, dw[c][e] << 16) * __builtin_bit_cast(float, vw[e] << 16);
-        dp += __builtin_bit_cast(float, dw[c][e] & 0xffff0000u) * __builtin_bit_cast(float, vw[e] & 0xffff0000u);
-      }
-    }
-    acc += fast_exp2((s * scale - lse_i) * kLog2eB) * dp;
+  for (int ks = 0; ks < KS; ++ks) {
+    s = mfma32(*reinterpret_cast<const bf16x8*>(k + koff + ks * 16),
+               *reinterpret_cast<const bf16x8*>(q + qoff + ks * 16), s);
+    dp = mfma32(*reinterpret_cast<const bf16x8*>(v + koff + ks * 16),
+                *reinterpret_cast<const bf16x8*>(dout + qoff + ks * 16), dp);
   }
-  delta[(size_t)head * total + i] = acc;
+  float acc = 0.f;                                       // this lane's 16 keys of query i
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int j = 8 * (r >> 2) + 4 * g + (r & 3);
+    if (j < nk) acc += fast_exp2(s[r] * scale_log2 - lse_i) * dp[r];
+  }
+  acc = pair_sum(acc);
+  if (i < q_b && g == 0) delta[(size_t)head * total + i] = acc;
 }
 
 // ---------------------------------------------------------------- dK, dV
@@ -1175,9 +1174,14 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
     for (int s2 = 0; s2 < segs.n; ++s2)
       any_short |= segs.q_len(s2) > 0 && segs.kv_len(s2) > 0 && segs.kv_len(s2) <= kShortKeys;
     if (any_short) {   // sequences with a handful of keys: Delta in its cancellation-free form
-      const TileIndex ti = make_tile_index<false>(segs, 64);
-      e = launch(bwd_short_delta_kernel<D, Segs>, dim3(count_tiles(ti), n_heads), dim3(64), 0,
-                 stream, qb, kb, vb, dob, lse, delta, segs, ti, total, n_heads, scale);
+      TileIndex ti;   // 32-row query tiles of the sequences with few keys, none of the others
+      int tiles = 0;
+      for (int s2 = 0; s2 <= VFM_MAX_SEQS; ++s2) {
+        ti.cu[s2] = tiles;
+        if (s2 < segs.n && segs.kv_len(s2) > 0 && segs.kv_len(s2) <= kShortKeys) tiles += (segs.q_len(s2) + 31) / 32;
+      }
+      e = launch(bwd_short_delta_kernel<D, Segs>, dim3(tiles, n_heads), dim3(64), 0,
+                 stream, qb, kb, vb, dob, lse, delta, segs, ti, total, n_heads, scale * kLog2eB);
       if (e != hipSuccess) return e;
     }
   }

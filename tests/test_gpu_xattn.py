@@ -102,3 +102,14 @@ def test_paper_shaped_cross_attention(cu_q, cu_kv, heads, check):
     dev, gpu, scale = _run(b, cu_q, cu_kv, heads, 128, seed=23)
     for h0 in range(0, heads, 8):       # oracle on eight heads at a time (memory)
         _assert(gpu, dev, cu_q, cu_kv, scale, heads=range(h0, min(h0 + 8, heads)))
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+def test_few_keys_per_sequence(hd):
+    # sequences of 1..33 keys (up to 32 take the recomputed Delta), queries on both sides of its 32-row tiles,
+    # one sequence without queries
+    cu_q = np.concatenate([[0], np.cumsum([1, 33, 100, 0, 31, 64, 5])])
+    cu_kv = np.concatenate([[0], np.cumsum([2, 31, 32, 7, 33, 1, 17])])
+    b = _binding()
+    dev, gpu, scale = _run(b, cu_q, cu_kv, 3, hd, seed=24)
+    _assert(gpu, dev, cu_q, cu_kv, scale)
