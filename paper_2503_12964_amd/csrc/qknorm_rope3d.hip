@@ -53,7 +53,7 @@ template <int D>
 __global__ __launch_bounds__(256) void qknorm_rope3d_kernel(const u32x4* x, u32x4* y,
                                                             const float* __restrict__ gain, float eps,
                                                             const RopeTable tab, const RopeFreq fr,
-                                                            int tok0, int tok_end, int n_heads) {
+                                                            int tok0, int tok_end, int n_heads, int heads_per_block) {
   constexpr int kLanesPerTok = D / 8;
   constexpr int kTokPerBlock = 256 / kLanesPerTok;
   const int tok = tok0 + blockIdx.x * kTokPerBlock + threadIdx.x / kLanesPerTok;   // the clips of tab
@@ -68,14 +68,15 @@ __global__ __launch_bounds__(256) void qknorm_rope3d_kernel(const u32x4* x, u32x
 
   const size_t base = ((size_t)tok * n_heads) * kLanesPerTok + chunk;
   constexpr int kUnroll = 4;
-  for (int h0 = 0; h0 < n_heads; h0 += kUnroll) {
+  const int h_begin = blockIdx.y * heads_per_block, h_end = min(n_heads, h_begin + heads_per_block);
+  for (int h0 = h_begin; h0 < h_end; h0 += kUnroll) {
     u32x4 v[kUnroll];
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u)
-      if (h0 + u < n_heads) v[u] = __builtin_nontemporal_load(x + base + (size_t)(h0 + u) * kLanesPerTok);
+      if (h0 + u < h_end) v[u] = __builtin_nontemporal_load(x + base + (size_t)(h0 + u) * kLanesPerTok);
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
-      if (h0 + u >= n_heads) break;     // uniform over the workgroup
+      if (h0 + u >= h_end) break;     // uniform over the workgroup
       float f[8];
       unpack8(v[u], f);
       float ss = 0.f;
@@ -100,15 +101,23 @@ __global__ void zero_f32_kernel(float* p, int n) {
   if (i < n) p[i] = 0.f;
 }
 
+// A work item is one slice of a token's heads.  Workgroups are large and few (one per CU, looping) because
+// each ends in one atomic per element of dgain: with 256 threads per workgroup and up to 4,096 of
+// them, the atomics on the same 64 or 128 addresses took a good part of a small call
+// (8,192 tokens x 16 heads x 128: 32.5 -> 23.6 us, 4.3 TB/s; 56,320 x 32 x 128 stays at 271 us, 5.1 TB/s).
+constexpr int kQkBwdThreads = 1024;
+constexpr int kQkBwdMaxGrid = 256;
+
 template <int D>
-__global__ __launch_bounds__(256) void qknorm_rope3d_bwd_kernel(const u32x4* __restrict__ x,
-                                                                const u32x4* dy, u32x4* dx,
-                                                                const float* __restrict__ gain, float eps,
-                                                                float* __restrict__ dgain,
-                                                                const RopeTable tab, const RopeFreq fr,
-                                                                int tok0, int tok_end, int n_heads) {
+__global__ __launch_bounds__(kQkBwdThreads) void qknorm_rope3d_bwd_kernel(const u32x4* __restrict__ x,
+                                                                          const u32x4* dy, u32x4* dx,
+                                                                          const float* __restrict__ gain, float eps,
+                                                                          float* __restrict__ dgain,
+                                                                          const RopeTable tab, const RopeFreq fr,
+                                                                          int tok0, int n_items, int slices,
+                                                                          int heads_per_slice, int n_heads) {
   constexpr int kLanesPerTok = D / 8;
-  constexpr int kTokPerBlock = 256 / kLanesPerTok;
+  constexpr int kTokPerBlock = kQkBwdThreads / kLanesPerTok;   // items per pass
   __shared__ float red[kTokPerBlock][D];
   const int group = threadIdx.x / kLanesPerTok;
   const int chunk = threadIdx.x % kLanesPerTok;
@@ -118,22 +127,24 @@ __global__ __launch_bounds__(256) void qknorm_rope3d_bwd_kernel(const u32x4* __r
   for (int e = 0; e < 8; ++e) { g[e] = gain[chunk * 8 + e]; dg[e] = 0.f; }
 
   // whole groups iterate together; nobody returns before the barrier below
-  for (int tok = tok0 + blockIdx.x * kTokPerBlock + group; tok < tok_end; tok += gridDim.x * kTokPerBlock) {
+  for (int item = blockIdx.x * kTokPerBlock + group; item < n_items; item += gridDim.x * kTokPerBlock) {
+    const int tok = tok0 + item / slices;
+    const int h_begin = (item % slices) * heads_per_slice, h_end = min(n_heads, h_begin + heads_per_slice);
     float cs[4], sn[4];
     rope_cos_sin(tab, fr, tok, chunk, 1, cs, sn);   // transpose rotation
     const size_t base = ((size_t)tok * n_heads) * kLanesPerTok + chunk;
     constexpr int kUnroll = 2;
-    for (int h0 = 0; h0 < n_heads; h0 += kUnroll) {
+    for (int h0 = h_begin; h0 < h_end; h0 += kUnroll) {
       u32x4 xv[kUnroll], gv[kUnroll];
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u)
-        if (h0 + u < n_heads) {
+        if (h0 + u < h_end) {
           xv[u] = __builtin_nontemporal_load(x + base + (size_t)(h0 + u) * kLanesPerTok);
           gv[u] = __builtin_nontemporal_load(dy + base + (size_t)(h0 + u) * kLanesPerTok);
         }
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
-        if (h0 + u >= n_heads) break;   // uniform over the workgroup
+        if (h0 + u >= h_end) break;   // uniform over the group
         float f[8], d[8];
         unpack8(xv[u], f);
         unpack8(gv[u], d);
@@ -170,7 +181,7 @@ __global__ __launch_bounds__(256) void qknorm_rope3d_bwd_kernel(const u32x4* __r
 #pragma unroll
   for (int e = 0; e < 8; ++e) red[group][chunk * 8 + e] = dg[e];
   __syncthreads();
-  for (int d = threadIdx.x; d < D; d += 256) {
+  for (int d = threadIdx.x; d < D; d += kQkBwdThreads) {
     float s = 0.f;
 #pragma unroll
     for (int t = 0; t < kTokPerBlock; ++t) s += red[t][d];
@@ -184,11 +195,11 @@ hipError_t launch_qknorm_rope3d(const void* x, void* y, const float* gain, float
   const int tok0 = tab.cu[0], tok_end = tab.cu[tab.n], count = tok_end - tok0;
   if (count == 0) return hipSuccess;
   const RopeFreq fr = make_rope_freq(dim_t, dim_h, dim_w, theta);
-  if (head_dim == 128)
-    return launch(qknorm_rope3d_kernel<128>, dim3((count + 15) / 16), dim3(256), 0, stream, (const u32x4*)x,
-                  (u32x4*)y, gain, eps, tab, fr, tok0, tok_end, n_heads);
-  return launch(qknorm_rope3d_kernel<64>, dim3((count + 31) / 32), dim3(256), 0, stream, (const u32x4*)x,
-                (u32x4*)y, gain, eps, tab, fr, tok0, tok_end, n_heads);
+  const int blocks = head_dim == 128 ? (count + 15) / 16 : (count + 31) / 32;
+  const int hpb = rope_heads_per_block(blocks, n_heads);
+  auto kern = head_dim == 128 ? qknorm_rope3d_kernel<128> : qknorm_rope3d_kernel<64>;
+  return launch(kern, dim3(blocks, (n_heads + hpb - 1) / hpb), dim3(256), 0, stream, (const u32x4*)x, (u32x4*)y, gain,
+                eps, tab, fr, tok0, tok_end, n_heads, hpb);
 }
 
 hipError_t launch_zero_f32(float* p, int n, hipStream_t stream) {
@@ -203,15 +214,15 @@ hipError_t launch_qknorm_rope3d_bwd(const void* x, const void* dy, void* dx, con
   const int tok0 = tab.cu[0], tok_end = tab.cu[tab.n], count = tok_end - tok0;
   if (count == 0) return hipSuccess;
   const RopeFreq fr = make_rope_freq(dim_t, dim_h, dim_w, theta);
-  constexpr int kMaxGrid = 4096;   // bounds the number of atomics; more tokens loop
-  if (head_dim == 128) {
-    const int grid = min((count + 15) / 16, kMaxGrid);
-    return launch(qknorm_rope3d_bwd_kernel<128>, dim3(grid), dim3(256), 0, stream, (const u32x4*)x,
-                  (const u32x4*)dy, (u32x4*)dx, gain, eps, dgain, tab, fr, tok0, tok_end, n_heads);
-  }
-  const int grid = min((count + 31) / 32, kMaxGrid);
-  return launch(qknorm_rope3d_bwd_kernel<64>, dim3(grid), dim3(256), 0, stream, (const u32x4*)x,
-                (const u32x4*)dy, (u32x4*)dx, gain, eps, dgain, tab, fr, tok0, tok_end, n_heads);
+  // slices: as many as it takes to give every group of the full grid an item, each of at least two heads
+  const int groups = kQkBwdThreads / (head_dim / 8);
+  const int want = min((kQkBwdMaxGrid * groups + count - 1) / count, (n_heads + 1) / 2);
+  const int per = (n_heads + want - 1) / want, slices = (n_heads + per - 1) / per;
+  const int n_items = count * slices;   // (count * n_heads * head_dim fits 31 bits)
+  const int grid = min((n_items + groups - 1) / groups, kQkBwdMaxGrid);
+  auto kern = head_dim == 128 ? qknorm_rope3d_bwd_kernel<128> : qknorm_rope3d_bwd_kernel<64>;
+  return launch(kern, dim3(grid), dim3(kQkBwdThreads), 0, stream, (const u32x4*)x, (const u32x4*)dy, (u32x4*)dx, gain,
+                eps, dgain, tab, fr, tok0, n_items, slices, per, n_heads);
 }
 
 }  // namespace vfm

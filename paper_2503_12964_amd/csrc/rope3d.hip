@@ -4,7 +4,7 @@
 // chunk c of every head vector of that token (four adjacent pairs).  The four
 // (cos, sin) values a lane needs depend on the token and on c only, so they are
 // computed once (angle reduced in fp64, then sincosf) and reused for all
-// heads.  A wavefront therefore moves 256-byte contiguous head rows; every byte
+// heads of the workgroup's slice (all of them, unless the call is too small to fill the chip).  A wavefront therefore moves 256-byte contiguous head rows; every byte
 // of x is read once and written once.
 #include "rope_common.h"
 
@@ -13,7 +13,7 @@ namespace vfm {
 template <int D>
 __global__ __launch_bounds__(256) void rope3d_kernel(u32x4* __restrict__ x, const RopeTable tab,
                                                      const RopeFreq fr, int tok0, int tok_end,
-                                                     int n_heads, int inverse) {
+                                                     int n_heads, int heads_per_block, int inverse) {
   // tokens [tok0, tok_end): the clips of tab (a call with more clips than a table holds is cut
   // into consecutive launches over runs of clips)
   constexpr int kLanesPerTok = D / 8;
@@ -27,8 +27,9 @@ __global__ __launch_bounds__(256) void rope3d_kernel(u32x4* __restrict__ x, cons
 
   u32x4* row = x + ((size_t)tok * n_heads) * kLanesPerTok + chunk;
   constexpr int kUnroll = 4;
-  int h = 0;
-  for (; h + kUnroll <= n_heads; h += kUnroll) {
+  int h = blockIdx.y * heads_per_block;
+  const int h_end = min(n_heads, h + heads_per_block);
+  for (; h + kUnroll <= h_end; h += kUnroll) {
     u32x4 v[kUnroll];
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) v[u] = __builtin_nontemporal_load(row + (size_t)(h + u) * kLanesPerTok);
@@ -47,7 +48,7 @@ __global__ __launch_bounds__(256) void rope3d_kernel(u32x4* __restrict__ x, cons
       __builtin_nontemporal_store(o, row + (size_t)(h + u) * kLanesPerTok);
     }
   }
-  for (; h < n_heads; ++h) {
+  for (; h < h_end; ++h) {
     const u32x4 v = row[(size_t)h * kLanesPerTok];
     u32x4 o;
 #pragma unroll
@@ -69,11 +70,11 @@ hipError_t launch_rope3d(void* x, const RopeTable& tab, int n_heads, int head_di
   const RopeFreq fr = make_rope_freq(dim_t, dim_h, dim_w, theta);
   const int tok0 = tab.cu[0], tok_end = tab.cu[tab.n], count = tok_end - tok0;
   if (count == 0) return hipSuccess;
-  if (head_dim == 128)
-    return launch(rope3d_kernel<128>, dim3((count + 15) / 16), dim3(256), 0, stream, (u32x4*)x, tab, fr, tok0,
-                  tok_end, n_heads, inverse);
-  return launch(rope3d_kernel<64>, dim3((count + 31) / 32), dim3(256), 0, stream, (u32x4*)x, tab, fr, tok0,
-                tok_end, n_heads, inverse);
+  const int blocks = head_dim == 128 ? (count + 15) / 16 : (count + 31) / 32;
+  const int hpb = rope_heads_per_block(blocks, n_heads);
+  const dim3 grid(blocks, (n_heads + hpb - 1) / hpb);
+  auto kern = head_dim == 128 ? rope3d_kernel<128> : rope3d_kernel<64>;
+  return launch(kern, grid, dim3(256), 0, stream, (u32x4*)x, tab, fr, tok0, tok_end, n_heads, hpb, inverse);
 }
 
 }  // namespace vfm

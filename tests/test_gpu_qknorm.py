@@ -119,3 +119,25 @@ def test_full_size_c4_every_element():
         assert np.sqrt(err2[key] / ref2[key]) <= TOL_RELRMS
     dg = U.to_f64(dgain)
     assert np.max(np.abs(dg - dg_ref)) <= TOL_DGAIN_REL * np.abs(dg_ref).max()
+
+
+@pytest.mark.parametrize("grids,heads,hd", [
+    (((1, 1, 1),), 1, 128),                          # one token: a single item
+    (((1, 3, 5), (0, 1, 1), (1, 1, 2)), 5, 64),      # slices of two heads, the last one short
+    (((1, 7, 43),), 33, 128),                        # a head count no slice size divides
+    (((4, 65, 64),), 3, 128),                        # more items than groups: workgroups loop
+])
+def test_head_slices(grids, heads, hd):
+    # every cut of the heads over workgroups (encode) and over items (backward), against the oracle
+    wl = W.Workload("head_slices", grids, heads, hd, (hd // 4, 3 * hd // 8, 3 * hd // 8), seed=31)
+    b = _binding()
+    xb, dyb, gain, gain_d = _inputs(wl)
+    x64, args = U.bits_to_f64(xb), (wl.thw, wl.cu_seqlens, wl.rope_dims, wl.theta)
+    y = b.vfm_qknorm_rope3d(U.to_device(xb), gain_d, EPS, *args)
+    r = b.vfm_rope3d(U.to_device(xb), *args)
+    dx, dgain = b.vfm_qknorm_rope3d_bwd(U.to_device(xb), gain_d, EPS, U.to_device(dyb), *args)
+    dx_ref, dg_ref = orc.qknorm_rope3d_bwd(x64, gain, EPS, U.bits_to_f64(dyb), *args)
+    for got, want in ((y, orc.qknorm_rope3d(x64, gain, EPS, *args)), (r, orc.rope3d(x64, *args)), (dx, dx_ref)):
+        _elementwise_ok(U.to_f64(got), want, np.abs(want).max())
+    # a sum of n = tokens * heads fp32 terms, in lanes, LDS and atomics: far below the relative bound of the sum itself
+    assert np.max(np.abs(U.to_f64(dgain) - dg_ref)) <= TOL_DGAIN_REL * np.abs(dg_ref).max()
