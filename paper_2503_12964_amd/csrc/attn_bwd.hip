@@ -1,6 +1,7 @@
 // Packed variable-length attention backward for gfx950 (bf16 MFMA, fp32 accumulate).
 //
-// Three kernels, no atomics (device-wide fp32 atomics are executed at the memory side on
+// Clips of at most 256 tokens: one kernel (attn_bwd_fused_kernel, further down), one workgroup per (clip,
+// head).  Longer ones: three kernels, no atomics (device-wide fp32 atomics are executed at the memory side on
 // this chip and were measured to bound the fused variant), so every output is written
 // once and the result is bitwise reproducible:
 //   bwd_prepare : Delta[h,i] = sum_d dO[i,h,d] O[i,h,d],  lse2 = lse * log2(e), and two
@@ -21,6 +22,7 @@
 //                 S and dP are recomputed here (7 GEMMs in total instead of 5).
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 #include "vfm_common.h"
 
@@ -1145,6 +1147,366 @@ void attn_bwd_both_kernel(const __bf16* __restrict__ q, const __bf16* __restrict
                           t - key_tiles);
 }
 
+// ---------------------------------------------------------------- sequences of up to 256 tokens: one pass
+// Self-attention over clips of at most kFusedMaxRows tokens: one workgroup owns a whole (clip, head), so
+// that the five products of the backward are formed once (the two passes above form seven), every
+// operand comes from memory once and Delta needs no pass of its own.  What bounds such packs is the
+// memory path (eight tensors of the clip against 10 D flops per pair of few pairs).
+//   prologue: K into LDS, V rows into registers, Delta and lse in log2 units of all rows into LDS
+//             (out and dO straight from memory; dO is read again below while it is in L2)
+//   per block b of 32 query rows (Q, dO in a ring of three LDS stages, requested two blocks ahead; two stages where that lets two
+//   workgroups share a CU):
+//     phase 1  dQ(b-1) = dS(b-1) K, every wavefront 32 columns over all keys, to memory;
+//              S(b) = Q K^T, dP(b) = dO V^T, P, dS of the wavefront's own 32 keys
+//     barrier
+//     phase 2  dS(b) to LDS, key-major; dV^T += dO^T P, dK^T += Q^T dS
+//     barrier
+// dS is written in phase 2 and read in phase 1 only, so it needs no second copy.  Keys past the clip's end
+// have dS = 0; query rows past it P = 0 (lse = +inf).  Four wavefronts serve 128 tokens in 73 KB of LDS (49 at
+// head_dim 64), so that two workgroups share a CU and one's loads and stores meet the other's products;
+// eight serve 256 tokens, at head_dim 128 one workgroup per CU.  Everything the loop could recompute it does
+// (opaque offsets): one spilled register tuple read back in the loop waits for the loads in flight.
+// Whole backward call, statistics pass included, 256 clips x 32 heads, two-pass kernels -> this one:
+// 256 tokens 1641 -> 1309 us (3.3 TB/s of the eight tensors), 128 tokens 822 -> 467, 64 tokens 555 -> 271,
+// 16 tokens 739 -> 135; head_dim 64, 256 tokens 1094 -> 766, 128 tokens 497 -> 253.
+template <int D, int NW>
+struct FusedCfg {
+  static constexpr int kRows = NW * 32;                      // longest clip
+  static constexpr int kBlockBytes = 32 * D * 2;             // 32 rows of one tensor
+  static constexpr int kRing = D == 128 && NW == 4 ? 2 : 3;  // stages of (Q, dO) blocks
+  static constexpr int kRingBase = kRows * D * 2;            // K first
+  static constexpr int kDsBase = kRingBase + kRing * 2 * kBlockBytes;
+  static constexpr int kStatBase = kDsBase + kRows * 64;     // dS: [key][32 queries] bf16; then lse2, Delta
+  static constexpr int kLdsBytes = kStatBase + 2 * kRows * 4;
+  static constexpr int kLoads = D / 8 / NW;                  // wave loads per block (Q and dO together)
+};
+
+template <int D, int NW>
+__global__ __launch_bounds__(NW * 64, 2)
+void attn_bwd_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
+                           const __bf16* __restrict__ v, const __bf16* __restrict__ out,
+                           const float* __restrict__ lse, const __bf16* __restrict__ dout,
+                           __bf16* __restrict__ dq, __bf16* __restrict__ dk, __bf16* __restrict__ dv,
+                           const SegTable segs, const UnitMap um, int total, int n_heads, float scale,
+                           float scale_log2) {
+  using Cfg = FusedCfg<D, NW>;
+  constexpr int KS = D / 16, DB = D / 32, CPR = D / 8, RB = D * 2;
+  constexpr int BB = Cfg::kBlockBytes;
+  constexpr int NT = NW * 64;
+
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+
+  // units run over the heads of a clip first: workgroups side by side read neighbouring columns
+  int seq, head;
+  if (!map_unit(um, blockIdx.x, seq, head)) return;
+  const int a = segs.start[seq], n = segs.len[seq];
+  const int n_blk = (n + 31) / 32;
+
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, c = lane & 31, g = lane >> 5;
+  const size_t row_stride = (size_t)n_heads * D;
+  const size_t clip_off = (size_t)a * row_stride + (size_t)head * D;
+  const uint32_t row_bytes = (uint32_t)row_stride * 2u;
+  const uint32_t smem_addr = lds_addr_of(smem);
+
+  // ---- K rows to LDS (rows past the end: copies of the last one; blocks without a row are left out)
+  const __bf16* kbase = k + clip_off;
+#pragma unroll
+  for (int x = 0; x < CPR / 2; ++x) {
+    const int p = (x * NW + wave) * 64 + lane;
+    const int r = p / CPR;
+    if ((x * NW + wave) * 64 / CPR < n_blk * 32)
+      lds_dma16(kbase, (uint32_t)min(r, n - 1) * row_bytes + (uint32_t)(((p % CPR) ^ swz<D>(r)) * 16),
+                __builtin_amdgcn_readfirstlane(smem_addr + (x * NW + wave) * 1024));
+  }
+
+  // ---- blocks of Q and dO: wave instruction i of a block fills 1 KB, the first half of them Q
+  const int jrow = wave * 32 + c;                 // this lane's key, relative to the clip
+  const bool active = wave * 32 < n;              // (wave-uniform) some key of the wavefront exists
+  const __bf16* src[Cfg::kLoads];
+  uint32_t st_colb[Cfg::kLoads], st_lds[Cfg::kLoads];
+  int st_row[Cfg::kLoads];
+#pragma unroll
+  for (int x = 0; x < Cfg::kLoads; ++x) {
+    const int i = x * NW + wave;
+    const int p = (i % (CPR / 2)) * 64 + lane;
+    const int r = p / CPR;
+    src[x] = uniform_ptr((i < CPR / 2 ? q : dout) + clip_off);
+    st_row[x] = r;
+    st_colb[x] = (uint32_t)(((p % CPR) ^ swz<D>(r)) * 16);
+    st_lds[x] = __builtin_amdgcn_readfirstlane(smem_addr + Cfg::kRingBase + i * 1024);
+  }
+  auto issue_block = [&](int stage) {   // strictly in order; blocks past the end re-read the last row
+#pragma unroll
+    for (int x = 0; x < Cfg::kLoads; ++x) {
+      lds_dma16(src[x], (uint32_t)min(st_row[x], n - 1) * row_bytes + st_colb[x], st_lds[x] + stage * 2 * BB);
+      st_row[x] += 32;
+    }
+  };
+  issue_block(0);
+  issue_block(1);
+
+  // ---- V rows as B operand
+  bf16x8 vreg[KS];
+  {
+    const __bf16* vp = v + clip_off + (size_t)min(jrow, n - 1) * row_stride + 8 * g;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) vreg[ks] = *reinterpret_cast<const bf16x8*>(vp + ks * 16);
+  }
+  // ---- statistics of all rows: CPR lanes per row, all loads in flight before the first sum
+  float* lse_s = reinterpret_cast<float*>(smem + Cfg::kStatBase);
+  float* delta_s = lse_s + Cfg::kRows;
+  {
+    constexpr int RP = NT / CPR, PASSES = Cfg::kRows / RP;
+    static_assert(Cfg::kRows <= NT, "one thread per row for lse");
+    u32x4 oa[PASSES], da[PASSES];
+    const int chunk = tid % CPR;
+    const float lse_r = lse[(size_t)head * total + a + min(tid, n - 1)];
+#pragma unroll
+    for (int i = 0; i < PASSES; ++i) {   // (rows past the end: copies of the last one, no branch between the loads)
+      const size_t off = clip_off + (size_t)min(i * RP + tid / CPR, n - 1) * row_stride + chunk * 8;
+      oa[i] = *reinterpret_cast<const u32x4*>(out + off);
+      da[i] = *reinterpret_cast<const u32x4*>(dout + off);
+    }
+    if (tid < Cfg::kRows) lse_s[tid] = tid < n ? lse_r * kLog2eB : INFINITY;
+#pragma unroll
+    for (int i = 0; i < PASSES; ++i) {
+      const int r = i * RP + tid / CPR;
+      float s = 0.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        s += __builtin_bit_cast(float, oa[i][e] << 16) * __builtin_bit_cast(float, da[i][e] << 16);
+        s += __builtin_bit_cast(float, oa[i][e] & 0xffff0000u) * __builtin_bit_cast(float, da[i][e] & 0xffff0000u);
+      }
+#pragma unroll
+      for (int o = CPR / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, CPR);
+      if (chunk == 0) delta_s[r] = r < n ? s : 0.f;
+    }
+  }
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) settle(vreg[ks]);
+
+  // ---- per-lane LDS offsets (see the dK/dV unit for the first two)
+  const int rbase = tile_off<D>(c, 8 * g);
+  int tbase[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+    tbase[t] = tile_off<D>(8 * t + 4 * g + ((lane & 15) >> 2), 16 * ((lane >> 4) & 1) + 4 * (lane & 3));
+  const char* kt = smem + wave * 32 * RB;
+  // dS rows are 64 bytes, 16-byte chunk x of key j kept at x ^ (j/4 mod 4)
+  // dQ: 16x16x32 products over 32 keys.  This wavefront's part of the 32 x D block: 32 columns, and one or
+  // both of the 16-row halves
+  constexpr int NROW = D / 32 >= NW ? 2 : 1;
+  const int col0 = (wave % (D / 32)) * 32, half0 = NROW == 2 ? 0 : wave / (D / 32);
+  const bool dq_part = half0 < 2;                          // (head_dim 64 has two parts per half only)
+  auto block_dq = [&](int blk, int rows_valid) {           // dQ of block blk, whose dS is in LDS -> memory
+    f32x4 acc[2][NROW];
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int h = 0; h < NROW; ++h) acc[x][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // contraction slot 4t + r of lane group l/16: key 8 (l/16) + 4t + r of a block of 32
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    int ktr[2], dtr[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int row = 8 * (ln >> 4) + 4 * t + ((ln & 15) >> 2);
+      ktr[t] = tile_off<D>(row, col0 + 4 * (ln & 3));
+      dtr[t] = Cfg::kDsBase + row * 64 + (((half0 * 2 + ((ln & 3) >> 1)) ^ ((row >> 2) & 3)) << 4) + (ln & 1) * 8;
+    }
+    // the next block's operands are read ahead of this block's products
+    bf16x8 kf[2][2], df[2][NROW];
+    auto read = [&](int kk, bf16x8 (&kr)[2], bf16x8 (&dr)[NROW]) {
+      const char* kb = smem + kk * 32 * RB;
+      const char* db = smem + kk * 32 * 64;
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+        kr[x] = join_tr(lds_read_tr(kb, ktr[0] ^ (x * 32)), lds_read_tr(kb, ktr[1] ^ (x * 32)));
+#pragma unroll
+      for (int h = 0; h < NROW; ++h)
+        dr[h] = join_tr(lds_read_tr(db, dtr[0] ^ (h * 32)), lds_read_tr(db, dtr[1] ^ (h * 32)));
+    };
+    auto mul = [&](bf16x8 (&kr)[2], bf16x8 (&dr)[NROW]) {
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int h = 0; h < NROW; ++h)
+          acc[x][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kr[x], dr[h], acc[x][h], 0, 0, 0);
+    };
+    if constexpr (NROW == 2) {   // (no registers left for a second set; the CU's other workgroup fills the gaps)
+      for (int kk = 0; kk < n_blk; ++kk) {
+        read(kk, kf[0], df[0]);
+        mul(kf[0], df[0]);
+      }
+    } else {
+      read(0, kf[0], df[0]);
+      for (int kk = 0; kk < n_blk; kk += 2) {
+        if (kk + 1 < n_blk) read(kk + 1, kf[1], df[1]);
+        mul(kf[0], df[0]);
+        if (kk + 1 >= n_blk) break;
+        if (kk + 2 < n_blk) read(kk + 2, kf[0], df[0]);
+        mul(kf[1], df[1]);
+      }
+    }
+    // a lane holds 4 columns of row l%16 in either 16-column product; exchanging 16-lane rows between the
+    // two leaves it 8 columns of one, so that a store writes 64 contiguous bytes of each row
+#pragma unroll
+    for (int h = 0; h < NROW; ++h) {
+      u32x2 w[2];
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        f32x4 f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f[e] = acc[x][h][e] * scale;
+        w[x] = __builtin_bit_cast(u32x2, to_bf16x4(f));
+      }
+      u32x4 o;
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        auto r = __builtin_amdgcn_permlane16_swap(w[0][e], w[1][e], false, false);
+        o[e] = r[0];
+        o[2 + e] = r[1];
+      }
+      const int row = (half0 + h) * 16 + (ln & 15), col = col0 + 16 * ((ln >> 4) & 1) + 8 * (ln >> 5);
+      if (row < rows_valid)
+        *reinterpret_cast<u32x4*>(dq + clip_off + (size_t)(blk * 32 + row) * row_stride + col) = o;
+    }
+  };
+
+  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  f32x16 dkacc[DB], dvacc[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db) { dkacc[db] = zero16; dvacc[db] = zero16; }
+
+  const uint32_t key_mask = jrow < n ? 0xffffffffu : 0u;
+  // the two wavefronts of a SIMD run phase 1 in different orders, so that one's matrix
+  // instructions meet the other's exponentials
+  const bool late_dq = NW == 8 && wave >= 4;
+  wait_vmcnt<0>();          // K, the first two blocks
+  int stage = 0;            // b mod 3
+  for (int b = 0; b < n_blk; ++b) {
+    // block b has landed (only block b+1's loads may be outstanding; dq stores only make the wait
+    // stricter), everyone is done with block b-1, dS(b-1) is complete
+    wait_vmcnt<(Cfg::kRing - 2) * Cfg::kLoads>();
+    __syncthreads();
+    const char* qt = smem + Cfg::kRingBase + stage * 2 * BB;
+    if (Cfg::kRing == 3 || b > 0) issue_block(stage == 0 ? Cfg::kRing - 1 : stage - 1);
+    stage = stage == Cfg::kRing - 1 ? 0 : stage + 1;
+    if (b > 0 && !late_dq && dq_part) block_dq(b - 1, 32);
+    bf16x8 pb[2], dsb[2];
+    if (active) {
+      // (offsets recomputed per block on purpose: held in registers they would push V out of them)
+      int ro = rbase;
+      asm volatile("" : "+v"(ro));
+      f32x16 s = zero16, dp = zero16;
+      bf16x8 qa[2], ka[2], da[2];
+      auto rows = [&](int ks) {
+        qa[ks & 1] = lds_read_b128(qt, ro ^ (ks << 5));
+        ka[ks & 1] = lds_read_b128(kt, ro ^ (ks << 5));
+        da[ks & 1] = lds_read_b128(qt + BB, ro ^ (ks << 5));
+      };
+      rows(0);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        if (ks + 1 < KS) rows(ks + 1);
+        s = mfma32(qa[ks & 1], ka[ks & 1], s);
+        dp = mfma32(da[ks & 1], vreg[ks], dp);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      f32x16 p, dl;
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const f32x4 l4 = *reinterpret_cast<const f32x4*>(lse_s + b * 32 + 8 * q4 + 4 * g);
+        const f32x4 d4 = *reinterpret_cast<const f32x4*>(delta_s + b * 32 + 8 * q4 + 4 * g);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          p[q4 * 4 + e] = fast_exp2(s[q4 * 4 + e] * scale_log2 - l4[e]);
+          dl[q4 * 4 + e] = d4[e];
+        }
+      }
+      if (n <= kShortKeys) {   // few keys: Delta in its cancellation-free form, sum_j P_ij dP_ij
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          float x = jrow < n ? p[r] * dp[r] : 0.f;
+#pragma unroll
+          for (int o = 1; o < 32; o <<= 1) x += __shfl_xor(x, o, 32);
+          dl[r] = x;
+        }
+      }
+#pragma unroll
+      for (int s2 = 0; s2 < 2; ++s2) {
+        f32x8 pf, df;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          pf[e] = p[8 * s2 + e];
+          df[e] = pf[e] * (dp[8 * s2 + e] - dl[8 * s2 + e]);
+        }
+        pb[s2] = to_bf16x8(pf);
+        u32x4 w = __builtin_bit_cast(u32x4, to_bf16x8(df));   // keys past the end: zero
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] &= key_mask;
+        dsb[s2] = __builtin_bit_cast(bf16x8, w);
+      }
+    }
+    if (b > 0 && late_dq && dq_part) block_dq(b - 1, 32);
+    __syncthreads();   // everyone has read dS(b-1)
+    if (active) {
+      int j = jrow;
+      asm volatile("" : "+v"(j));
+      char* ds_w = smem + Cfg::kDsBase + j * 64 + 8 * g;
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const bf16x8 d = dsb[q4 >> 1];
+        const bf16x4 w = (q4 & 1) ? __builtin_shufflevector(d, d, 4, 5, 6, 7) : __builtin_shufflevector(d, d, 0, 1, 2, 3);
+        *reinterpret_cast<bf16x4*>(ds_w + ((q4 ^ ((j >> 2) & 3)) << 4)) = w;
+      }
+      int t0 = tbase[0], t1 = tbase[1];
+      asm volatile("" : "+v"(t0), "+v"(t1));
+      s16x4 tr[2][4];
+      auto cols = [&](int i) {
+        const int o0 = (t0 ^ ((i % DB) << 6)) + 16 * (i / DB) * RB, o1 = (t1 ^ ((i % DB) << 6)) + 16 * (i / DB) * RB;
+        tr[i & 1][0] = lds_read_tr(qt + BB, o0);
+        tr[i & 1][1] = lds_read_tr(qt + BB, o1);
+        tr[i & 1][2] = lds_read_tr(qt, o0);
+        tr[i & 1][3] = lds_read_tr(qt, o1);
+      };
+      cols(0);
+#pragma unroll
+      for (int i = 0; i < 2 * DB; ++i) {
+        if (i + 1 < 2 * DB) cols(i + 1);
+        dvacc[i % DB] = mfma32(join_tr(tr[i & 1][0], tr[i & 1][1]), pb[i / DB], dvacc[i % DB]);
+        dkacc[i % DB] = mfma32(join_tr(tr[i & 1][2], tr[i & 1][3]), dsb[i / DB], dkacc[i % DB]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  wait_vmcnt<0>();   // no load may still be writing LDS when the workgroup ends
+  __syncthreads();
+  if (dq_part) block_dq(n_blk - 1, n - (n_blk - 1) * 32);
+  __syncthreads();
+  // K is no longer needed: each wavefront turns its dK, dV tiles through its own rows of it
+  if (active) {
+    const int row0 = wave * 32;
+    store_tile_rows<D>(smem + row0 * RB, dkacc, scale, dk + clip_off + (size_t)row0 * row_stride, row_stride, n - row0);
+    store_tile_rows<D>(smem + row0 * RB, dvacc, 1.0f, dv + clip_off + (size_t)row0 * row_stride, row_stride, n - row0);
+  }
+}
+
+template <int D, int NW>
+static hipError_t launch_bwd_fused(const __bf16* q, const __bf16* k, const __bf16* v, const __bf16* out,
+                                   const float* lse, const __bf16* dout, const SegTable& segs, int total,
+                                   int n_heads, float scale, __bf16* dq, __bf16* dk, __bf16* dv, hipStream_t stream) {
+  constexpr int lds = FusedCfg<D, NW>::kLdsBytes;
+  static_assert(lds <= 160 * 1024, "LDS of one CU");
+  const UnitMap um = make_unit_map(n_heads, segs.n);   // (clip, head) units, heads first
+  auto kern = attn_bwd_fused_kernel<D, NW>;
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (e != hipSuccess) return e;
+  return launch(kern, dim3(um.chunk * kNumXcd), dim3(NW * 64), lds, stream, q, k, v, out, lse, dout, dq, dk, dv, segs,
+                um, total, n_heads, scale, scale * kLog2eB);
+}
+
 // Sequences up to this many rows (queries and keys) take the single launch above.
 constexpr int kBothMaxRows = 1024;
 
@@ -1169,6 +1531,16 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
                                int kv_lo, int kv_hi, hipStream_t stream) {
   const __bf16 *qb = (const __bf16*)q, *kb = (const __bf16*)k, *vb = (const __bf16*)v, *dob = (const __bf16*)dout;
   hipError_t e;
+  if constexpr (std::is_same_v<Segs, SegTable>) {
+    if (segs.n == 0) return hipSuccess;
+    if (bwd_one_pass(segs.len[0], segs.n, n_heads, D)) {   // (longest clip first)
+      if (segs.len[0] <= 128)
+        return launch_bwd_fused<D, 4>(qb, kb, vb, (const __bf16*)out, lse, dob, segs, total, n_heads, scale,
+                                      (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, stream);
+      return launch_bwd_fused<D, 8>(qb, kb, vb, (const __bf16*)out, lse, dob, segs, total, n_heads, scale,
+                                    (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, stream);
+    }
+  }
   if (total > 0) {   // (with no queries at all only the keys' zero gradients remain to be written)
     bool any_short = false;
     for (int s2 = 0; s2 < segs.n; ++s2)

@@ -423,9 +423,21 @@ int attn_bwd_common(const void* q, const void* k, const void* v, const void* out
                     const void* dout, const int32_t* cu_seqlens, int n_seqs, int total_tokens,
                     int n_heads, int head_dim, float scale, void* dq, void* dk, void* dv, float* delta,
                     float* lse2, float* sentinel, hipStream_t stream) {
-  hipError_t e = vfm::launch_bwd_prepare(out, dout, lse, delta, lse2, sentinel, total_tokens, n_heads,
-                                         head_dim, stream);
-  if (e != hipSuccess) return launch_status(e);
+  hipError_t e;
+  bool need_stats = false;   // some run of clips takes the two-pass kernels
+  for (int s0 = 0; s0 < n_seqs; s0 += VFM_MAX_SEQS) {
+    int longest = 0, clips = 0;
+    for (int i = s0; i < std::min(n_seqs, s0 + VFM_MAX_SEQS); ++i) {
+      const int len = cu_seqlens[i + 1] - cu_seqlens[i];
+      longest = std::max(longest, len);
+      clips += len > 0;
+    }
+    need_stats |= !vfm::bwd_one_pass(longest, clips, n_heads, head_dim);
+  }
+  if (need_stats) {
+    e = vfm::launch_bwd_prepare(out, dout, lse, delta, lse2, sentinel, total_tokens, n_heads, head_dim, stream);
+    if (e != hipSuccess) return launch_status(e);
+  }
   for (int s0 = 0; s0 < n_seqs; s0 += VFM_MAX_SEQS) {
     SegTable segs;
     build_seg_table(cu_seqlens + s0, std::min(VFM_MAX_SEQS, n_seqs - s0), &segs);

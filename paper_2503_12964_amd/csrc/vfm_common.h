@@ -178,6 +178,19 @@ inline int fwd_tile_rows(const Segs& segs, int head_dim) {
   return longest_kv <= 1024 ? 128 : 256;
 }
 
+// Whether a run of clips takes the one-pass backward, which forms its own statistics: one workgroup per
+// (clip, head), clips of at most 256 tokens.  A lone workgroup of it takes longer than the two-pass
+// kernel's, which spreads a (clip, head) over up to three, so at head_dim 128 a run whose two-pass
+// workgroups all fit the chip at once stays there (256 tokens x 64 clip-heads: 23 us against 34; x 256:
+// about 60 against 42); at head_dim 64 and up to 64 tokens the one pass is level or faster from the
+// first unit on (64 tokens x 2: 11.4 against 8.1 us).
+constexpr int kOnePassMaxRows = 256;
+inline bool bwd_one_pass(int longest, int n_clips, int n_heads, int head_dim) {
+  if (longest > kOnePassMaxRows) return false;
+  if (head_dim == 64 || longest <= 64) return true;
+  return (long long)n_clips * n_heads * (longest > 128 ? 3 : 2) > 256;
+}
+
 // LDS tiles hold rows of D bf16 without padding; the 16-byte chunk index within
 // a row is XOR-ed with a function of the row so that both row-wise 16-byte reads
 // (16 consecutive rows, one chunk) and transposing 8-byte reads (4 consecutive

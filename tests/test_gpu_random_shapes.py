@@ -75,3 +75,41 @@ def test_maximum_number_of_clips():
     wl = W.Workload("max_clips", grids, 2, 128, (32, 48, 48), seed=77)
     gpu, host = _run_fwd_bwd(wl, rope=True)
     _assert_parity(wl, gpu, host, relative_maxabs=True)
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("lengths", [
+    (64, 63, 33, 32, 31, 2, 1),                       # up to 64: any number of clips takes the one pass
+    (128, 127, 97, 96, 65, 64, 40, 20, 1),            # four wavefronts, 128 keys
+    (256, 255, 225, 224, 193, 161, 160, 129, 128, 33, 16, 5),   # eight wavefronts, odd and even block counts
+], ids=["64", "128", "256"])
+def test_one_pass_backward_block_edges(head_dim, lengths):
+    """Clips of at most 256 tokens whose backward is one workgroup per (clip, head): every remainder
+    of the 32-row blocks, enough (clip, head) units (over 128 and over 256/3) to leave the two-pass kernels."""
+    grids = tuple((1, 1, n) for n in lengths for _ in range(3)) + ((0, 1, 1),)
+    dims = (16, 24, 24) if head_dim == 64 else (32, 48, 48)
+    wl = W.Workload(f"one_pass{lengths[0]}", grids, 5, head_dim, dims, seed=300 + lengths[0])
+    gpu, host = _run_fwd_bwd(wl)
+    _assert_parity(wl, gpu, host, relative_maxabs=True)
+
+
+def test_one_pass_backward_under_graph_replay_and_without_workspace():
+    """The one pass ignores the statistics buffers: both entry points give the same bits, and a
+    captured call gives them again on every replay."""
+    import torch
+    from paper_2503_12964_amd import binding as b
+    wl = W.Workload("one_pass_graph", tuple((1, 1, n) for n in (200, 256, 129) * 10), 4, 128, (32, 48, 48), seed=9)
+    q, k, v, do = (U.to_device(W.make_inputs(wl)[n]) for n in ("q", "k", "v", "dout"))
+    out, lse = b.vfm_attn_fwd(q, k, v, wl.cu_seqlens, wl.scale)
+    want = b.vfm_attn_bwd(q, k, v, out, lse, do, wl.cu_seqlens, wl.scale)
+    got = [torch.empty_like(q) for _ in range(3)]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        b.vfm_attn_bwd_noalloc(q, k, v, out, lse, do, wl.cu_seqlens, wl.scale, *got)
+    for _ in range(3):
+        for t in got:
+            t.fill_(7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a.view(torch.int16), c.view(torch.int16)) for a, c in zip(got, want))
