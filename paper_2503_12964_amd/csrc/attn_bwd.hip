@@ -43,13 +43,13 @@ __global__ __launch_bounds__(256) void bwd_prepare_kernel(const u32x4* __restric
                                                           float* __restrict__ delta,
                                                           float* __restrict__ lse2,
                                                           float* __restrict__ sentinel, int total,
-                                                          int n_heads) {
+                                                          int n_heads, int tok0, int tok_end) {
   constexpr int kLanesPerRow = D / 8;
   constexpr int kTokPerBlock = 256 / kLanesPerRow;
-  const int tok = blockIdx.x * kTokPerBlock + threadIdx.x / kLanesPerRow;
+  const int tok = tok0 + blockIdx.x * kTokPerBlock + threadIdx.x / kLanesPerRow;   // the run's query tokens
   const int chunk = threadIdx.x % kLanesPerRow;
-  const bool valid = tok < total;
-  const int tk = valid ? tok : total - 1;
+  const bool valid = tok < tok_end;
+  const int tk = valid ? tok : tok_end - 1;
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {   // statistics fetched for rows past a clip's end
     sentinel[0] = INFINITY;                    // lse2: P = exp2(s - inf) = 0
     sentinel[1] = 0.f;                         // Delta
@@ -70,8 +70,9 @@ __global__ __launch_bounds__(256) void bwd_prepare_kernel(const u32x4* __restric
     float s = 0.f;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      s += __builtin_bit_cast(float, a[i][e] << 16) * __builtin_bit_cast(float, b[i][e] << 16);
-      s += __builtin_bit_cast(float, a[i][e] & 0xffff0000u) * __builtin_bit_cast(float, b[i][e] & 0xffff0000u);
+      s = __builtin_fmaf(__builtin_bit_cast(float, a[i][e] << 16), __builtin_bit_cast(float, b[i][e] << 16), s);
+      s = __builtin_fmaf(__builtin_bit_cast(float, a[i][e] & 0xffff0000u),
+                         __builtin_bit_cast(float, b[i][e] & 0xffff0000u), s);
     }
 #pragma unroll
     for (int o = kLanesPerRow / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, kLanesPerRow);
@@ -794,12 +795,16 @@ struct Dq2Cfg {
   static constexpr int kChunksPerThread = kDqBC * kChunksPerRow / (kDq2Waves * 64);
 };
 
-// The work of one workgroup: query tile tq of sequence seq, one head.
-template <int D, class Segs>
+// The work of one workgroup: query tile tq of sequence seq, one head.  STATS: form Delta and lse in log2
+// units of the tile's rows here, from `out` and `lse`, and leave them for the dK/dV pass (Delta of a sequence
+// with few keys is already in place).  The rows of dO are in registers anyway, so this costs the reads of
+// `out`, where the separate pass reads dO as well and is one more launch.
+template <int D, class Segs, bool STATS>
 __device__ __forceinline__
 void bwd_dq2_unit(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
                   const __bf16* __restrict__ v, const __bf16* __restrict__ dout,
-                  const float* __restrict__ lse2g, const float* __restrict__ delta,
+                  const __bf16* __restrict__ out, const float* __restrict__ lse,
+                  float* __restrict__ lse2g, float* __restrict__ delta,
                   __bf16* __restrict__ dq, const Segs& segs, int total, int n_heads, float scale,
                   float scale_log2, int head, int seq, int tq) {
   using Cfg = Dq2Cfg<D>;
@@ -843,8 +848,36 @@ void bwd_dq2_unit(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
       qreg[ib][ks] = *reinterpret_cast<const bf16x8*>(q + off + ks * 16);
       doreg[ib][ks] = *reinterpret_cast<const bf16x8*>(dout + off + ks * 16);
     }
-    lse2[ib] = lse2g[(size_t)head * total + r];
-    dlt[ib] = delta[(size_t)head * total + r];
+    const size_t stat = (size_t)head * total + r;
+    if constexpr (STATS) {
+      bf16x8 oreg[KS];
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) oreg[ks] = *reinterpret_cast<const bf16x8*>(out + off + ks * 16);
+      lse2[ib] = lse[stat] * kLog2eB;
+      // the order of bwd_prepare_kernel's sums (chunks of 8 columns, then pairs of chunks 8, 4, 2, 1 apart), so
+      // that a clip's gradients do not depend, to the bit, on what else is in the pack
+      float s[KS];
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        s[ks] = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s[ks] = __builtin_fmaf((float)oreg[ks][e], (float)doreg[ib][ks][e], s[ks]);
+      }
+#pragma unroll
+      for (int o = KS / 2; o > 0; o >>= 1)
+#pragma unroll
+        for (int ks = 0; ks < o; ++ks) s[ks] += s[ks + o];
+      dlt[ib] = pair_sum(s[0]);
+      const bool few = segs.kv_len(seq) <= kShortKeys;
+      if (few) dlt[ib] = delta[stat];
+      if (g == 0 && qrow[ib] < q_b) {
+        lse2g[stat] = lse2[ib];
+        if (!few) delta[stat] = dlt[ib];
+      }
+    } else {
+      lse2[ib] = lse2g[stat];
+      dlt[ib] = delta[stat];
+    }
   }
 
   // ---- K/V staging with direct global->LDS loads; tiles are requested in sequence
@@ -1103,18 +1136,24 @@ void bwd_dq2_unit(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   }
 }
 
-template <int D, class Segs>
+template <int D, class Segs, bool STATS>
 __global__ __launch_bounds__(kDq2Waves * 64, 1)
 void attn_bwd_dq2_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
                          const __bf16* __restrict__ v, const __bf16* __restrict__ dout,
-                         const float* __restrict__ lse2g, const float* __restrict__ delta,
+                         const __bf16* __restrict__ out, const float* __restrict__ lse,
+                         float* __restrict__ lse2g, float* __restrict__ delta, float* __restrict__ sentinel,
                          __bf16* __restrict__ dq, const Segs segs, const UnitMap um, const TileIndex ti,
                          int total, int n_heads, float scale, float scale_log2) {
   int head, tile;
   if (!map_unit(um, blockIdx.x, head, tile)) return;
+  if (STATS && blockIdx.x == 0 && threadIdx.x == 0) {   // the dK/dV pass' statistics of rows past a clip's end
+    sentinel[0] = INFINITY;
+    sentinel[1] = 0.f;
+  }
   int seq, tq;
   locate_tile(ti, segs.n, tile, seq, tq);
-  bwd_dq2_unit<D, Segs>(q, k, v, dout, lse2g, delta, dq, segs, total, n_heads, scale, scale_log2, head, seq, tq);
+  bwd_dq2_unit<D, Segs, STATS>(q, k, v, dout, out, lse, lse2g, delta, dq, segs, total, n_heads, scale, scale_log2,
+                               head, seq, tq);
 }
 
 // ---------------------------------------------------------------- short sequences: one launch
@@ -1128,7 +1167,7 @@ template <int D, class Segs>
 __global__ __launch_bounds__(kBwdWaves * 64, 1)
 void attn_bwd_both_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
                           const __bf16* __restrict__ v, const __bf16* __restrict__ dout,
-                          const float* __restrict__ lse2, const float* __restrict__ delta,
+                          float* __restrict__ lse2, float* __restrict__ delta,
                           const float* __restrict__ sentinel, __bf16* __restrict__ dq,
                           __bf16* __restrict__ dk, __bf16* __restrict__ dv,
                           const Segs segs, const UnitMap um, const TileIndex ti,
@@ -1143,8 +1182,8 @@ void attn_bwd_both_kernel(const __bf16* __restrict__ q, const __bf16* __restrict
     bwd_dkdv_unit<D, Segs, false>(q, k, v, dout, lse2, delta, sentinel, dk, dv, segs, total, n_heads, scale,
                                   scale_log2, nullptr, 0, 1, head, seq, t, 0);
   else
-    bwd_dq2_unit<D, Segs>(q, k, v, dout, lse2, delta, dq, segs, total, n_heads, scale, scale_log2, head, seq,
-                          t - key_tiles);
+    bwd_dq2_unit<D, Segs, false>(q, k, v, dout, nullptr, nullptr, lse2, delta, dq, segs, total, n_heads, scale,
+                                 scale_log2, head, seq, t - key_tiles);
 }
 
 // ---------------------------------------------------------------- sequences of up to 256 tokens: one pass
@@ -1523,6 +1562,17 @@ static int compute_unit_count() {
   return n;
 }
 
+// Delta, lse in log2 units and the sentinels for the query tokens [tok0, tok_end) of a run.
+static hipError_t launch_bwd_prepare(const void* out, const void* dout, const float* lse, float* delta, float* lse2,
+                                     float* sentinel, int total, int n_heads, int head_dim, int tok0, int tok_end,
+                                     hipStream_t stream) {
+  const int tok_per_block = 256 / (head_dim / 8);
+  const dim3 grid((tok_end - tok0 + tok_per_block - 1) / tok_per_block, (n_heads + kPrepHeads - 1) / kPrepHeads);
+  auto kern = head_dim == 128 ? bwd_prepare_kernel<128> : bwd_prepare_kernel<64>;
+  return launch(kern, grid, dim3(256), 0, stream, (const u32x4*)out, (const u32x4*)dout, lse, delta, lse2, sentinel,
+                total, n_heads, tok0, tok_end);
+}
+
 template <int D, class Segs>
 static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, const void* out,
                                const float* lse, const void* dout, const Segs& segs, int total,
@@ -1541,44 +1591,92 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
                                     (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, stream);
     }
   }
-  if (total > 0) {   // (with no queries at all only the keys' zero gradients remain to be written)
-    bool any_short = false;
-    for (int s2 = 0; s2 < segs.n; ++s2)
-      any_short |= segs.q_len(s2) > 0 && segs.kv_len(s2) > 0 && segs.kv_len(s2) <= kShortKeys;
+  const TileIndex ti = make_tile_index<true>(segs, kBwdBC);
+  const int tiles = count_tiles(ti);
+  // Few key tiles and long query ranges (cross-attention): split the queries over workgroups.
+  int q_split = 1, longest = 0, max_q = 0;
+  int tok0 = 0x7fffffff, tok_end = 0;   // the run's query tokens
+  bool any_short = false;
+  for (int s2 = 0; s2 < segs.n; ++s2) {
+    const int nq = segs.q_len(s2), nk = segs.kv_len(s2);
+    max_q = std::max(max_q, nq);
+    longest = std::max(longest, std::max(nq, nk));
+    if (nq == 0) continue;
+    tok0 = std::min(tok0, segs.q_start(s2));
+    tok_end = std::max(tok_end, segs.q_start(s2) + nq);
+    any_short |= nk > 0 && nk <= kShortKeys;
+  }
+  const int cus = compute_unit_count();
+  if (dkv32 && tiles > 0 && tiles * n_heads < cus)
+    q_split = std::min(std::min(16, (cus + tiles * n_heads - 1) / (tiles * n_heads)), std::max(1, max_q / 512));
+  const bool both = D == 128 && q_split == 1 && longest <= kBothMaxRows;
+  // At head_dim 128 the dQ pass runs first and forms the statistics on the way (backward call, separate
+  // pass -> here: 20,000 queries x 300 keys x 16 heads 413 -> 403 us, 2 x 4,096 tokens x 16 heads 785 -> 775,
+  // 12,000 tokens x 4 heads level).  Elsewhere, and where dq takes the place of an operand that the
+  // dK/dV pass reads, they come from a pass of their own.
+  const bool dq_first = D == 128 && !both && dq != q && dq != dout;
+  if (max_q > 0) {   // (with no queries at all only the keys' zero gradients remain to be written)
+    if (!dq_first) {
+      e = launch_bwd_prepare(out, dout, lse, delta, lse2, sentinel, total, n_heads, D, tok0, tok_end, stream);
+      if (e != hipSuccess) return e;
+    }
     if (any_short) {   // sequences with a handful of keys: Delta in its cancellation-free form
-      TileIndex ti;   // 32-row query tiles of the sequences with few keys, none of the others
-      int tiles = 0;
+      TileIndex ti_few;   // 32-row query tiles of the sequences with few keys, none of the others
+      int few = 0;
       for (int s2 = 0; s2 <= VFM_MAX_SEQS; ++s2) {
-        ti.cu[s2] = tiles;
-        if (s2 < segs.n && segs.kv_len(s2) > 0 && segs.kv_len(s2) <= kShortKeys) tiles += (segs.q_len(s2) + 31) / 32;
+        ti_few.cu[s2] = few;
+        if (s2 < segs.n && segs.kv_len(s2) > 0 && segs.kv_len(s2) <= kShortKeys) few += (segs.q_len(s2) + 31) / 32;
       }
-      e = launch(bwd_short_delta_kernel<D, Segs>, dim3(tiles, n_heads), dim3(64), 0,
-                 stream, qb, kb, vb, dob, lse, delta, segs, ti, total, n_heads, scale * kLog2eB);
+      e = launch(bwd_short_delta_kernel<D, Segs>, dim3(few, n_heads), dim3(64), 0,
+                 stream, qb, kb, vb, dob, lse, delta, segs, ti_few, total, n_heads, scale * kLog2eB);
       if (e != hipSuccess) return e;
     }
   }
+  if (tiles == 0) return hipSuccess;
+  UnitMap um = make_unit_map(tiles, n_heads);
+  auto launch_dq = [&](auto stats_c) -> hipError_t {
+    if constexpr (D == 128) {
+      constexpr bool STATS = decltype(stats_c)::value != 0;
+      using Cfg = Dq2Cfg<D>;
+      const TileIndex tq = make_tile_index<false>(segs, Cfg::kBR);
+      const int n = count_tiles(tq);
+      if (n == 0) return hipSuccess;
+      const UnitMap uq = make_unit_map(n, n_heads);
+      auto kern = attn_bwd_dq2_kernel<D, Segs, STATS>;
+      hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::kLdsBytes);
+      if (err != hipSuccess) return err;
+      return launch(kern, dim3(uq.chunk * kNumXcd), dim3(kDq2Waves * 64), Cfg::kLdsBytes, stream, qb, kb, vb, dob,
+                    (const __bf16*)out, lse, lse2, delta, sentinel, (__bf16*)dq, segs, uq, tq, total, n_heads, scale,
+                    scale * kLog2eB);
+    } else {
+      constexpr int NI = 1;
+      constexpr int W = 8;   // 256 query rows share each staged K/V tile
+      using Cfg = DqCfg<D, NI, W>;
+      const TileIndex tq = make_tile_index<false>(segs, Cfg::kBR);
+      const int n = count_tiles(tq);
+      if (n == 0) return hipSuccess;
+      const UnitMap uq = make_unit_map(n, n_heads);
+      auto kern = attn_bwd_dq_kernel<D, NI, W, Segs>;
+      hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::kLdsBytes);
+      if (err != hipSuccess) return err;
+      return launch(kern, dim3(uq.chunk * kNumXcd), dim3(W * 64), Cfg::kLdsBytes, stream, qb, kb, vb, dob, lse2,
+                    delta, (__bf16*)dq, segs, uq, tq, total, n_heads, scale, scale * kLog2eB);
+    }
+  };
+  if (dq_first) {
+    e = launch_dq(IntC<1>{});
+    if (e != hipSuccess) return e;
+  }
   {
     using Cfg = BwdCfg<D>;
-    const TileIndex ti = make_tile_index<true>(segs, kBwdBC);
-    const int tiles = count_tiles(ti);
-    if (tiles == 0) return hipSuccess;
-    UnitMap um = make_unit_map(tiles, n_heads);
-    // Few key tiles and long query ranges (cross-attention): split the queries over workgroups.
-    int q_split = 1;
-    const int cus = compute_unit_count();
-    if (dkv32 && tiles * n_heads < cus) {
-      int max_q = 0;
-      for (int s2 = 0; s2 < segs.n; ++s2) max_q = std::max(max_q, segs.q_len(s2));
-      q_split = std::min(std::min(16, (cus + tiles * n_heads - 1) / (tiles * n_heads)), std::max(1, max_q / 512));
-    }
     if constexpr (D == 128) {
-      int longest = 0;
-      for (int s2 = 0; s2 < segs.n; ++s2) longest = std::max(longest, std::max(segs.q_len(s2), segs.kv_len(s2)));
-      if (q_split == 1 && longest <= kBothMaxRows) {   // short sequences: both passes from one grid
-        TileIndex both;
+      if (both) {   // short sequences: both passes from one grid
+        TileIndex tb;
         int n_both = 0;
         for (int s2 = 0; s2 <= VFM_MAX_SEQS; ++s2) {
-          both.cu[s2] = n_both;
+          tb.cu[s2] = n_both;
           if (s2 < segs.n)
             n_both += (segs.kv_len(s2) + kBwdBC - 1) / kBwdBC + (segs.q_len(s2) + Dq2Cfg<D>::kBR - 1) / Dq2Cfg<D>::kBR;
         }
@@ -1588,7 +1686,7 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
         e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
         return launch(kern, dim3(um.chunk * kNumXcd), dim3(kBwdWaves * 64), lds, stream, qb, kb, vb, dob, lse2,
-                      delta, sentinel, (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, segs, um, both, total, n_heads, scale,
+                      delta, sentinel, (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, segs, um, tb, total, n_heads, scale,
                       scale * kLog2eB);
       }
     }
@@ -1628,47 +1726,8 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
       if (e != hipSuccess) return e;
     }
   }
-  if constexpr (D == 128) {
-    using Cfg = Dq2Cfg<D>;
-    const TileIndex ti = make_tile_index<false>(segs, Cfg::kBR);
-    const int tiles = count_tiles(ti);
-    if (tiles == 0) return hipSuccess;
-    UnitMap um = make_unit_map(tiles, n_heads);
-    auto kern = attn_bwd_dq2_kernel<D, Segs>;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::kLdsBytes);
-    if (e != hipSuccess) return e;
-    return launch(kern, dim3(um.chunk * kNumXcd), dim3(kDq2Waves * 64), Cfg::kLdsBytes, stream, qb, kb, vb, dob,
-                  lse2, delta, (__bf16*)dq, segs, um, ti, total, n_heads, scale, scale * kLog2eB);
-  } else {
-    constexpr int NI = 1;
-    constexpr int W = 8;   // 256 query rows share each staged K/V tile
-    using Cfg = DqCfg<D, NI, W>;
-    const TileIndex ti = make_tile_index<false>(segs, Cfg::kBR);
-    const int tiles = count_tiles(ti);
-    if (tiles == 0) return hipSuccess;
-    UnitMap um = make_unit_map(tiles, n_heads);
-    auto kern = attn_bwd_dq_kernel<D, NI, W, Segs>;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::kLdsBytes);
-    if (e != hipSuccess) return e;
-    return launch(kern, dim3(um.chunk * kNumXcd), dim3(W * 64), Cfg::kLdsBytes, stream, qb, kb, vb, dob, lse2,
-                  delta, (__bf16*)dq, segs, um, ti, total, n_heads, scale, scale * kLog2eB);
-  }
-}
-
-// Delta, lse in log2 units and the sentinels for all `total` query tokens of a call (once per
-// call, before the runs of clips).
-hipError_t launch_bwd_prepare(const void* out, const void* dout, const float* lse, float* delta, float* lse2,
-                              float* sentinel, int total, int n_heads, int head_dim, hipStream_t stream) {
-  if (total == 0) return hipSuccess;
-  const int tok_per_block = 256 / (head_dim / 8);
-  const dim3 grid((total + tok_per_block - 1) / tok_per_block, (n_heads + kPrepHeads - 1) / kPrepHeads);
-  if (head_dim == 128)
-    return launch(bwd_prepare_kernel<128>, grid, dim3(256), 0, stream, (const u32x4*)out, (const u32x4*)dout, lse,
-                  delta, lse2, sentinel, total, n_heads);
-  return launch(bwd_prepare_kernel<64>, grid, dim3(256), 0, stream, (const u32x4*)out, (const u32x4*)dout, lse,
-                delta, lse2, sentinel, total, n_heads);
+  if (dq_first) return hipSuccess;
+  return launch_dq(IntC<0>{});
 }
 
 template <class Segs>

@@ -423,26 +423,11 @@ int attn_bwd_common(const void* q, const void* k, const void* v, const void* out
                     const void* dout, const int32_t* cu_seqlens, int n_seqs, int total_tokens,
                     int n_heads, int head_dim, float scale, void* dq, void* dk, void* dv, float* delta,
                     float* lse2, float* sentinel, hipStream_t stream) {
-  hipError_t e;
-  bool need_stats = false;   // some run of clips takes the two-pass kernels
-  for (int s0 = 0; s0 < n_seqs; s0 += VFM_MAX_SEQS) {
-    int longest = 0, clips = 0;
-    for (int i = s0; i < std::min(n_seqs, s0 + VFM_MAX_SEQS); ++i) {
-      const int len = cu_seqlens[i + 1] - cu_seqlens[i];
-      longest = std::max(longest, len);
-      clips += len > 0;
-    }
-    need_stats |= !vfm::bwd_one_pass(longest, clips, n_heads, head_dim);
-  }
-  if (need_stats) {
-    e = vfm::launch_bwd_prepare(out, dout, lse, delta, lse2, sentinel, total_tokens, n_heads, head_dim, stream);
-    if (e != hipSuccess) return launch_status(e);
-  }
   for (int s0 = 0; s0 < n_seqs; s0 += VFM_MAX_SEQS) {
     SegTable segs;
     build_seg_table(cu_seqlens + s0, std::min(VFM_MAX_SEQS, n_seqs - s0), &segs);
-    e = vfm::launch_attn_bwd(q, k, v, out, lse, dout, segs, total_tokens, n_heads, head_dim, scale, dq, dk,
-                             dv, delta, lse2, sentinel, nullptr, 0, 0, 0, stream);
+    hipError_t e = vfm::launch_attn_bwd(q, k, v, out, lse, dout, segs, total_tokens, n_heads, head_dim, scale, dq,
+                                        dk, dv, delta, lse2, sentinel, nullptr, 0, 0, 0, stream);
     if (e != hipSuccess) return launch_status(e);
   }
   return VFM_OK;
@@ -561,15 +546,13 @@ int vfm_xattn_bwd(const void* q, const void* k, const void* v, const void* out, 
   float* sentinel = reinterpret_cast<float*>(static_cast<char*>(workspace) + 2 * part);
   float* dkv32 = reinterpret_cast<float*>(static_cast<char*>(workspace) + stats);
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  hipError_t e = vfm::launch_bwd_prepare(out, dout, lse, delta, lse2, sentinel, total_q, n_heads, head_dim, stream);
-  if (e != hipSuccess) return launch_status(e);
   for (int s0 = 0; s0 < n_seqs; s0 += VFM_MAX_XSEQS) {
     const int n = std::min(VFM_MAX_XSEQS, n_seqs - s0);
     XSegTable segs;
     build_xseg_table(cu_seqlens_q + s0, cu_seqlens_kv + s0, n, &segs);
-    e = vfm::launch_attn_bwd(q, k, v, out, lse, dout, segs, total_q, n_heads, head_dim, scale, dq, dk, dv,
-                             delta, lse2, sentinel, dkv32, total_kv, cu_seqlens_kv[s0], cu_seqlens_kv[s0 + n],
-                             stream);
+    hipError_t e = vfm::launch_attn_bwd(q, k, v, out, lse, dout, segs, total_q, n_heads, head_dim, scale, dq, dk,
+                                        dv, delta, lse2, sentinel, dkv32, total_kv, cu_seqlens_kv[s0],
+                                        cu_seqlens_kv[s0 + n], stream);
     if (e != hipSuccess) return launch_status(e);
   }
   return VFM_OK;

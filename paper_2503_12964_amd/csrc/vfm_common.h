@@ -458,9 +458,6 @@ hipError_t launch_attn_fwd(const void* q, const void* k, const void* v, const Se
                            int total_q, int n_heads, int head_dim, float scale, void* out,
                            float* lse, hipStream_t stream);
 
-// Once per call: the statistics of all total_q query tokens.
-hipError_t launch_bwd_prepare(const void* out, const void* dout, const float* lse, float* delta, float* lse2,
-                              float* sentinel, int total_q, int n_heads, int head_dim, hipStream_t stream);
 // The sequences of segs (one run of a call's clips).  dkv32: optional fp32 dK, dV accumulators of
 // total_kv rows each (query-split pass); [kv_lo, kv_hi) is the run's range of key rows.
 template <class Segs>
