@@ -264,10 +264,12 @@ VFM_API int vfm_xattn_bwd(const void* q, const void* k, const void* v, const voi
  * pixel p < H*W the sequence is the T rows cu_seqlens[s] + t*H*W + p; per head
  *     out_i = sum_j softmax_j(scale * q_i . k_j) v_j       i, j over the T frames.
  * Any T >= 1 (the section speaks of hundreds of frames): up to 128 frames a
- * sequence is held on chip and the call is bound by HBM; a call (run of
- * clips) in which some clip has more is walked in 32-frame blocks with an
- * online softmax.  q, k, v, out: bf16 [total_tokens, n_heads, head_dim]; thw,
- * cu_seqlens: host.  No statistics are saved.
+ * sequence is held on chip and the call is bound by HBM; a clip with more is
+ * walked in 32-frame blocks with an online softmax.  Clips go to the kernels made
+ * for their own frame count (few of them beside longer ones of the run to the
+ * longer ones' kernels: the same result up to the rounding of sums).  q, k, v,
+ * out: bf16 [total_tokens, n_heads, head_dim]; thw, cu_seqlens: host.  No
+ * statistics are saved.
  * Errors: NULL, SHAPE, CU_SEQLENS, THW, DTYPE, ALIGN, LAUNCH.
  */
 VFM_API int vfm_tattn_fwd(const void* q, const void* k, const void* v,
@@ -279,7 +281,7 @@ VFM_API int vfm_tattn_fwd(const void* q, const void* k, const void* v,
  * Temporal attention backward: dq, dk, dv (bf16, fully overwritten) from dout.
  * The softmax is recomputed from q and k; Delta_i = sum_j P_ij (dout_i . v_j).
  * No atomics, no workspace; every output is written once, except that with clips
- * of more than 128 frames the first 8 bytes of every dq row hold that query's
+ * of more than 128 frames the first 8 bytes of a dq row hold that query's
  * softmax statistics while the call runs, before dq is written over them.
  * Errors: NULL, SHAPE, CU_SEQLENS, THW, DTYPE, ALIGN, LAUNCH.
  */

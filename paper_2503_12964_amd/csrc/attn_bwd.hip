@@ -1549,8 +1549,7 @@ static hipError_t launch_bwd_fused(const __bf16* q, const __bf16* k, const __bf1
 // Sequences up to this many rows (queries and keys) take the single launch above.
 constexpr int kBothMaxRows = 1024;
 
-// Compute units of the current device (asked once; 256 on MI355X, also the fallback).
-static int compute_unit_count() {
+int compute_unit_count() {
   static std::atomic<int> cached{0};
   int n = cached.load(std::memory_order_relaxed);
   if (n > 0) return n;

@@ -339,7 +339,7 @@ __device__ __forceinline__ bf16x8 half_to_bf16(const f32x16& x, int s2) {
 // A whole sequence fits in LDS (128 frames of q, k, v and dout at head_dim 128 are 128 KB), so one
 // workgroup owns one (pixel, head), gathers every row once, needs nothing from memory after that
 // and stores whole rows: bound by HBM.  NB = 32-row blocks of the longest sequence of the launch;
-// shorter ones skip the blocks they do not have (uniform branches).
+// shorter ones (few, see temporal_joins) skip the blocks they do not have (uniform branches).
 // Forward: wave b owns query block b and holds its whole score row S^T in registers (NB 32 x 32
 // tiles), so the softmax is exact and needs no rescaling.
 // Measured at head_dim 128, forward and backward together, against the kernels that walk 32-row
@@ -644,7 +644,8 @@ template <int D, int NB>
 static hipError_t launch_blocks(const void* q, const void* k, const void* v, const void* dout,
                                 const TemporalTable& tab, int n_heads, float scale, void* o0, void* o1,
                                 void* o2, hipStream_t stream) {
-  const dim3 grid((unsigned)(tab.pix_cu[tab.n] * n_heads));
+  const TemporalGrid tg = temporal_grid(tab, NB, n_heads, dout != nullptr);
+  const dim3 grid(tg.blocks), block(tg.threads);
   constexpr int TB = T2Cfg<D>::kTileBytes;
   const float scale_log2 = scale * kLog2eT;
   if (!dout) {
@@ -652,19 +653,19 @@ static hipError_t launch_blocks(const void* q, const void* k, const void* v, con
     auto kern = tattnB_fwd_kernel<D, NB>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
-    return launch(kern, grid, dim3(NB * 64), lds, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (__bf16*)o0,
+    return launch(kern, grid, block, lds, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (__bf16*)o0,
                   tab, n_heads, scale_log2);
   }
   constexpr int lds = 4 * NB * TB + 2 * NB * kT2Rows * 4;
   auto kern = tattnB_bwd_kernel<D, NB>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return e;
-  return launch(kern, grid, dim3(NB * 128), lds, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v,
+  return launch(kern, grid, block, lds, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v,
                 (const __bf16*)dout, (__bf16*)o0, (__bf16*)o1, (__bf16*)o2, tab, n_heads, scale, scale_log2);
 }
 
 // ---------------------------------------------------------------- more than 128 frames
-// Section 4.6 speaks of videos of hundreds of frames.  For clips with T > 128 a wavefront owns one
+// Section 4.6 speaks of videos of hundreds of frames.  In clips with T > 128 a wavefront owns one
 // 32-row block of one (pixel, head) sequence and walks the sequence's other side in blocks of 32
 // with the online softmax of the packed kernels (running reference m, running sum l, rescaled
 // accumulators), on the 32 x 32 tiles, lane layouts and LDS helpers above.
@@ -1001,7 +1002,7 @@ __global__ __launch_bounds__(kTWaves * 64) void tattnL_dq_kernel(const __bf16* _
   for (int db = 0; db < DB; ++db) store_block<D>(dq, u, w.blk, row_stride, lane, db, dqacc[db], scale);
 }
 
-// Some clip of the run has more than 128 frames: the block-walking kernels serve the whole run.
+// tab: the clips of more than 128 frames and the few others that joined them.
 template <int D>
 static hipError_t launch_long(const void* q, const void* k, const void* v, const void* dout,
                               const TemporalTable& tab, int n_heads, float scale, void* o0, void* o1,
@@ -1014,10 +1015,8 @@ static hipError_t launch_long(const void* q, const void* k, const void* v, const
     lt.blk_cu[s] = blocks;
     if (s < VFM_MAX_SEQS) {
       lt.hw[s] = tab.hw[s];
-      if (s < tab.n && tab.cu[s + 1] > tab.cu[s]) {
-        const int T = (tab.cu[s + 1] - tab.cu[s]) / tab.hw[s];
-        blocks += tab.hw[s] * ((T + kT2Rows - 1) / kT2Rows);
-      }
+      if (s < tab.n && tab.pix_cu[s + 1] > tab.pix_cu[s])
+        blocks += tab.hw[s] * ((temporal_frames(tab, s) + kT2Rows - 1) / kT2Rows);
     }
   }
   const long long n_units = (long long)blocks * n_heads;
@@ -1050,38 +1049,43 @@ static hipError_t launch_long(const void* q, const void* k, const void* v, const
   return launch(dqk, grid, block, lds, stream, qb, kb, vb, dob, (__bf16*)o0, lt, n_heads, scale, scale_log2);
 }
 
+// Up to 16 frames.
 template <int D>
-static hipError_t launch_t(const void* q, const void* k, const void* v, const void* dout,
-                           const TemporalTable& tab, int n_heads, float scale, void* o0, void* o1,
-                           void* o2, hipStream_t stream) {
-  const long long n_units = (long long)tab.pix_cu[tab.n] * n_heads;
-  if (n_units == 0) return hipSuccess;
-  int max_t = 0;
-  for (int s = 0; s < tab.n; ++s)
-    if (tab.hw[s] > 0) max_t = std::max(max_t, (tab.cu[s + 1] - tab.cu[s]) / tab.hw[s]);
-  // the longest sequence of the run picks the kernels for all of it
-  if (max_t > 4 * kT2Rows) return launch_long<D>(q, k, v, dout, tab, n_heads, scale, o0, o1, o2, stream);
-  if (max_t > 3 * kT2Rows) return launch_blocks<D, 4>(q, k, v, dout, tab, n_heads, scale, o0, o1, o2, stream);
-  if (max_t > 2 * kT2Rows) return launch_blocks<D, 3>(q, k, v, dout, tab, n_heads, scale, o0, o1, o2, stream);
-  if (max_t > kT2Rows) return launch_blocks<D, 2>(q, k, v, dout, tab, n_heads, scale, o0, o1, o2, stream);
-  if (max_t > kTRows) return launch_blocks<D, 1>(q, k, v, dout, tab, n_heads, scale, o0, o1, o2, stream);
-  const int grid = (int)((n_units + kTWaves - 1) / kTWaves);
+static hipError_t launch_waves(const void* q, const void* k, const void* v, const void* dout,
+                               const TemporalTable& tab, int n_heads, float scale, void* o0, void* o1,
+                               void* o2, hipStream_t stream) {
+  const TemporalGrid tg = temporal_grid(tab, 0, n_heads, dout != nullptr);
+  const dim3 grid(tg.blocks), block(tg.threads);
   const int lds = kTWaves * (dout ? 4 : 3) * TCfg<D>::kTileBytes;
   if (!dout) {
     auto kern = tattn_fwd_kernel<D>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
-    return launch(kern, dim3(grid), dim3(kTWaves * 64), lds, stream, (const __bf16*)q, (const __bf16*)k,
+    return launch(kern, grid, block, lds, stream, (const __bf16*)q, (const __bf16*)k,
                   (const __bf16*)v, (__bf16*)o0, tab, n_heads, scale * kLog2eT);
   }
   auto kern = tattn_bwd_kernel<D>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return e;
-  return launch(kern, dim3(grid), dim3(kTWaves * 64), lds, stream, (const __bf16*)q, (const __bf16*)k,
-                (const __bf16*)v, (const __bf16*)dout, (__bf16*)o0, (__bf16*)o1, (__bf16*)o2, tab, n_heads,
-                scale, scale * kLog2eT);
+  return launch(kern, grid, block, lds, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v,
+                (const __bf16*)dout, (__bf16*)o0, (__bf16*)o1, (__bf16*)o2, tab, n_heads, scale, scale * kLog2eT);
+}
+
+template <int D>
+static hipError_t launch_t(const void* q, const void* k, const void* v, const void* dout,
+                           const TemporalTable& tab, int n_heads, float scale, void* o0, void* o1,
+                           void* o2, hipStream_t stream) {
+  const TemporalPlan plan = make_temporal_plan(tab, n_heads, D, compute_unit_count());
+  constexpr decltype(&launch_waves<D>) kLaunch[kTemporalClasses] = {
+      launch_waves<D>, launch_blocks<D, 1>, launch_blocks<D, 2>, launch_blocks<D, 3>, launch_blocks<D, 4>, launch_long<D>};
+  for (int l = kTemporalClasses - 1; l >= 0; --l) {
+    if (plan.launch_of[l] != l) continue;   // (a launch is named by its longest class)
+    const hipError_t e = kLaunch[l](q, k, v, dout, temporal_launch_table(tab, plan, l), n_heads, scale, o0, o1, o2, stream);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_tattn_fwd(const void* q, const void* k, const void* v, const TemporalTable& tab,

@@ -90,8 +90,76 @@ struct TemporalTable {
   int hw[VFM_MAX_SEQS];          // H*W of clip s (1 for an empty clip)
 };
 
-// The same clips for the temporal kernels that walk sequences of more than 32 frames in
-// 32-row blocks: a work unit is one block of one (pixel, head) sequence.
+// A clip's frame count picks its kernels.  Class 0: up to 16 frames (one wavefront per sequence); classes 1
+// to 4: up to 32, 64, 96, 128 frames (one workgroup per sequence, as many 32-row blocks as the class
+// says); class 5: more (a wavefront per 32-row block).  A run is one launch per class that it holds.
+// With the longest clip picking the kernels of the whole run, every single-frame pixel beside a
+// 100-frame clip took a 512-thread workgroup and 129 KB of LDS (200 images of 32 x 32 beside 100
+// frames of 8 x 8, 8 heads, head_dim 128, forward and backward: 53.3 ms, now 5.9), and 262,144
+// pixels x 32 heads were more threads than one launch can have.
+constexpr int kTemporalClasses = 6;
+inline int temporal_class(int frames) { return frames <= 16 ? 0 : frames <= 128 ? (frames + 31) / 32 : 5; }
+inline int temporal_frames(const TemporalTable& tab, int s) { return (tab.cu[s + 1] - tab.cu[s]) / tab.hw[s]; }
+
+// Another launch costs a call forward and backward 5 to 8 us, so a class of few sequences joins the next
+// longer class of the run.  Up to class 4: no more of them than twice the workgroups of that class'
+// backward that fit the chip's LDS at once, four times where the classes are neighbours and their kernels
+// differ least.  The line lies where joined is still level (head_dim 128, forward and backward, joined
+// against apart: 2,048 sequences of 16 frames beside 32-frame ones 35 us against 34, 1,024 beside 64
+// frames 32 against 33, 512 beside 96 frames 36 against 35; 2,048 of 32 beside 64 frames 57 against 61,
+// 1,024 of 96 beside 128 frames 113 against 112; head_dim 64: 2,048 of 16 beside 64 frames 27 against
+// 33, 2,048 of 96 beside 128 frames 90 against 98).  Class 5: no more than 1,024 32-row blocks (head_dim
+// 128, beside 200 frames: 1,024 x 16 frames 124 against 126, 64 x 128 frames 115 against 133).
+inline bool temporal_joins(int cls, int into, long long sequences, int head_dim, int cus) {
+  if (into == 5) return sequences * (cls == 0 ? 1 : cls) <= 4LL * cus;
+  const int chipful = 160 * 1024 / (into * (head_dim + 1) * 256) * cus;   // LDS of a backward workgroup: into * 32 rows
+  return sequences <= (long long)chipful * (into == cls + 1 ? 4 : 2);
+}
+
+// The launch (named by its class) that the clips of every class take; -1: the run has none of the class.
+struct TemporalPlan { int launch_of[kTemporalClasses]; };
+inline TemporalPlan make_temporal_plan(const TemporalTable& tab, int n_heads, int head_dim, int cus) {
+  TemporalPlan p;
+  long long seqs[kTemporalClasses] = {};
+  for (int s = 0; s < tab.n; ++s)
+    if (tab.pix_cu[s + 1] > tab.pix_cu[s]) seqs[temporal_class(temporal_frames(tab, s))] += (long long)tab.hw[s] * n_heads;
+  for (int c = 0; c < kTemporalClasses; ++c) p.launch_of[c] = seqs[c] > 0 ? c : -1;
+  for (int c = 0; c < kTemporalClasses; ++c) {
+    int into = c + 1;
+    while (into < kTemporalClasses && seqs[into] == 0) ++into;
+    if (seqs[c] == 0 || into == kTemporalClasses || !temporal_joins(c, into, seqs[c], head_dim, cus)) continue;
+    seqs[into] += seqs[c];
+    seqs[c] = 0;
+    for (int x = 0; x <= c; ++x)
+      if (p.launch_of[x] == c) p.launch_of[x] = into;
+  }
+  return p;
+}
+
+// The clips of one launch as a table of their own: the other clips keep their place and have no pixels.
+inline TemporalTable temporal_launch_table(const TemporalTable& tab, const TemporalPlan& plan, int launch) {
+  TemporalTable t = tab;
+  int pix = 0;
+  for (int s = 0; s <= VFM_MAX_SEQS; ++s) {
+    t.pix_cu[s] = pix;
+    if (s < tab.n && tab.pix_cu[s + 1] > tab.pix_cu[s] && plan.launch_of[temporal_class(temporal_frames(tab, s))] == launch)
+      pix += tab.hw[s];
+  }
+  return t;
+}
+
+// Workgroups and threads of launches 0 to 4.  A tensor holds at most 2^25 (token, head) rows; a class 0
+// sequence is at least one of them and takes 64 threads, a class c sequence at least 32 c - 31 (c = 1:
+// 17) and 128 c threads in the backward: 2^31 threads at most (few more with the sequences that joined),
+// where one launch can have 2^32 - 1.
+struct TemporalGrid { unsigned blocks, threads; };
+inline TemporalGrid temporal_grid(const TemporalTable& t, int launch, int n_heads, bool backward) {
+  const long long units = (long long)t.pix_cu[t.n] * n_heads;
+  if (launch == 0) return {(unsigned)((units + 3) / 4), 256u};                 // four sequences per workgroup
+  return {(unsigned)units, (unsigned)(launch * (backward ? 128 : 64))};        // one wave per block (and role)
+}
+
+// The clips of launch 5: a work unit is one 32-row block of one (pixel, head) sequence.
 struct TemporalLTable {
   int n;
   int cu[VFM_MAX_SEQS + 1];      // first packed token of clip s
@@ -419,6 +487,9 @@ inline hipError_t launch(void (*kern)(P...), dim3 grid, dim3 block, size_t lds, 
 }
 
 // ---- launchers (defined next to their kernels) -----------------------------
+// Compute units of the current device (asked once; 256 on MI355X, also the fallback).
+int compute_unit_count();
+
 // The RoPE launchers work on the tokens [tab.cu[0], tab.cu[tab.n]) of the clips in tab.
 hipError_t launch_rope3d(void* x, const RopeTable& tab, int n_heads, int head_dim,
                          int dim_t, int dim_h, int dim_w, float theta, int inverse,

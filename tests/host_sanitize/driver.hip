@@ -49,11 +49,46 @@ hipError_t launch_qknorm_rope3d_bwd(const void*, const void*, void*, const float
   ++g_launches; check_rope_table(tab); return hipSuccess;
 }
 hipError_t launch_zero_f32(float*, int, hipStream_t) { ++g_launches; return hipSuccess; }
-hipError_t launch_tattn_fwd(const void*, const void*, const void*, const TemporalTable& t, int, int, float, void*,
+// The launches by frame class: every pixel of every clip in exactly one launch table, at its place and with
+// its own frame count, no clip in kernels too short for it, only few in kernels made for longer ones,
+// and no launch of 2^32 threads or more.
+static void check_temporal_launches(const TemporalTable& t, int heads, int hd) {
+  const TemporalPlan plan = make_temporal_plan(t, heads, hd, 256);
+  std::vector<int> seen(VFM_MAX_SEQS, 0);
+  long pixels = 0;
+  for (int l = 0; l < kTemporalClasses; ++l) {
+    const TemporalTable c = temporal_launch_table(t, plan, l);
+    EXPECT(c.n == t.n && c.pix_cu[0] == 0 && (c.pix_cu[t.n] > 0) == (plan.launch_of[l] == l));
+    long long joined = 0;
+    for (int s = 0; s < t.n; ++s) {
+      const int pix = c.pix_cu[s + 1] - c.pix_cu[s];
+      EXPECT(c.cu[s] == t.cu[s] && c.cu[s + 1] == t.cu[s + 1] && c.hw[s] == t.hw[s]);
+      if (pix == 0) continue;
+      const int frames = temporal_frames(c, s);
+      EXPECT(pix == t.hw[s] && pix * frames == t.cu[s + 1] - t.cu[s]);
+      EXPECT(l == 5 || frames <= (l == 0 ? 16 : 32 * l));
+      if (temporal_class(frames) != l) joined += (long long)pix * heads;
+      ++seen[s];
+    }
+    EXPECT(joined <= 256 * 9 * 4);
+    pixels += c.pix_cu[t.n];
+    if (l < 5)
+      for (bool backward : {false, true}) {
+        const TemporalGrid g = temporal_grid(c, l, heads, backward);
+        const long long waves = (long long)c.pix_cu[t.n] * heads * (l == 0 ? 1 : l * (backward ? 2 : 1));
+        EXPECT((long long)g.blocks * g.threads >= waves * 64 && (long long)g.blocks * g.threads < waves * 64 + 256);
+        EXPECT((long long)g.blocks * g.threads < 1LL << 32);
+      }
+  }
+  EXPECT(pixels == t.pix_cu[t.n]);
+  for (int s = 0; s < t.n; ++s) EXPECT(seen[s] == (t.cu[s + 1] > t.cu[s]));
+}
+hipError_t launch_tattn_fwd(const void*, const void*, const void*, const TemporalTable& t, int heads, int hd, float, void*,
                             hipStream_t) {
   ++g_launches;
   EXPECT(t.n >= 0 && t.n <= VFM_MAX_SEQS);
   for (int s = 0; s < t.n; ++s) { EXPECT(t.hw[s] >= 1 && t.pix_cu[s] <= t.pix_cu[s + 1] && t.cu[s] <= t.cu[s + 1]); }
+  check_temporal_launches(t, heads, hd);
   return hipSuccess;
 }
 hipError_t launch_tattn_bwd(const void* q, const void* k, const void* v, const void*, const TemporalTable& t, int h, int d,
@@ -175,6 +210,15 @@ int main() {
       EXPECT(g_launches == before);
     }
   }
+  // temporal attention at the size limit: the largest tensors (2^25 and 2^24 rows) as single frames, as the shortest
+  // clips of every class, and as single frames beside one long clip
+  for (int hd : {64, 128})
+    for (int frames : {1, 16, 17, 32, 33, 64, 65, 96, 97, 128, 129, 300})
+      for (int beside : {0, 100, 300}) {
+        const int rows = (int)((1LL << 31) / hd) - 300, pix = (rows - beside) / frames;
+        const int32_t thw[6] = {frames, 1, pix, beside, 1, beside ? 1 : 0}, cu[3] = {0, frames * pix, frames * pix + beside};
+        EXPECT(vfm_tattn_bwd(P, P, P, P, thw, cu, 2, cu[2], 1, hd, 0.1f, P, P, P, VFM_BF16, nullptr) == VFM_OK);
+      }
   printf("%s: %ld stub launches, %d failures\n", g_failures ? "FAILED" : "ok", g_launches, g_failures);
   return g_failures ? 1 : 0;
 }

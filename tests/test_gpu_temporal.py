@@ -135,3 +135,60 @@ def test_block_edges(frames, head_dim):
     wl = W.Workload(f"edge{frames}", ((frames, 1, 3), (5, 2, 1)), 2, head_dim, (0, head_dim // 2, head_dim // 2), seed=frames)
     dev, gpu = _run(_binding(), wl)
     _check(wl, gpu, dev)
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_clips_take_the_kernels_of_their_own_frame_count(head_dim):
+    """A call that holds every class of frame counts, each with more sequences than join a longer class: a clip's
+    results are to the bit what a call of its own gives.  One class is spread over two clips around an
+    empty one."""
+    import torch
+    frames = (5, 100, 1, 17, 0, 200, 70, 16, 40, 129, 32)
+    wl = W.Workload("classes", tuple((t, 29, 30) for t in frames), 12, head_dim, (0, head_dim // 2, head_dim // 2), seed=51)
+    b = _binding()
+    gen = torch.Generator(device="cuda").manual_seed(51)
+    dev = {n: torch.empty((wl.total_tokens, 12, head_dim), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+           for n in ("q", "k", "v", "dout")}
+
+    def both_ways(x, thw, cu):
+        return (b.vfm_tattn_fwd(x["q"], x["k"], x["v"], thw, cu, wl.scale),
+                *b.vfm_tattn_bwd(x["q"], x["k"], x["v"], x["dout"], thw, cu, wl.scale))
+
+    gpu = both_ways(dev, wl.thw, wl.cu_seqlens)
+    for i in range(len(frames)):
+        lo, hi = int(wl.cu_seqlens[i]), int(wl.cu_seqlens[i + 1])
+        if lo == hi:
+            continue
+        alone = both_ways({n: t[lo:hi].contiguous() for n, t in dev.items()}, wl.thw[i:i + 1], [0, hi - lo])
+        for nm, x, y in zip(("out", "dq", "dk", "dv"), gpu, alone):
+            assert torch.equal(x[lo:hi].view(torch.int16), y.view(torch.int16)), (nm, frames[i])
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_few_short_clips_join_longer_ones(head_dim):
+    # every class of frame counts in one small call: all of them end in the kernels of the longest
+    wl = W.Workload("few", tuple((t, 1, 2 + i % 3) for i, t in enumerate((5, 100, 1, 17, 0, 200, 70, 16, 40, 129, 32))), 3,
+                    head_dim, (0, head_dim // 2, head_dim // 2), seed=52)
+    dev, gpu = _run(_binding(), wl)
+    _check(wl, gpu, dev)
+
+
+def test_many_pixels_beside_a_long_clip():
+    """262,144 single-frame pixels and 32 heads beside one 100-frame clip: 2^23 sequences, which at a workgroup
+    of the long clip's size each would be more threads than a launch can have.  Single frames copy v
+    and dout to the bit (P is within a few fp32 ulp of 1); dS = P (dP - P dP) is within 2^-21 |dP| of 0, and
+    with |dP| < 100, |q|, |k| < 8 and the scale 1/11 so are the gradients of q and k within 4e-5."""
+    import torch
+    b = _binding()
+    n, t, heads, hd = 512 * 512, 100, 32, 128
+    thw = np.array([[1, 512, 512], [t, 1, 1]], dtype=np.int32)
+    cu = [0, n, n + t]
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    q, k, v, do = (torch.empty((n + t, heads, hd), dtype=torch.bfloat16, device="cuda").normal_(generator=gen) for _ in range(4))
+    out = b.vfm_tattn_fwd(q, k, v, thw, cu, hd ** -0.5)
+    dq, dk, dv = b.vfm_tattn_bwd(q, k, v, do, thw, cu, hd ** -0.5)
+    assert torch.equal(out[:n], v[:n]) and torch.equal(dv[:n], do[:n])
+    assert dq[:n].abs().max() <= 4e-5 and dk[:n].abs().max() <= 4e-5
+    wl = W.Workload("tail", ((t, 1, 1),), heads, hd, (0, 64, 64), seed=0)
+    tail = {name: x[n:].contiguous() for name, x in (("q", q), ("k", k), ("v", v), ("dout", do))}
+    _check(wl, tuple(x[n:].contiguous() for x in (out, dq, dk, dv)), tail)
