@@ -340,8 +340,12 @@ __device__ __forceinline__ bf16x8 half_to_bf16(const f32x16& x, int s2) {
 // workgroup owns one (pixel, head), gathers every row once, needs nothing from memory after that
 // and stores whole rows: bound by HBM.  NB = 32-row blocks of the longest sequence of the launch;
 // shorter ones (few, see temporal_joins) skip the blocks they do not have (uniform branches).
-// Forward: wave b owns query block b and holds its whole score row S^T in registers (NB 32 x 32
-// tiles), so the softmax is exact and needs no rescaling.
+// Forward: wave b owns query block b and takes the key blocks in turn with a running reference.  (The
+// whole row's maximum could be known first, but P relative to a running one has more elements that
+// are exactly 1 in bf16: out is 2.11e-3 instead of 2.16e-3 from 64-bit arithmetic at 128 frames.  The
+// accumulators' rescaling cost 2 to 4% at 97 to 128 frames of head_dim 128, where one workgroup has the CU
+// to itself; forming the scores before the values have landed gives 9: 128 frames x 1,500 pixels x
+// 8 heads 391 us with the row's maximum, 405 with the running one, now 368, 4.3 TB/s.)
 // Measured at head_dim 128, forward and backward together, against the kernels that walk 32-row
 // blocks (below), which read q, k, v, dout three times in the backward: 64 frames x 3,520
 // pixels x 8 heads 2.36 -> 1.07 ms (4.7 TB/s of the 11 tensors; a large copy reaches 5.0), 40
@@ -412,42 +416,61 @@ __global__ __launch_bounds__(NB * 64, 2) void tattnB_fwd_kernel(const __bf16* __
   gather_blocks<D, NB, NB>(q, u, n_blk, row_bytes, lds0, wave, lane);
   gather_blocks<D, NB, NB>(k, u, n_blk, row_bytes, lds0 + NB * TB, wave, lane);
   gather_blocks<D, NB, NB>(v, u, n_blk, row_bytes, lds0 + 2 * NB * TB, wave, lane);
-  wait_vmcnt<0>();
+  // the scores are formed while the values are still on their way
+  if (n_blk == NB) wait_vmcnt<T2Cfg<D>::kLoadsPerTile>(); else wait_vmcnt<0>();   // (a wave's v pieces: as many if all blocks exist)
   __syncthreads();
-  if (wave >= n_blk) return;         // (no barrier below)
 
-  bf16x8 qf[KS];
-  read_rows32<D>(qt + wave * TB, lane, qf);
   f32x16 s[NB];
-  float mx = -INFINITY;
+  float m[NB];                    // reference of block kb: the largest score of blocks 0..kb, log2 units
+  if (wave < n_blk) {
+    bf16x8 qf[KS];
+    read_rows32<D>(qt + wave * TB, lane, qf);
 #pragma unroll
-  for (int kb = 0; kb < NB; ++kb) {
-    if (kb < n_blk) {
-      bf16x8 kf[KS];
-      read_rows32<D>(kt + kb * TB, lane, kf);
-      s[kb] = kZero16;
+    for (int kb = 0; kb < NB; ++kb) {
+      if (kb < n_blk) {
+        bf16x8 kf[KS];
+        read_rows32<D>(kt + kb * TB, lane, kf);
+        s[kb] = kZero16;
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) s[kb] = mfma32(kf[ks], qf[ks], s[kb]);
-      // lane: query l%32 of the block; register r: key 32*kb + 8*(r/4) + 4g + r%4
+        for (int ks = 0; ks < KS; ++ks) s[kb] = mfma32(kf[ks], qf[ks], s[kb]);
+        // lane: query l%32 of the block; register r: key 32*kb + 8*(r/4) + 4g + r%4
+        float mx = -INFINITY;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        if (kb * kT2Rows + 8 * (r >> 2) + 4 * g + (r & 3) >= u.T) s[kb][r] = -INFINITY;
-        mx = fmaxf(mx, s[kb][r]);
+        for (int r = 0; r < 16; ++r) {
+          if (kb * kT2Rows + 8 * (r >> 2) + 4 * g + (r & 3) >= u.T) s[kb][r] = -INFINITY;
+          mx = fmaxf(mx, s[kb][r]);
+        }
+        mx = pair_max(mx) * scale_log2;
+        m[kb] = kb == 0 ? mx : fmaxf(m[kb > 0 ? kb - 1 : 0], mx);
       }
     }
   }
-  const float m2 = pair_max(mx) * scale_log2;
-  float sum = 0.f;
+  wait_vmcnt<0>();
+  __syncthreads();
+  if (wave >= n_blk) return;      // (no barrier below)
+
+  float l = 0.f;                  // sum of this lane's half of the keys
   f32x16 oacc[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db) oacc[db] = kZero16;
 #pragma unroll
   for (int kb = 0; kb < NB; ++kb) {
     if (kb < n_blk) {
+      float sum = 0.f;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        s[kb][r] = fast_exp2(s[kb][r] * scale_log2 - m2);
+        s[kb][r] = fast_exp2(s[kb][r] * scale_log2 - m[kb]);
         sum += s[kb][r];
+      }
+      if (kb == 0) {
+        l = sum;
+      } else {
+        const float alpha = fast_exp2(m[kb > 0 ? kb - 1 : 0] - m[kb]);
+        l = l * alpha + sum;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
       }
       const bf16x8 p0 = half_to_bf16(s[kb], 0), p1 = half_to_bf16(s[kb], 1);
 #pragma unroll
@@ -457,7 +480,7 @@ __global__ __launch_bounds__(NB * 64, 2) void tattnB_fwd_kernel(const __bf16* __
       }
     }
   }
-  const float inv = 1.0f / pair_sum(sum);
+  const float inv = 1.0f / pair_sum(l);
   // this wave's q tile is its own: turn the result through it and store whole rows
   store_tile_rows<D>(qt + wave * TB, oacc, inv,
                      out + (size_t)(u.first_row + wave * kT2Rows * u.hw) * row_stride + (size_t)u.head * D,
