@@ -33,7 +33,11 @@
  *     VFM_MAX_SEQS clips, so a call with more is cut, inside the library, into
  *     consecutive launches on hip_stream over runs of VFM_MAX_SEQS clips in
  *     packed order (VFM_MAX_XSEQS sequences for cross-attention).  Clips are
- *     independent, so the result does not depend on where the runs are cut.
+ *     independent, so the result does not depend on where the runs are cut, nor on
+ *     what else is in the call: to the bit where every output is written once
+ *     (self-attention, position encoding and its dx, FP8 packing, cross-attention
+ *     without split queries), up to the rounding of sums in temporal attention and
+ *     where fp32 atomics are named below.
  *   - Every function returns a vfm_status; 0 is success.  Argument errors are
  *     detected before anything is launched and leave all outputs untouched.
  *   - Re-entrant: no global mutable state (beyond the calling thread's last

@@ -98,6 +98,13 @@ __global__ __launch_bounds__(256) void bwd_prepare_kernel(const u32x4* __restric
 // a sequence, over the tiles of those sequences only.
 constexpr int kShortKeys = 32;
 
+// A product that is rounded by itself, not within a fused multiply-add: two kernels that sum such products
+// in the same order get the same bits.
+__device__ __forceinline__ float mul_alone(float a, float b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
+
 template <int D, class Segs>
 __global__ __launch_bounds__(64) void bwd_short_delta_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
@@ -125,13 +132,17 @@ __global__ __launch_bounds__(64) void bwd_short_delta_kernel(
     dp = mfma32(*reinterpret_cast<const bf16x8*>(v + koff + ks * 16),
                 *reinterpret_cast<const bf16x8*>(dout + qoff + ks * 16), dp);
   }
-  float acc = 0.f;                                       // this lane's 16 keys of query i
+  // summed in the order of the key's index bits, 0 to 4, as the one-pass kernel does over its lanes
+  float y[4];                                            // keys 8 x .. 8 x + 7 of query i
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int j = 8 * (r >> 2) + 4 * g + (r & 3);
-    if (j < nk) acc += fast_exp2(s[r] * scale_log2 - lse_i) * dp[r];
+  for (int x = 0; x < 4; ++x) {
+    float t[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      t[e] = 8 * x + 4 * g + e < nk ? mul_alone(fast_exp2(s[4 * x + e] * scale_log2 - lse_i), dp[4 * x + e]) : 0.f;
+    y[x] = pair_sum((t[0] + t[1]) + (t[2] + t[3]));
   }
-  acc = pair_sum(acc);
+  const float acc = (y[0] + y[1]) + (y[2] + y[3]);
   if (i < q_b && g == 0) delta[(size_t)head * total + i] = acc;
 }
 
@@ -854,8 +865,9 @@ void bwd_dq2_unit(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) oreg[ks] = *reinterpret_cast<const bf16x8*>(out + off + ks * 16);
       lse2[ib] = lse[stat] * kLog2eB;
-      // the order of bwd_prepare_kernel's sums (chunks of 8 columns, then pairs of chunks 8, 4, 2, 1 apart), so
-      // that a clip's gradients do not depend, to the bit, on what else is in the pack
+      // the order of bwd_prepare_kernel's sums (chunks of 8 columns, then pairs of chunks 8, 4, 2, 1 apart; the
+      // one-pass kernel's too), so that a clip's gradients do not depend, to the bit, on what else is in
+      // the pack
       float s[KS];
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
@@ -1313,8 +1325,9 @@ void attn_bwd_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restric
       float s = 0.f;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        s += __builtin_bit_cast(float, oa[i][e] << 16) * __builtin_bit_cast(float, da[i][e] << 16);
-        s += __builtin_bit_cast(float, oa[i][e] & 0xffff0000u) * __builtin_bit_cast(float, da[i][e] & 0xffff0000u);
+        s = __builtin_fmaf(__builtin_bit_cast(float, oa[i][e] << 16), __builtin_bit_cast(float, da[i][e] << 16), s);
+        s = __builtin_fmaf(__builtin_bit_cast(float, oa[i][e] & 0xffff0000u),
+                           __builtin_bit_cast(float, da[i][e] & 0xffff0000u), s);
       }
 #pragma unroll
       for (int o = CPR / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, CPR);
@@ -1343,13 +1356,18 @@ void attn_bwd_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restric
     for (int x = 0; x < 2; ++x)
 #pragma unroll
       for (int h = 0; h < NROW; ++h) acc[x][h] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // contraction slot 4t + r of lane group l/16: key 8 (l/16) + 4t + r of a block of 32
+    // The instruction sums its 32 products in four groups of 8, one per lane group l/16, in that order;
+    // the order within a group does not matter (measured: the same bits).  Lane group h takes keys
+    // 16 (h/2) + 4 (h%2) + {0..3, 8..11}, which are the groups of the two-pass kernels' two 32x32x16 products, so
+    // that dq is theirs to the bit.  Odd lane groups read the upper four first: rows read together then
+    // differ in row/4 mod 4, which keeps them on different banks.
     int ln = lane;
     asm volatile("" : "+v"(ln));
     int ktr[2], dtr[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      const int row = 8 * (ln >> 4) + 4 * t + ((ln & 15) >> 2);
+      const int odd = (ln >> 4) & 1;
+      const int row = 16 * (ln >> 5) + 4 * odd + 8 * (t ^ odd) + ((ln & 15) >> 2);
       ktr[t] = tile_off<D>(row, col0 + 4 * (ln & 3));
       dtr[t] = Cfg::kDsBase + row * 64 + (((half0 * 2 + ((ln & 3) >> 1)) ^ ((row >> 2) & 3)) << 4) + (ln & 1) * 8;
     }
@@ -1463,10 +1481,10 @@ void attn_bwd_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restric
           dl[q4 * 4 + e] = d4[e];
         }
       }
-      if (n <= kShortKeys) {   // few keys: Delta in its cancellation-free form, sum_j P_ij dP_ij
+      if (n <= kShortKeys) {   // few keys: Delta in its cancellation-free form, sum_j P_ij dP_ij (order: see there)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          float x = jrow < n ? p[r] * dp[r] : 0.f;
+          float x = jrow < n ? mul_alone(p[r], dp[r]) : 0.f;
 #pragma unroll
           for (int o = 1; o < 32; o <<= 1) x += __shfl_xor(x, o, 32);
           dl[r] = x;

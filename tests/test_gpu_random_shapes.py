@@ -93,6 +93,38 @@ def test_one_pass_backward_block_edges(head_dim, lengths):
     _assert_parity(wl, gpu, host, relative_maxabs=True)
 
 
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("lengths", [(64, 63, 33, 32, 31, 17, 5, 2, 1), (128, 127, 97, 65, 32, 16),
+                                     (256, 255, 225, 193, 160, 129, 33, 8)], ids=["64", "128", "256"])
+def test_a_clip_does_not_depend_on_its_pack_mates(head_dim, lengths):
+    """Clips of at most 256 tokens take the one pass or the two-pass kernels by what else is in the run, and
+    equal ranges may come through the cross-attention entry: every route gives the same bits."""
+    import torch
+    from paper_2503_12964_amd import binding as b
+    lens, heads = lengths * 6, 4        # 144 units and more: the one pass
+    n = sum(lens)
+    gen = torch.Generator(device="cuda").manual_seed(head_dim + lengths[0])
+    x = [torch.empty((n + 1100, heads, head_dim), device="cuda").normal_(generator=gen).to(torch.bfloat16) for _ in range(4)]
+
+    def run(lo, hi, cu, cross=False):
+        q, k, v, do = (t[lo:hi].contiguous() for t in x)
+        cu = np.asarray(cu, dtype=np.int32)
+        scale = head_dim ** -0.5
+        fwd = b.vfm_xattn_fwd(q, k, v, cu, cu, scale) if cross else b.vfm_attn_fwd(q, k, v, cu, scale)
+        bwd = b.vfm_xattn_bwd(q, k, v, *fwd, do, cu, cu, scale) if cross else b.vfm_attn_bwd(q, k, v, *fwd, do, cu, scale)
+        return [fwd[0], fwd[1].T.contiguous(), *bwd]
+
+    cu = np.concatenate([[0], np.cumsum(lens)])
+    want = run(0, n, cu)
+    routes = {"beside 1,100 tokens": (0, n, run(0, n + 1100, [*cu, n + 1100])), "cross": (0, n, run(0, n, cu, cross=True))}
+    for i in range(len(lengths)):
+        lo, hi = int(cu[i]), int(cu[i + 1])
+        routes[f"alone {lens[i]}"] = (lo, hi, run(lo, hi, [0, hi - lo]))
+    for route, (lo, hi, got) in routes.items():
+        for nm, g, w in zip(("out", "lse", "dq", "dk", "dv"), got, want):
+            assert torch.equal(g[:hi - lo], w[lo:hi]), (route, nm)
+
+
 def test_one_pass_backward_under_graph_replay_and_without_workspace():
     """The one pass ignores the statistics buffers: both entry points give the same bits, and a
     captured call gives them again on every replay."""
