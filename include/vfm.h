@@ -177,7 +177,9 @@ VFM_API size_t vfm_attn_bwd_workspace_size(int total_tokens, int n_heads, int he
  *     dq_i   = scale * sum_j dS_ij k_j
  *     dk_j   = scale * sum_i dS_ij q_i
  * dq, dk, dv: bf16 [total_tokens, n_heads, head_dim], fully overwritten (not
- * accumulated into).  workspace: device, 256-byte aligned, at least
+ * accumulated into).  dq may be the same buffer as q or as dout (the same bits as
+ * in a buffer of its own; also in vfm_attn_bwd_noalloc and vfm_xattn_bwd); the
+ * outputs must not overlap the inputs in any other way.  workspace: device, 256-byte aligned, at least
  * vfm_attn_bwd_workspace_size() bytes.  No atomics are used: dq, dk and dv are
  * bitwise reproducible from run to run.
  * Accuracy: Delta_i = sum_d dout[i,d] out[i,d] is formed from the bf16 `out`

@@ -1564,9 +1564,6 @@ static hipError_t launch_bwd_fused(const __bf16* q, const __bf16* k, const __bf1
                 um, total, n_heads, scale, scale * kLog2eB);
 }
 
-// Sequences up to this many rows (queries and keys) take the single launch above.
-constexpr int kBothMaxRows = 1024;
-
 int compute_unit_count() {
   static std::atomic<int> cached{0};
   int n = cached.load(std::memory_order_relaxed);
@@ -1626,12 +1623,7 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
   const int cus = compute_unit_count();
   if (dkv32 && tiles > 0 && tiles * n_heads < cus)
     q_split = std::min(std::min(16, (cus + tiles * n_heads - 1) / (tiles * n_heads)), std::max(1, max_q / 512));
-  const bool both = D == 128 && q_split == 1 && longest <= kBothMaxRows;
-  // At head_dim 128 the dQ pass runs first and forms the statistics on the way (backward call, separate
-  // pass -> here: 20,000 queries x 300 keys x 16 heads 413 -> 403 us, 2 x 4,096 tokens x 16 heads 785 -> 775,
-  // 12,000 tokens x 4 heads level).  Elsewhere, and where dq takes the place of an operand that the
-  // dK/dV pass reads, they come from a pass of their own.
-  const bool dq_first = D == 128 && !both && dq != q && dq != dout;
+  const auto [both, dq_first] = bwd_order(D, q_split, longest, dq == q || dq == dout);
   if (max_q > 0) {   // (with no queries at all only the keys' zero gradients remain to be written)
     if (!dq_first) {
       e = launch_bwd_prepare(out, dout, lse, delta, lse2, sentinel, total, n_heads, D, tok0, tok_end, stream);

@@ -259,6 +259,21 @@ inline bool bwd_one_pass(int longest, int n_clips, int n_heads, int head_dim) {
   return (long long)n_clips * n_heads * (longest > 128 ? 3 : 2) > 256;
 }
 
+// The passes of a run that does not take the one-pass backward.  both: dK/dV and dQ units from one grid,
+// where no sequence has more than this many rows (queries or keys).  dq_first: the dQ pass runs before
+// the dK/dV pass and forms the statistics on the way (backward call at head_dim 128, separate pass ->
+// here: 20,000 queries x 300 keys x 16 heads 413 -> 403 us, 2 x 4,096 tokens x 16 heads 785 -> 775, 12,000
+// tokens x 4 heads level).  Without dq_first the statistics come from a pass of their own, without either
+// (head_dim 64) dQ comes last.  The dK/dV workgroups of a sequence read all of its q and dout rows: where dq takes the place
+// of either it has to be written after all of them are done, so neither of the first two will do.
+constexpr int kBothMaxRows = 1024;
+struct BwdOrder { bool both, dq_first; };
+inline BwdOrder bwd_order(int head_dim, int q_split, int longest, bool dq_over_input) {
+  if (head_dim != 128 || dq_over_input) return {false, false};
+  const bool both = q_split == 1 && longest <= kBothMaxRows;
+  return {both, !both};
+}
+
 // LDS tiles hold rows of D bf16 without padding; the 16-byte chunk index within
 // a row is XOR-ed with a function of the row so that both row-wise 16-byte reads
 // (16 consecutive rows, one chunk) and transposing 8-byte reads (4 consecutive

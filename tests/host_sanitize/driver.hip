@@ -142,7 +142,23 @@ template hipError_t launch_attn_bwd<XSegTable>(const void*, const void*, const v
                                                float*, float*, int, int, int, hipStream_t);
 }  // namespace vfm
 
+// dq over q or dout must be written after every dK/dV workgroup has read them: never from the grid that
+// holds both kinds of unit, never first.
+static void check_bwd_order() {
+  for (int hd : {64, 128})
+    for (int split : {1, 2, 16})
+      for (int longest : {1, 32, 257, 1024, 1025, 56320})
+        for (bool over : {false, true}) {
+          const vfm::BwdOrder o = vfm::bwd_order(hd, split, longest, over);
+          EXPECT(!(o.both && o.dq_first));
+          if (over) EXPECT(!o.both && !o.dq_first);
+          if (o.both) EXPECT(hd == 128 && split == 1 && longest <= 1024);
+          if (!over && hd == 128) EXPECT(o.both || o.dq_first);
+        }
+}
+
 int main() {
+  check_bwd_order();
   std::mt19937 rng(12345);
   void* const P = reinterpret_cast<void*>(0x10000);     // never dereferenced: the stubs launch nothing
   float* const F = reinterpret_cast<float*>(0x20000);

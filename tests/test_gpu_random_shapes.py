@@ -160,3 +160,35 @@ def test_statistics_from_the_dq_pass(lengths):
     q, k, v, do = (U.to_device(W.make_inputs(wl)[n]) for n in ("q", "k", "v", "dout"))
     got = b.vfm_attn_bwd(q, k, v, gpu[0], gpu[1], do, wl.cu_seqlens, wl.scale, dq=do)
     assert all(torch.equal(x.view(torch.int16), y.view(torch.int16)) for x, y in zip(got, gpu[2:]))
+
+
+@pytest.mark.parametrize("cross", [False, True], ids=["self", "cross"])
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("lengths,heads", [((1000, 700, 300, 20), 3), ((256, 129, 31), 2), ((200, 64, 256, 7) * 20, 3), ((1300, 40), 2)],
+                         ids=["one_grid", "few_short", "one_pass", "two_passes"])
+def test_dq_in_place_of_q_or_dout(lengths, heads, head_dim, cross):
+    """dq may be the buffer of q or of dout: the rows that a workgroup overwrites with dq are read by every
+    dK/dV workgroup of the sequence, so the two must not run side by side.  Same bits as without."""
+    import torch
+    from paper_2503_12964_amd import binding as b
+    cu = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    gen = torch.Generator(device="cuda").manual_seed(int(cu[-1]))
+    q, k, v, do = (torch.empty((int(cu[-1]), heads, head_dim), device="cuda").normal_(generator=gen).to(torch.bfloat16)
+                   for _ in range(4))
+    scale = head_dim ** -0.5
+    out, lse = b.vfm_attn_fwd(q, k, v, cu, scale)
+
+    def bwd(qq, dd, dq):
+        if cross:
+            return b.vfm_xattn_bwd(qq, k, v, out, lse, dd, cu, cu, scale, dq=dq)
+        return b.vfm_attn_bwd(qq, k, v, out, lse, dd, cu, scale, dq=dq)
+
+    want = bwd(q, do, None)
+    for over in ("q", "dout"):
+        qq, dd = q.clone(), do.clone()
+        got = bwd(qq, dd, qq if over == "q" else dd)
+        names = ("dq", "dk", "dv")
+        if cross and max(lengths) >= 1024:      # split queries: dk, dv are summed with atomics
+            names = ("dq",)
+        for nm, g, w in zip(names, got, want):
+            assert torch.equal(g, w), (over, nm)
