@@ -73,13 +73,19 @@ def test_single_frame_clip_copies_values_and_has_zero_qk_gradients():
 
 
 LONG = {
-    # more than 32 frames (Section 4.6: videos of hundreds of frames): 33, 48, 121 frames, block
-    # multiples (64, 96) and short clips, an empty and a single-frame one in the same call
+    # more than 32 frames (Section 4.6: videos of hundreds of frames).  Up to 128, a workgroup per sequence: 33,
+    # 48, 121 frames, block multiples (64, 96) and short clips, an empty and a single-frame one in the call
     "t128_33_48": W.Workload("t128_33_48", ((33, 2, 3), (48, 1, 5), (4, 3, 3), (0, 1, 1), (1, 2, 2), (64, 1, 2)), 3, 128,
                              (32, 48, 48), seed=35),
     "t128_121": W.Workload("t128_121", ((121, 3, 2), (96, 1, 1), (17, 2, 2)), 2, 128, (32, 48, 48), seed=36),
     "t64_long": W.Workload("t64_100", ((100, 2, 2), (33, 1, 3), (65, 1, 1), (2, 2, 2)), 2, 64, (16, 24, 24), seed=37),
     "t128_300": W.Workload("t128_300", ((300, 1, 2),), 1, 128, (32, 48, 48), seed=38),
+    # more than 128, a wavefront per 32-row block: block multiples and both sides of one, several long clips, and
+    # short, empty and single-frame ones, few enough to be walked in blocks with them
+    "t128_129_200": W.Workload("t128_129_200", ((129, 2, 3), (200, 1, 2), (0, 1, 1), (1, 2, 2), (160, 1, 3), (17, 1, 2), (100, 1, 1)),
+                               2, 128, (32, 48, 48), seed=39),
+    "t64_161_300": W.Workload("t64_161_300", ((161, 1, 3), (1, 1, 1), (300, 2, 1), (0, 2, 2), (64, 1, 2), (9, 2, 2)), 3, 64,
+                              (16, 24, 24), seed=40),
 }
 
 
@@ -90,11 +96,13 @@ def test_more_than_thirty_two_frames(name):
     _check(wl, gpu, dev)
 
 
-def test_long_clip_statistics_do_not_leak_into_dq():
-    # with more than 32 frames the dq rows carry the queries' statistics while the call runs; afterwards
-    # every dq element is a gradient, also after a second call into the same buffers
+@pytest.mark.parametrize("name", ["t128_33_48", "t128_129_200", "t64_161_300"])
+def test_long_clip_statistics_do_not_leak_into_dq(name):
+    # with more than 128 frames the dq rows carry the queries' statistics while the call runs; afterwards
+    # every dq element is a gradient, also after a second call into the same buffers.  (Up to 128 frames
+    # the statistics are in LDS: buffers full of NaN must not matter there either.)
     import torch
-    wl = LONG["t128_33_48"]
+    wl = LONG[name]
     b = _binding()
     inp = W.make_inputs(wl)
     dev = {n: U.to_device(inp[n]) for n in ("q", "k", "v", "dout")}
@@ -109,7 +117,7 @@ def test_long_clip_statistics_do_not_leak_into_dq():
 
 
 def test_single_frame_clip_in_a_long_call():
-    # the 32-row kernels serve every clip of a call that has a long one
+    # a few single frames beside clips of up to 32 frames are served by the latter's kernels
     wl = CASES["t128_long"]
     dev, (out, dq, dk, dv) = _run(_binding(), wl)
     a, b = int(wl.cu_seqlens[5]), int(wl.cu_seqlens[6])      # the (1,3,1) clip
