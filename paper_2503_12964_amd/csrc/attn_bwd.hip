@@ -1199,7 +1199,7 @@ void attn_bwd_both_kernel(const __bf16* __restrict__ q, const __bf16* __restrict
 }
 
 // ---------------------------------------------------------------- sequences of up to 256 tokens: one pass
-// Self-attention over clips of at most kFusedMaxRows tokens: one workgroup owns a whole (clip, head), so
+// Self-attention over clips of at most kOnePassMaxRows tokens: one workgroup owns a whole (clip, head), so
 // that the five products of the backward are formed once (the two passes above form seven), every
 // operand comes from memory once and Delta needs no pass of its own.  What bounds such packs is the
 // memory path (eight tensors of the clip against 10 D flops per pair of few pairs).
@@ -1230,6 +1230,9 @@ struct FusedCfg {
   static constexpr int kStatBase = kDsBase + kRows * 64;     // dS: [key][32 queries] bf16; then lse2, Delta
   static constexpr int kLdsBytes = kStatBase + 2 * kRows * 4;
   static constexpr int kLoads = D / 8 / NW;                  // wave loads per block (Q and dO together)
+  // Neighbouring (clip, head) units per XCD: one at head_dim 128 (256 bytes of a row each; groups of 8 take 3%
+  // longer), 8 at head_dim 64 (1 KB of a row; single units take 2 to 4% longer).
+  static constexpr int kGroup = D == 128 ? 1 : 8;
 };
 
 template <int D, int NW>
@@ -1238,8 +1241,7 @@ void attn_bwd_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restric
                            const __bf16* __restrict__ v, const __bf16* __restrict__ out,
                            const float* __restrict__ lse, const __bf16* __restrict__ dout,
                            __bf16* __restrict__ dq, __bf16* __restrict__ dk, __bf16* __restrict__ dv,
-                           const SegTable segs, const UnitMap um, int total, int n_heads, float scale,
-                           float scale_log2) {
+                           const SegTable segs, int total, int n_heads, float scale, float scale_log2) {
   using Cfg = FusedCfg<D, NW>;
   constexpr int KS = D / 16, DB = D / 32, CPR = D / 8, RB = D * 2;
   constexpr int BB = Cfg::kBlockBytes;
@@ -1247,9 +1249,10 @@ void attn_bwd_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restric
 
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
-  // units run over the heads of a clip first: workgroups side by side read neighbouring columns
-  int seq, head;
-  if (!map_unit(um, blockIdx.x, seq, head)) return;
+  // units run over the heads of a clip first, clips longest first
+  const int unit = dealt_unit(blockIdx.x, Cfg::kGroup);
+  if (unit >= segs.n * n_heads) return;
+  const int seq = unit / n_heads, head = unit - seq * n_heads;
   const int a = segs.start[seq], n = segs.len[seq];
   const int n_blk = (n + 31) / 32;
 
@@ -1440,7 +1443,7 @@ void attn_bwd_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restric
   // instructions meet the other's exponentials
   const bool late_dq = NW == 8 && wave >= 4;
   wait_vmcnt<0>();          // K, the first two blocks
-  int stage = 0;            // b mod 3
+  int stage = 0;            // b mod the ring's stages
   for (int b = 0; b < n_blk; ++b) {
     // block b has landed (only block b+1's loads may be outstanding; dq stores only make the wait
     // stricter), everyone is done with block b-1, dS(b-1) is complete
@@ -1555,13 +1558,12 @@ static hipError_t launch_bwd_fused(const __bf16* q, const __bf16* k, const __bf1
                                    int n_heads, float scale, __bf16* dq, __bf16* dk, __bf16* dv, hipStream_t stream) {
   constexpr int lds = FusedCfg<D, NW>::kLdsBytes;
   static_assert(lds <= 160 * 1024, "LDS of one CU");
-  const UnitMap um = make_unit_map(n_heads, segs.n);   // (clip, head) units, heads first
   auto kern = attn_bwd_fused_kernel<D, NW>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return e;
-  return launch(kern, dim3(um.chunk * kNumXcd), dim3(NW * 64), lds, stream, q, k, v, out, lse, dout, dq, dk, dv, segs,
-                um, total, n_heads, scale, scale * kLog2eB);
+  return launch(kern, dim3(dealt_grid(segs.n * n_heads, FusedCfg<D, NW>::kGroup)), dim3(NW * 64), lds, stream, q, k, v,
+                out, lse, dout, dq, dk, dv, segs, total, n_heads, scale, scale * kLog2eB);
 }
 
 int compute_unit_count() {

@@ -198,6 +198,15 @@ __host__ __device__ __forceinline__ bool map_unit(const UnitMap& um, int block, 
   return true;
 }
 
+// The other way to deal units: in order, round-robin over the XCDs in groups of `group` neighbours.  For units
+// that share no operand but differ in length, longest first: a contiguous chunk per XCD would give one
+// XCD all the long ones.  Grid = dealt_grid(); workgroups whose unit is >= units have none.
+__host__ __device__ __forceinline__ int dealt_unit(int block, int group) {
+  const int local = block / kNumXcd;
+  return (local / group * kNumXcd + block % kNumXcd) * group + local % group;
+}
+inline int dealt_grid(int units, int group) { return (units + kNumXcd * group - 1) / (kNumXcd * group) * kNumXcd * group; }
+
 // Tiles of the sequences before s (table order) for one launch's tile height, built on the host
 // and passed by value beside the sequence table.  A workgroup finds its sequence by binary
 // search in it: walking the table instead costs a dependent scalar load per sequence, which with

@@ -5,6 +5,7 @@
 #include <stdio.h>
 #include <stdlib.h>
 
+#include <algorithm>
 #include <random>
 #include <vector>
 
@@ -157,8 +158,33 @@ static void check_bwd_order() {
         }
 }
 
+// Units dealt over the XCDs: each exactly once, and with clips longest first no XCD has more rows than
+// another beyond one group of the longest clip.
+static void check_dealt_units() {
+  for (int group : {1, 8})
+    for (int heads : {1, 2, 5, 16, 33})
+      for (int clips : {1, 3, 32, 255, 256})
+        for (int n_long : {1, 32, 100}) {
+          const int units = clips * heads, grid = vfm::dealt_grid(units, group);
+          std::vector<int> seen(units, 0);
+          long long rows[vfm::kNumXcd] = {};
+          EXPECT(grid % vfm::kNumXcd == 0 && grid >= units && grid < units + vfm::kNumXcd * group);
+          for (int b = 0; b < grid; ++b) {
+            const int u = vfm::dealt_unit(b, group);
+            EXPECT(u >= 0 && u < grid);
+            if (u >= units) continue;
+            ++seen[u];
+            rows[b % vfm::kNumXcd] += u / heads < n_long ? 256 : 1;
+          }
+          for (int u = 0; u < units; ++u) EXPECT(seen[u] == 1);
+          const auto [lo, hi] = std::minmax_element(rows, rows + vfm::kNumXcd);
+          EXPECT(*hi - *lo <= 256 * group);
+        }
+}
+
 int main() {
   check_bwd_order();
+  check_dealt_units();
   std::mt19937 rng(12345);
   void* const P = reinterpret_cast<void*>(0x10000);     // never dereferenced: the stubs launch nothing
   float* const F = reinterpret_cast<float*>(0x20000);
