@@ -1599,7 +1599,7 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
   hipError_t e;
   if constexpr (std::is_same_v<Segs, SegTable>) {
     if (segs.n == 0) return hipSuccess;
-    if (bwd_one_pass(segs.len[0], segs.n, n_heads, D)) {   // (longest clip first)
+    if (bwd_one_pass(segs, n_heads, D, compute_unit_count())) {
       if (segs.len[0] <= 128)
         return launch_bwd_fused<D, 4>(qb, kb, vb, (const __bf16*)out, lse, dob, segs, total, n_heads, scale,
                                       (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, stream);

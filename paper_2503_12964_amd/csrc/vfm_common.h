@@ -255,17 +255,24 @@ inline int fwd_tile_rows(const Segs& segs, int head_dim) {
   return longest_kv <= 1024 ? 128 : 256;
 }
 
-// Whether a run of clips takes the one-pass backward, which forms its own statistics: one workgroup per
-// (clip, head), clips of at most 256 tokens.  A lone workgroup of it takes longer than the two-pass
-// kernel's, which spreads a (clip, head) over up to three, so at head_dim 128 a run whose two-pass
-// workgroups all fit the chip at once stays there (256 tokens x 64 clip-heads: 23 us against 34; x 256:
-// about 60 against 42); at head_dim 64 and up to 64 tokens the one pass is level or faster from the
-// first unit on (64 tokens x 2: 11.4 against 8.1 us).
+// Whether a run of clips (longest first) takes the one-pass backward, which forms its own statistics: one
+// workgroup per (clip, head), clips of at most 256 tokens.  At head_dim 64 it is level or faster from the
+// first unit on (2 units: 64 tokens 6.7 us against 11.0, 128 tokens 10.1 against 13.9, 256 tokens 19.9 against
+// 19.4; 256 units of 256 tokens 27 against 39), at head_dim 128 up to 96 tokens too (2 units of 64 and 96
+// tokens 10.1 and 12.0 against 10.4 and 12.2; 256 units 12.6 and 16 against 22 and 28).  Beyond, its lone
+// workgroup takes longer than the two-pass kernel's, which spreads a (clip, head) over up to three, so a run
+// whose two-pass workgroups fit the chip at once stays there (two passes, one pass: 128 tokens x 64 units
+// 14.1, 15.6, x 112 16.4, 16.5, x 136 26.6, 16.9; 256 tokens x 80 units 24.6, 33.5, x 88 33.8, 33.2, x 256 60,
+// 44).  A clip shorter than the longest counts for its share of it, down to 64 rows (one of 256 and 7 of 64
+// tokens, 16 heads: 19, 30; with 31 of them 45, 35).
 constexpr int kOnePassMaxRows = 256;
-inline bool bwd_one_pass(int longest, int n_clips, int n_heads, int head_dim) {
+inline bool bwd_one_pass(const SegTable& segs, int n_heads, int head_dim, int cus) {
+  const int longest = segs.len[0];
   if (longest > kOnePassMaxRows) return false;
-  if (head_dim == 64 || longest <= 64) return true;
-  return (long long)n_clips * n_heads * (longest > 128 ? 3 : 2) > 256;
+  if (head_dim == 64 || longest <= 96) return true;
+  long long rows = 0;   // two-pass workgroups (tiles of 128 keys, of 256 queries), each as the rows of its clip
+  for (int s = 0; s < segs.n; ++s) rows += (segs.len[s] > 128 ? 3 : 2) * (segs.len[s] > 64 ? segs.len[s] : 64);
+  return rows * n_heads > (long long)cus * longest;
 }
 
 // The passes of a run that does not take the one-pass backward.  both: dK/dV and dQ units from one grid,

@@ -182,9 +182,27 @@ static void check_dealt_units() {
         }
 }
 
+// The one pass serves clips of up to 256 tokens; at head_dim 128 and more than 96 it needs more two-pass
+// workgroups than the chip has places for, short clips counting for their share.
+static void check_one_pass_rule() {
+  auto run = [](int n, int len, int m, int other) {
+    vfm::SegTable t{};
+    t.n = n + m;
+    for (int s = 0; s < t.n; ++s) t.len[s] = s < n ? len : other;
+    return t;
+  };
+  EXPECT(!vfm::bwd_one_pass(run(1, 257, 255, 1), 32, 64, 256) && !vfm::bwd_one_pass(run(1, 257, 255, 1), 32, 128, 256));
+  EXPECT(vfm::bwd_one_pass(run(1, 256, 0, 0), 1, 64, 256) && vfm::bwd_one_pass(run(1, 96, 0, 0), 1, 128, 256));
+  EXPECT(!vfm::bwd_one_pass(run(1, 256, 0, 0), 85, 128, 256) && vfm::bwd_one_pass(run(1, 256, 0, 0), 86, 128, 256));
+  EXPECT(!vfm::bwd_one_pass(run(1, 128, 0, 0), 128, 128, 256) && vfm::bwd_one_pass(run(1, 128, 0, 0), 129, 128, 256));
+  EXPECT(!vfm::bwd_one_pass(run(1, 256, 7, 64), 16, 128, 256) && vfm::bwd_one_pass(run(1, 256, 31, 64), 16, 128, 256));
+  EXPECT(vfm::bwd_one_pass(run(256, 256, 0, 0), 65535, 128, 256));
+}
+
 int main() {
   check_bwd_order();
   check_dealt_units();
+  check_one_pass_rule();
   std::mt19937 rng(12345);
   void* const P = reinterpret_cast<void*>(0x10000);     // never dereferenced: the stubs launch nothing
   float* const F = reinterpret_cast<float*>(0x20000);
