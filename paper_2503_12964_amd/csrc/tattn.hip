@@ -344,8 +344,10 @@ __device__ __forceinline__ bf16x8 half_to_bf16(const f32x16& x, int s2) {
 // whole row's maximum could be known first, but P relative to a running one has more elements that
 // are exactly 1 in bf16: out is 2.11e-3 instead of 2.16e-3 from 64-bit arithmetic at 128 frames.  The
 // accumulators' rescaling cost 2 to 4% at 97 to 128 frames of head_dim 128, where one workgroup has the CU
-// to itself; forming the scores before the values have landed gives 9: 128 frames x 1,500 pixels x
-// 8 heads 391 us with the row's maximum, 405 with the running one, now 368, 4.3 TB/s.)
+// to itself; forming the scores before the values have landed gives 9 there: 128 frames x 1,500 pixels x
+// 8 heads 391 us with the row's maximum, 405 with the running one, now 368, 4.3 TB/s.  Its second barrier does
+// not pay where many workgroups share the CU, at head_dim 64 and up to 96 frames: 65 frames x 100 pixels
+// x 8 heads 8.7 us, without 8.2.)
 // Measured at head_dim 128, forward and backward together, against the kernels that walk 32-row
 // blocks (below), which read q, k, v, dout three times in the backward: 64 frames x 3,520
 // pixels x 8 heads 2.36 -> 1.07 ms (4.7 TB/s of the 11 tensors; a large copy reaches 5.0), 40
@@ -416,8 +418,9 @@ __global__ __launch_bounds__(NB * 64, 2) void tattnB_fwd_kernel(const __bf16* __
   gather_blocks<D, NB, NB>(q, u, n_blk, row_bytes, lds0, wave, lane);
   gather_blocks<D, NB, NB>(k, u, n_blk, row_bytes, lds0 + NB * TB, wave, lane);
   gather_blocks<D, NB, NB>(v, u, n_blk, row_bytes, lds0 + 2 * NB * TB, wave, lane);
-  // the scores are formed while the values are still on their way
-  if (n_blk == NB) wait_vmcnt<T2Cfg<D>::kLoadsPerTile>(); else wait_vmcnt<0>();   // (a wave's v pieces: as many if all blocks exist)
+  // the scores are formed while the values are still on their way, where few workgroups share the CU
+  constexpr bool kEarly = NB * D >= 256;
+  if (kEarly && n_blk == NB) wait_vmcnt<T2Cfg<D>::kLoadsPerTile>(); else wait_vmcnt<0>();   // (a wave's v pieces: as many if all blocks exist)
   __syncthreads();
 
   f32x16 s[NB];
@@ -445,8 +448,10 @@ __global__ __launch_bounds__(NB * 64, 2) void tattnB_fwd_kernel(const __bf16* __
       }
     }
   }
-  wait_vmcnt<0>();
-  __syncthreads();
+  if constexpr (kEarly) {
+    wait_vmcnt<0>();
+    __syncthreads();
+  }
   if (wave >= n_blk) return;      // (no barrier below)
 
   float l = 0.f;                  // sum of this lane's half of the keys
