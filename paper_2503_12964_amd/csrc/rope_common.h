@@ -29,14 +29,18 @@ inline RopeFreq make_rope_freq(int dim_t, int dim_h, int dim_w, float theta) {
 
 // Heads per workgroup of the position-encoding kernels, whose blocks cover all tokens in x and
 // slices of the heads in y.  A token's angles are worth computing once for all heads as long as
-// the tokens alone fill the chip; below kRopeFillBlocks blocks (4 per CU) a workgroup's walk over its
-// heads is a serial chain of memory round trips on an idle chip, so the heads are cut into
-// slices of at least four (one batch of loads in flight), each forming the angles again.
-// (512 tokens x 32 heads x 128, 32 blocks: 7.9 -> 5.4 us, of which 3 are an empty pass;
-// 8,192 tokens x 16 heads, 512 blocks: normalised form 19.5 -> 17.6 us.)
+// the tokens alone fill the chip; with few blocks a workgroup's walk over its heads is a serial chain
+// of memory round trips on an idle chip, so the heads are cut into slices of at least four (one batch of
+// loads in flight), each forming the angles again.  The number of slices is the power of two nearest to
+// what makes 1,024 workgroups (4 per CU); rounded up instead, 3 slices for 375 blocks or 2 for 897 lose more
+// to the shorter walks than they fill.
+// (512 tokens x 32 heads x 128, 32 blocks: 6.1 -> 3.7 us; 10,000 tokens x 16 heads, 625 blocks: normalised form
+// 19.9 -> 17.7; 12,000 tokens x 32 heads x 64, 375 blocks: none 21.0, two 20.0, three 22.9; 28,704 tokens x
+// 32 heads x 64, 897 blocks: none 53.1, two 59.4.)
 constexpr int kRopeFillBlocks = 1024;
 inline int rope_heads_per_block(int token_blocks, int n_heads) {
-  const int slices = (kRopeFillBlocks + token_blocks - 1) / token_blocks;
+  int slices = 1;   // (sqrt 2: the middle between a power of two and the next)
+  while (slices < n_heads && slices * token_blocks * 1.4142f < kRopeFillBlocks) slices *= 2;
   const int per = (n_heads + slices - 1) / slices;
   return (per + 3) / 4 * 4;
 }

@@ -9,6 +9,7 @@
 #include <random>
 #include <vector>
 
+#include "rope_common.h"
 #include "vfm_common.h"
 
 static long g_launches = 0;
@@ -199,7 +200,21 @@ static void check_one_pass_rule() {
   EXPECT(vfm::bwd_one_pass(run(256, 256, 0, 0), 65535, 128, 256));
 }
 
+// Heads per workgroup of the position encoding: batches of four, about 1,024 workgroups where there are too
+// few tokens for that, and one slice from 725 blocks on.
+static void check_rope_slices() {
+  for (int heads : {1, 3, 4, 8, 24, 32, 48, 65535})
+    for (int blocks : {1, 13, 63, 188, 256, 313, 375, 512, 625, 724, 725, 750, 897, 1024, 4000}) {
+      const int per = vfm::rope_heads_per_block(blocks, heads), slices = (heads + per - 1) / per;
+      EXPECT(per >= 4 && per % 4 == 0 && slices >= 1 && slices <= 65535);
+      EXPECT((long long)slices * blocks <= 1449 || slices == 1);
+      if (blocks >= 725) EXPECT(slices == 1);
+      if (blocks < 600 && heads >= 8) EXPECT(slices >= 2);
+    }
+}
+
 int main() {
+  check_rope_slices();
   check_bwd_order();
   check_dealt_units();
   check_one_pass_rule();
