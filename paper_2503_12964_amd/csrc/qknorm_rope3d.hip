@@ -101,24 +101,17 @@ __global__ void zero_f32_kernel(float* p, int n) {
   if (i < n) p[i] = 0.f;
 }
 
-// A work item is one slice of a token's heads.  Workgroups are large and few (one per CU, looping) because
-// each ends in one atomic per element of dgain: with 256 threads per workgroup and up to 4,096 of
-// them, the atomics on the same 64 or 128 addresses took a good part of a small call
-// (8,192 tokens x 16 heads x 128: 32.5 -> 23.6 us, 4.3 TB/s; 56,320 x 32 x 128 stays at 271 us, 5.1 TB/s).
-constexpr int kQkBwdThreads = 1024;
-constexpr int kQkBwdMaxGrid = 256;
-
-template <int D>
-__global__ __launch_bounds__(kQkBwdThreads) void qknorm_rope3d_bwd_kernel(const u32x4* __restrict__ x,
-                                                                          const u32x4* dy, u32x4* dx,
-                                                                          const float* __restrict__ gain, float eps,
-                                                                          float* __restrict__ dgain,
-                                                                          const RopeTable tab, const RopeFreq fr,
-                                                                          int tok0, int n_items, int slices,
-                                                                          int heads_per_slice, int n_heads) {
+template <int D, int THREADS>
+__global__ __launch_bounds__(THREADS) void qknorm_rope3d_bwd_kernel(const u32x4* __restrict__ x,
+                                                                    const u32x4* dy, u32x4* dx,
+                                                                    const float* __restrict__ gain, float eps,
+                                                                    float* __restrict__ dgain,
+                                                                    const RopeTable tab, const RopeFreq fr,
+                                                                    int tok0, int n_items, int slices,
+                                                                    int heads_per_slice, int n_heads) {
   constexpr int kLanesPerTok = D / 8;
-  constexpr int kTokPerBlock = kQkBwdThreads / kLanesPerTok;   // items per pass
-  __shared__ float red[kTokPerBlock][D];
+  constexpr int kTokPerBlock = THREADS / kLanesPerTok;   // items per pass
+  __shared__ float red[THREADS / 64][D];
   const int group = threadIdx.x / kLanesPerTok;
   const int chunk = threadIdx.x % kLanesPerTok;
 
@@ -178,13 +171,20 @@ __global__ __launch_bounds__(kQkBwdThreads) void qknorm_rope3d_bwd_kernel(const 
     }
   }
 
+  // the wavefront's groups first, then the wavefronts through LDS
 #pragma unroll
-  for (int e = 0; e < 8; ++e) red[group][chunk * 8 + e] = dg[e];
+  for (int o = kLanesPerTok; o < 64; o <<= 1)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) dg[e] += __shfl_xor(dg[e], o);
+  if ((int)(threadIdx.x & 63) < kLanesPerTok) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) red[threadIdx.x >> 6][chunk * 8 + e] = dg[e];
+  }
   __syncthreads();
-  for (int d = threadIdx.x; d < D; d += kQkBwdThreads) {
+  for (int d = threadIdx.x; d < D; d += THREADS) {
     float s = 0.f;
 #pragma unroll
-    for (int t = 0; t < kTokPerBlock; ++t) s += red[t][d];
+    for (int t = 0; t < THREADS / 64; ++t) s += red[t][d];
     atomicAdd(dgain + d, s);
   }
 }
@@ -214,15 +214,16 @@ hipError_t launch_qknorm_rope3d_bwd(const void* x, const void* dy, void* dx, con
   const int tok0 = tab.cu[0], tok_end = tab.cu[tab.n], count = tok_end - tok0;
   if (count == 0) return hipSuccess;
   const RopeFreq fr = make_rope_freq(dim_t, dim_h, dim_w, theta);
-  // slices: as many as it takes to give every group of the full grid an item, each of at least two heads
-  const int groups = kQkBwdThreads / (head_dim / 8);
-  const int want = min((kQkBwdMaxGrid * groups + count - 1) / count, (n_heads + 1) / 2);
-  const int per = (n_heads + want - 1) / want, slices = (n_heads + per - 1) / per;
-  const int n_items = count * slices;   // (count * n_heads * head_dim fits 31 bits)
-  const int grid = min((n_items + groups - 1) / groups, kQkBwdMaxGrid);
-  auto kern = head_dim == 128 ? qknorm_rope3d_bwd_kernel<128> : qknorm_rope3d_bwd_kernel<64>;
-  return launch(kern, dim3(grid), dim3(kQkBwdThreads), 0, stream, (const u32x4*)x, (const u32x4*)dy, (u32x4*)dx, gain,
-                eps, dgain, tab, fr, tok0, n_items, slices, per, n_heads);
+  const QkBwdSplit sp = qk_bwd_split(count, n_heads, head_dim);
+  const int per = (n_heads + sp.slices - 1) / sp.slices;
+  const int n_items = count * sp.slices;   // (count * n_heads * head_dim fits 31 bits)
+  const int groups = sp.threads / (head_dim / 8);
+  const int grid = min((n_items + groups - 1) / groups, kQkBwdLargeGrid);
+  auto kern = sp.threads == kQkBwdSmall
+      ? (head_dim == 128 ? qknorm_rope3d_bwd_kernel<128, kQkBwdSmall> : qknorm_rope3d_bwd_kernel<64, kQkBwdSmall>)
+      : (head_dim == 128 ? qknorm_rope3d_bwd_kernel<128, kQkBwdLarge> : qknorm_rope3d_bwd_kernel<64, kQkBwdLarge>);
+  return launch(kern, dim3(grid), dim3(sp.threads), 0, stream, (const u32x4*)x, (const u32x4*)dy, (u32x4*)dx, gain,
+                eps, dgain, tab, fr, tok0, n_items, sp.slices, per, n_heads);
 }
 
 }  // namespace vfm

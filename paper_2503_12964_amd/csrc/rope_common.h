@@ -3,6 +3,8 @@
 
 #include <math.h>
 
+#include <algorithm>
+
 #include "vfm_common.h"
 
 namespace vfm {
@@ -43,6 +45,44 @@ inline int rope_heads_per_block(int token_blocks, int n_heads) {
   while (slices < n_heads && slices * token_blocks * 1.4142f < kRopeFillBlocks) slices *= 2;
   const int per = (n_heads + slices - 1) / slices;
   return (per + 3) / 4 * 4;
+}
+
+// Backward of the normalised form.  A work item is one slice of a token's heads, taken by D/8 lanes.  Every workgroup ends in one atomic per
+// element of dgain, about 25 ns a workgroup on the same 64 or 128 addresses, so workgroups are few: up to 64
+// of 256 threads where those have a place for every item (200 tokens x 1 head x 128: 5.2 us, in workgroups
+// of 1024 threads 6.8), else up to one of 1024 threads per CU, looping (8,192 tokens x 16 heads x 128: 25 us,
+// with up to 4,096 small workgroups 31).
+constexpr int kQkBwdSmall = 256, kQkBwdLarge = 1024;
+constexpr int kQkBwdSmallGrid = 64, kQkBwdLargeGrid = 256;
+
+// Slices of a token's heads (at least two heads each) and the workgroup's size.  Items are walked in passes
+// over all places of the grid; an item costs its heads and about two more for the angles, and the passes'
+// start and end about a third of one.  The split with the least of it keeps the last pass full (20,000
+// tokens x 48 heads x 128 in two passes of which the second is a fifth full 189 us, in five 141).
+struct QkBwdSplit { int slices, threads; };
+inline QkBwdSplit qk_bwd_split(int count, int n_heads, int head_dim) {
+  const int lanes = head_dim / 8;
+  const int small_places = kQkBwdSmallGrid * kQkBwdSmall / lanes, large_places = kQkBwdLargeGrid * kQkBwdLarge / lanes;
+  const int max_slices = (n_heads + 1) / 2;
+  if (count <= small_places) {
+    const int s = std::min(small_places / count, max_slices), per = (n_heads + s - 1) / s;
+    if (per <= 4) return {(n_heads + per - 1) / per, kQkBwdSmall};
+  }
+  int best = 0;
+  long long least = 0;
+  auto consider = [&](int s) {
+    const int per = (n_heads + s - 1) / s;
+    if (s > max_slices || (n_heads + per - 1) / per != s) return;   // (or the same slices as fewer)
+    const long long passes = ((long long)count * s + large_places - 1) / large_places;
+    const long long cost = (3 * passes + 1) * (per + 2);
+    if (best == 0 || cost * 40 < least * 39) { least = cost; best = s; }   // (a finer split has to promise 2.5%)
+  };
+  for (int s = 1; s <= std::min(64, max_slices); ++s) consider(s);
+  if (large_places / count > 64) {   // few tokens of very many heads: as many slices as one pass has places for
+    const int s = std::min(large_places / count, max_slices), per = (n_heads + s - 1) / s;
+    consider((n_heads + per - 1) / per);
+  }
+  return {best, kQkBwdLarge};
 }
 
 // (cos, sin) of the four adjacent pairs in 16-byte chunk `chunk` of token `tok`'s head

@@ -213,8 +213,27 @@ static void check_rope_slices() {
     }
 }
 
+// The cut of heads over work items in the backward of the normalised position encoding: every head in one
+// slice, the grid's limits, and no more than a quarter of the places' time idle once there is work for
+// twenty passes of single heads.
+static void check_qk_bwd_split() {
+  for (int hd : {64, 128})
+    for (int heads : {1, 2, 3, 4, 5, 8, 12, 16, 24, 33, 48, 64, 200, 65535})
+      for (int count : {1, 2, 63, 200, 512, 1001, 2000, 2049, 6000, 8192, 10000, 12000, 16384, 16385, 20000, 28704, 40000, 56320, 262144}) {
+        if ((long long)count * heads * hd * 2 > 0xffffffffLL) continue;
+        const vfm::QkBwdSplit sp = vfm::qk_bwd_split(count, heads, hd);
+        const int per = (heads + sp.slices - 1) / sp.slices;
+        const long long items = (long long)count * sp.slices, places = 256LL * 1024 / (hd / 8);
+        EXPECT(sp.slices >= 1 && (sp.slices - 1) * per < heads && items < 1LL << 31);
+        EXPECT(sp.threads == 1024 || (sp.threads == 256 && per <= 4 && items <= places / 16));
+        const long long passes = (items + places - 1) / places;
+        if (heads >= 8 && (long long)count * heads >= 20 * places) EXPECT(passes * per * places * 3 <= 4LL * count * heads);
+      }
+}
+
 int main() {
   check_rope_slices();
+  check_qk_bwd_split();
   check_bwd_order();
   check_dealt_units();
   check_one_pass_rule();

@@ -126,6 +126,8 @@ def test_full_size_c4_every_element():
     (((1, 3, 5), (0, 1, 1), (1, 1, 2)), 5, 64),      # slices of two heads, the last one short
     (((1, 7, 43),), 33, 128),                        # a head count no slice size divides
     (((4, 65, 64),), 3, 128),                        # more items than groups: workgroups loop
+    (((1, 13, 77),), 4, 128),                        # small workgroups, the last one short
+    (((2, 85, 59),), 12, 64),                        # three slices of four heads in one pass of the large grid
 ])
 def test_head_slices(grids, heads, hd):
     # every cut of the heads over workgroups (encode) and over items (backward), against the oracle
