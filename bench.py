@@ -244,6 +244,28 @@ def _bench_cross(args, wl) -> int:
     return 0
 
 
+def _backward_kernels(lens, n_heads: int, head_dim: int, cus: int = 256) -> str:
+    """The kernels that vfm_attn_bwd launches for self-attention over clips of these lengths (at most 256 of
+    them), by the library's rules: bwd_one_pass and bwd_order in csrc/vfm_common.h."""
+    lens = [int(n) for n in lens if n > 0][:256]
+    longest = max(lens)
+    tiles = sum((3 if n > 128 else 2) * max(n, 64) for n in lens)
+    if longest <= 256 and (head_dim == 64 or longest <= 96 or tiles * n_heads > cus * longest):
+        return "attn_bwd_fused_kernel"
+    few = "bwd_short_delta_kernel + " if min(lens) <= 32 else ""
+    if head_dim == 64:
+        return "bwd_prepare_kernel + " + few + "attn_bwd_dkdv_kernel + attn_bwd_dq_kernel"
+    if longest <= 1024:      # both units in one grid
+        return "bwd_prepare_kernel + " + few + "attn_bwd_both_kernel"
+    return few + "attn_bwd_dq2_kernel + attn_bwd_dkdv_kernel"
+
+
+def _temporal_backward_kernels(frames: int) -> str:
+    if frames > 128:
+        return "tattnL_fwd_kernel (statistics) + tattnL_dkdv_kernel + tattnL_dq_kernel"
+    return "tattn_bwd_kernel" if frames <= 16 else "tattnB_bwd_kernel"
+
+
 def _bench_temporal(args, wl) -> int:
     """Temporal-attention workload: a step is vfm_tattn_fwd + vfm_tattn_bwd on the workload's clips."""
     import torch
@@ -285,7 +307,7 @@ def _bench_temporal(args, wl) -> int:
         "breakdown": {"fwd_ms": ms_fwd, "bwd_ms": ms_bwd,
                       "fwd_gbs": 4 * tensor_bytes / (ms_fwd * 1e-3) / 1e9, "bwd_gbs": gbs_bwd,
                       "tflops": flops / (ms_step * 1e-3) / 1e12},
-        "roofline": {"bound": "hbm", "kernel": "tattn_bwd_kernel", "achieved": gbs_bwd, "peak": HBM_PEAK_GBS,
+        "roofline": {"bound": "hbm", "kernel": _temporal_backward_kernels(max(g[0] for g in wl.grids)), "achieved": gbs_bwd, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": gbs_bwd / HBM_PEAK_GBS, "traffic": None, "ms": ms_bwd,
                      "note": "algorithmic bytes: q, k, v, dout read and dq, dk, dv written once = 7 tensors "
                              "(forward: q, k, v read, out written = 4 tensors)"}}))
@@ -440,15 +462,12 @@ def main() -> int:
     f_bwd = f_all - f_fwd
     value = f_all / (ms_step * 1e-3) / 1e12
     rope_bytes = 2 * 2 * wl.total_tokens * wl.n_heads * wl.head_dim * 2   # q and k, read + write
-    if wl.backward and int(np.max(np.diff(cu_attn))) <= 1024 and wl.head_dim == 128:
-        # sequences of at most 1,024 rows: the library deals both backward units from one grid
-        dom, dom_flops, dom_ms = "attn_bwd_both_kernel", f_bwd, ms_bwd
-        dom_note = ("vfm_attn_bwd call: bwd_prepare + attn_bwd_both_kernel (dK/dV and dQ units in one grid); "
-                    "10*D algorithmic flops/pair/head (the units execute 14*D)")
-    elif wl.backward:
-        dom, dom_flops, dom_ms = "attn_bwd_dkdv_kernel + attn_bwd_dq2_kernel", f_bwd, ms_bwd
-        dom_note = ("vfm_attn_bwd call: bwd_prepare + attn_bwd_dkdv_kernel + attn_bwd_dq2_kernel; "
-                    "10*D algorithmic flops/pair/head (the two kernels execute 14*D)")
+    executed = 1.0
+    if wl.backward:
+        dom, dom_flops, dom_ms = _backward_kernels(np.diff(cu_attn), wl.n_heads, wl.head_dim), f_bwd, ms_bwd
+        executed = 1.0 if dom == "attn_bwd_fused_kernel" else 1.4     # flops per flop credited
+        dom_note = (f"vfm_attn_bwd call: {dom}; 10*D algorithmic flops/pair/head"
+                    + (" (the kernels execute 14*D)" if executed > 1 else ""))
     else:
         dom, dom_flops, dom_ms = "attn_fwd_kernel", f_fwd, ms_fwd
         dom_note = "vfm_attn_fwd call: attn_fwd_kernel; 4*D flops/pair/head"
@@ -488,15 +507,15 @@ def main() -> int:
         result["roofline"]["mfma_only_measured"] = {
             **ceiling, "unit": "TFLOP/s",
             "frac_of_random_operand_ceiling": achieved / rnd if rnd > 0 else None,
-            # the split backward executes 14*D flops per pair for the 10*D it is credited with
-            "executed_tflops": achieved * (1.4 if wl.backward else 1.0),
-            "executed_frac_of_random_operand_ceiling": achieved * (1.4 if wl.backward else 1.0) / rnd if rnd > 0 else None,
+            # the two-pass backward executes 14*D flops per pair for the 10*D it is credited with
+            "executed_tflops": achieved * executed,
+            "executed_frac_of_random_operand_ceiling": achieved * executed / rnd if rnd > 0 else None,
             "note": "loop of MFMA instructions only, sustained; with random operands the clock drops "
                     "under the power limit, which also bounds kernels working on real data"}
         if ceiling.get("exp2_only_tera_per_s"):
             # secondary ceiling: one exponential per (query, key) pair per head in the forward and in
-            # each of the two backward kernels, at the measured rate of a loop of v_exp_f32 only
-            n_exp = wl.flops(False) / (4.0 * wl.head_dim) * (3.0 if wl.backward else 1.0)
+            # each of the backward's one or two passes, at the measured rate of a loop of v_exp_f32 only
+            n_exp = wl.flops(False) / (4.0 * wl.head_dim) * ((3.0 if executed > 1 else 2.0) if wl.backward else 1.0)
             exp_ms = n_exp / (ceiling["exp2_only_tera_per_s"] * 1e12) * 1e3
             result["roofline"]["exp_only_measured"] = {
                 "tera_exp_per_s": ceiling["exp2_only_tera_per_s"], "exponentials_per_step": n_exp,

@@ -1,11 +1,12 @@
 // Packed variable-length attention backward for gfx950 (bf16 MFMA, fp32 accumulate).
 //
-// Clips of at most 256 tokens: one kernel (attn_bwd_fused_kernel, further down), one workgroup per (clip,
-// head).  Longer ones: three kernels, no atomics (device-wide fp32 atomics are executed at the memory side on
-// this chip and were measured to bound the fused variant), so every output is written
-// once and the result is bitwise reproducible:
-//   bwd_prepare : Delta[h,i] = sum_d dO[i,h,d] O[i,h,d],  lse2 = lse * log2(e), and two
-//                 sentinel statistics (+inf, 0) used for rows past a clip's end
+// Runs of clips of at most 256 tokens: one kernel (attn_bwd_fused_kernel, further down), one workgroup per
+// (clip, head), but for small runs (bwd_one_pass).  Otherwise two passes, dQ and dK/dV, without atomics
+// (device-wide fp32 atomics are executed at the memory side on this chip and were measured to bound the
+// fused variant of long clips), so every output is written once and the result is bitwise reproducible;
+// they run one after the other or, up to 1,024 rows, from one grid (bwd_order).  Both need
+//   Delta[h,i] = sum_d dO[i,h,d] O[i,h,d],  lse2 = lse * log2(e), and two sentinel statistics (+inf, 0) for rows
+//   past a clip's end, which the dQ pass forms itself where it runs first, else bwd_prepare before both.
 //   bwd_dkdv    : one workgroup owns kBC key/value rows of one (clip, head); its four
 //                 wavefronts own 32 of those rows each and keep their K and V rows, and
 //                 their dK^T / dV^T accumulators, in registers.  The workgroup walks the

@@ -39,13 +39,17 @@ LDS_COUNTERS = ("SQ_LDS_IDX_ACTIVE SQ_ACTIVE_INST_LDS SQ_WAIT_INST_LDS SQ_INSTS_
 
 # kernel-name fragment -> short label, most specific first
 KERNELS = (("tattn_fwd", "tattn_fwd_kernel"), ("tattn_bwd", "tattn_bwd_kernel"),
+           ("tattnB_fwd", "tattnB_fwd_kernel"), ("tattnB_bwd", "tattnB_bwd_kernel"), ("tattnL_fwd", "tattnL_fwd_kernel"),
+           ("tattnL_dkdv", "tattnL_dkdv_kernel"), ("tattnL_dq", "tattnL_dq_kernel"), ("attn_bwd_fused", "attn_bwd_fused_kernel"),
            ("attn_bwd_both", "attn_bwd_both_kernel"), ("attn_bwd_dkdv", "attn_bwd_dkdv_kernel"), ("attn_bwd_dq2", "attn_bwd_dq2_kernel"),
            ("attn_bwd_dq", "attn_bwd_dq_kernel"), ("attn_fwd_fp8", "attn_fwd_fp8_kernel"),
            ("attn_fwd", "attn_fwd_kernel"), ("qknorm_rope3d_bwd", "qknorm_rope3d_bwd_kernel (outside the step)"),
            ("qknorm_rope3d", "qknorm_rope3d_kernel (outside the step)"), ("rope3d", "rope3d_kernel"),
            ("bwd_prepare", "bwd_prepare_kernel"), ("bwd_short_delta", "bwd_short_delta_kernel"),
            ("copyBuffer", "copy kernel (1 GiB)"))
-ATTENTION = ("attn_bwd_dkdv_kernel", "attn_bwd_dq2_kernel", "attn_bwd_both_kernel", "attn_fwd_kernel")
+ATTENTION = ("attn_bwd_fused_kernel", "attn_bwd_dkdv_kernel", "attn_bwd_dq2_kernel", "attn_bwd_dq_kernel", "attn_bwd_both_kernel",
+             "attn_fwd_kernel")
+BACKWARD = ATTENTION[:-1] + ("bwd_prepare_kernel", "bwd_short_delta_kernel")   # kernels of a vfm_attn_bwd call
 N_SIMD, N_CU, N_SE = 1024, 256, 32      # MI355X: 256 CUs x 4 SIMDs, 8 XCDs x 4 shader engines
 
 
@@ -142,8 +146,7 @@ def summarise(run_dir: str, workload: str, out_path: str) -> str:
                 avg[lab] = float(r["AverageNs"]) / 1e6
                 P(f"    {lab:46s} {r['Calls']:>5s} {float(r['AverageNs']) / 1e6:10.3f} {float(r['MinNs']) / 1e6:10.3f} "
                   f"{float(r['MaxNs']) / 1e6:10.3f} {float(r['Percentage']):7.3f}")
-        bwd_sum = sum(avg.get(x, 0.0) for x in ("attn_bwd_dkdv_kernel", "attn_bwd_dq2_kernel", "attn_bwd_both_kernel",
-                                                "bwd_prepare_kernel"))
+        bwd_sum = sum(avg.get(x, 0.0) for x in BACKWARD)
         if b and bwd_sum:
             P(f"    backward kernels summed: {bwd_sum:.3f} ms (bench.py's HIP-event time for the vfm_attn_bwd call: "
               f"{b['breakdown']['bwd_ms']:.3f} ms)")
@@ -160,9 +163,7 @@ def summarise(run_dir: str, workload: str, out_path: str) -> str:
         P(f"                 WRITE_SIZE reads {cwv:.0f} KiB for 1,048,576 KiB written -> scale {kw:.4f}")
         P(f"    {'kernel':46s} {'FETCH_SIZE':>12s} {'WRITE_SIZE':>12s} {'scaled read GB':>15s} {'scaled write GB':>16s}")
         bwd_total, fwd_total = 0.0, 0.0
-        for lab in ("attn_bwd_dkdv_kernel", "attn_bwd_dq2_kernel", "attn_bwd_both_kernel", "attn_bwd_dq_kernel",
-                    "attn_fwd_kernel", "rope3d_kernel",
-                    "bwd_prepare_kernel", "bwd_short_delta_kernel"):
+        for lab in BACKWARD + ("attn_fwd_kernel", "rope3d_kernel"):
             fv, wv = f.get((lab, "FETCH_SIZE")), w.get((lab, "WRITE_SIZE"))
             if fv is None and wv is None:
                 continue
@@ -228,7 +229,7 @@ WIDENED = (("C2", "2 x 4,096 tokens, 16 heads (classifier-free-guidance batch), 
            ("P288", "288 images of 256 tokens packed (73,728 tokens), 32 heads, rope+fwd+bwd"),
            ("C4-cross", "cross-attention: 56,320 queries x 512 text keys/values, fwd+bwd"),
            ("C4-temporal", "temporal attention: 3,520 pixels x 16 frames, 32 heads, fwd+bwd"),
-           ("L64-temporal", "temporal attention: 3,520 pixels x 64 frames, 8 heads, fwd+bwd (block-walking kernels)"),
+           ("L64-temporal", "temporal attention: 3,520 pixels x 64 frames, 8 heads, fwd+bwd (one workgroup per sequence)"),
            ("C4-fp8", "FP8 (E4M3, per-tile scales) forward at the headline shape: pack + attention"),
            ("C5-fp8", "FP8 forward at the 130,560-token inference shape: pack + attention"))
 

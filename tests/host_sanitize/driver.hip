@@ -122,9 +122,6 @@ size_t fp8_scales_bytes(int total, int n_heads, int n_units) {
 template <class Segs>
 hipError_t launch_attn_fwd(const void*, const void*, const void*, const Segs& segs, int total_q, int, int, float, void*,
                            float*, hipStream_t) { ++g_launches; check_segs(segs, total_q); return hipSuccess; }
-hipError_t launch_bwd_prepare(const void*, const void*, const float*, float*, float*, float*, int, int, int, hipStream_t) {
-  ++g_launches; return hipSuccess;
-}
 template <class Segs>
 hipError_t launch_attn_bwd(const void*, const void*, const void*, const void*, const float*, const void*, const Segs& segs,
                            int total_q, int, int, float, void*, void*, void*, float*, float*, float*, float*, int total_kv,

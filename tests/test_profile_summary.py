@@ -106,6 +106,8 @@ def test_traffic_file_keeps_other_workloads(tmp_path, monkeypatch):
 def test_kernel_labels():
     assert PS._label("void vfm::tattn_fwd_kernel<128>(...)") == "tattn_fwd_kernel"
     assert PS._label("_ZN3vfm20attn_bwd_both_kernelILi128E") == "attn_bwd_both_kernel"
+    assert PS._label("_ZN3vfm21attn_bwd_fused_kernelILi128ELi8EEEvPK") == "attn_bwd_fused_kernel" in PS.BACKWARD
+    assert PS._label("_ZN3vfm17tattnB_bwd_kernelILi128ELi2EEEvPK") == "tattnB_bwd_kernel"
     assert PS._label("_ZN3vfm19attn_fwd_fp8_kernelILi128E") == "attn_fwd_fp8_kernel"
     assert PS._label("void vfm::qknorm_rope3d_bwd_kernel<128>(...)").startswith("qknorm_rope3d_bwd_kernel")
     assert PS._label("some_other_kernel") is None
