@@ -1219,8 +1219,8 @@ void attn_bwd_both_kernel(const __bf16* __restrict__ q, const __bf16* __restrict
 // eight serve 256 tokens, at head_dim 128 one workgroup per CU.  Everything the loop could recompute it does
 // (opaque offsets): one spilled register tuple read back in the loop waits for the loads in flight.
 // Whole backward call, statistics pass included, 256 clips x 32 heads, two-pass kernels -> this one:
-// 256 tokens 1641 -> 1309 us (3.3 TB/s of the eight tensors), 128 tokens 822 -> 467, 64 tokens 555 -> 271,
-// 16 tokens 739 -> 135; head_dim 64, 256 tokens 1094 -> 766, 128 tokens 497 -> 253.
+// 256 tokens 1653 -> 1266 us (3.4 TB/s of the eight tensors), 128 tokens 801 -> 443, 64 tokens 557 -> 230,
+// 16 tokens 739 -> 140; head_dim 64, 256 tokens 1067 -> 757, 128 tokens 506 -> 240.
 template <int D, int NW>
 struct FusedCfg {
   static constexpr int kRows = NW * 32;                      // longest clip

@@ -350,10 +350,10 @@ __device__ __forceinline__ bf16x8 half_to_bf16(const f32x16& x, int s2) {
 // x 8 heads 8.7 us, without 8.2.)
 // Measured at head_dim 128, forward and backward together, against the kernels that walk 32-row
 // blocks (below), which read q, k, v, dout three times in the backward: 64 frames x 3,520
-// pixels x 8 heads 2.36 -> 1.07 ms (4.7 TB/s of the 11 tensors; a large copy reaches 5.0), 40
-// frames 2.1x, 80 to 120 frames 1.7 to 1.8x (one workgroup per CU there: its loads and its
-// arithmetic do not overlap); at 17 to 32 frames against one wavefront per sequence with 16-byte
-// stores 1.14 to 1.2x.
+// pixels x 8 heads 2.36 -> 1.07 ms (4.7 TB/s of the 11 tensors; a large copy reaches 5.0; its fetches and
+// writes are within 1% of the tensors' sizes), 40 frames 2.1x, 80 to 120 frames 1.7 to 1.9x (one workgroup
+// per CU there: the backward's loads and its arithmetic do not overlap); at 17 to 32 frames against one
+// wavefront per sequence with 16-byte stores 1.14 to 1.2x.
 namespace {
 
 __device__ __forceinline__ bool temporal_block_unit(const TemporalTable& tab, int n_heads, TUnit& u) {

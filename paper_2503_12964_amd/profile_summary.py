@@ -272,16 +272,19 @@ def summarise_widened(run_dir: str, out_path: str) -> str:
             k = _short_kernel(r["Name"])
             if k and float(r["Percentage"]) >= 0.05 and "qknorm" not in k:
                 P(f"    {k:32s} {r['Calls']:>5s} {float(r['AverageNs']) / 1e6:9.3f} {float(r['MinNs']) / 1e6:9.3f} {float(r['MaxNs']) / 1e6:9.3f}")
-    tf, tw = _pmc(run_dir, "temporal_fetch"), _pmc(run_dir, "temporal_write")
-    if tf and tw:
+    for w, stem, tokens_heads, kernels in (("C4-temporal", "temporal", 56320 * 32, ("tattn_fwd_kernel", "tattn_bwd_kernel")),
+                                           ("L64-temporal", "long", 225280 * 8, ("tattnB_fwd_kernel", "tattnB_bwd_kernel"))):
+        tf, tw = _pmc(run_dir, f"{stem}_fetch"), _pmc(run_dir, f"{stem}_write")
+        if not tf or not tw:
+            continue
         P("")
-        P(f"[C4-temporal HBM traffic]  rocprofv3 --pmc FETCH_SIZE (then WRITE_SIZE) -d {rel} -o temporal_fetch (temporal_write) --output-format csv")
-        P("        -- python3 bench.py --workload C4-temporal --steps 2 --warmup 1 --no-cpu-baseline --no-mfma-ceiling")
+        P(f"[{w} HBM traffic]  rocprofv3 --pmc FETCH_SIZE (then WRITE_SIZE) -d {rel} -o {stem}_fetch ({stem}_write) --output-format csv")
+        P(f"        -- python3 bench.py --workload {w} --steps 2 --warmup 1 --no-cpu-baseline --no-mfma-ceiling")
         P("    counter scale factors from the plain-copy calibration in attention_C4_56k_rocprofv3.txt: FETCH_SIZE x 2.0, WRITE_SIZE x 1.0 (KiB)")
-        tensor_gb = 56320 * 32 * 128 * 2 / 1e9
-        for kname, nt_r, nt_w in (("tattn_fwd_kernel", 3, 1), ("tattn_bwd_kernel", 4, 3)):
-            rg = sum(v for (k, c), v in tf.items() if c == "FETCH_SIZE" and kname.split("_kernel")[0] in k) * 2.0 * 1024 / 1e9
-            wg = sum(v for (k, c), v in tw.items() if c == "WRITE_SIZE" and kname.split("_kernel")[0] in k) * 1024 / 1e9
+        tensor_gb = tokens_heads * 128 * 2 / 1e9
+        for kname, (nt_r, nt_w) in zip(kernels, ((3, 1), (4, 3))):
+            rg = tf.get((kname, "FETCH_SIZE"), 0.0) * 2.0 * 1024 / 1e9
+            wg = tw.get((kname, "WRITE_SIZE"), 0.0) * 1024 / 1e9
             P(f"    {kname:20s} read {rg:.3f} GB (algorithmic {nt_r * tensor_gb:.3f}), written {wg:.3f} GB (algorithmic {nt_w * tensor_gb:.3f})")
     text = "\n".join(L) + "\n"
     os.makedirs(os.path.dirname(os.path.abspath(out_path)), exist_ok=True)
