@@ -97,7 +97,6 @@ __global__ __launch_bounds__(256) void bwd_prepare_kernel(const u32x4* __restric
 // loads deep.  (One lane per query row walking the keys in a serial loop took 31 us of the smallest
 // training step, 32 tokens x 2 heads; this takes 2.6 us.)  Launched only when the call has such
 // a sequence, over the tiles of those sequences only.
-constexpr int kShortKeys = 32;
 
 // A product that is rounded by itself, not within a fused multiply-add: two kernels that sum such products
 // in the same order get the same bits.
@@ -1611,35 +1610,20 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
   const TileIndex ti = make_tile_index<true>(segs, kBwdBC);
   const int tiles = count_tiles(ti);
   // Few key tiles and long query ranges (cross-attention): split the queries over workgroups.
-  int q_split = 1, longest = 0, max_q = 0;
-  int tok0 = 0x7fffffff, tok_end = 0;   // the run's query tokens
-  bool any_short = false;
-  for (int s2 = 0; s2 < segs.n; ++s2) {
-    const int nq = segs.q_len(s2), nk = segs.kv_len(s2);
-    max_q = std::max(max_q, nq);
-    longest = std::max(longest, std::max(nq, nk));
-    if (nq == 0) continue;
-    tok0 = std::min(tok0, segs.q_start(s2));
-    tok_end = std::max(tok_end, segs.q_start(s2) + nq);
-    any_short |= nk > 0 && nk <= kShortKeys;
-  }
+  int q_split = 1;
+  const RunSpan span = run_span(segs);
   const int cus = compute_unit_count();
   if (dkv32 && tiles > 0 && tiles * n_heads < cus)
-    q_split = std::min(std::min(16, (cus + tiles * n_heads - 1) / (tiles * n_heads)), std::max(1, max_q / 512));
-  const auto [both, dq_first] = bwd_order(D, q_split, longest, dq == q || dq == dout);
-  if (max_q > 0) {   // (with no queries at all only the keys' zero gradients remain to be written)
+    q_split = std::min(std::min(16, (cus + tiles * n_heads - 1) / (tiles * n_heads)), std::max(1, span.max_q / 512));
+  const auto [both, dq_first] = bwd_order(D, q_split, span.longest, dq == q || dq == dout);
+  if (span.max_q > 0) {   // (with no queries at all only the keys' zero gradients remain to be written)
     if (!dq_first) {
-      e = launch_bwd_prepare(out, dout, lse, delta, lse2, sentinel, total, n_heads, D, tok0, tok_end, stream);
+      e = launch_bwd_prepare(out, dout, lse, delta, lse2, sentinel, total, n_heads, D, span.tok0, span.tok_end, stream);
       if (e != hipSuccess) return e;
     }
-    if (any_short) {   // sequences with a handful of keys: Delta in its cancellation-free form
-      TileIndex ti_few;   // 32-row query tiles of the sequences with few keys, none of the others
-      int few = 0;
-      for (int s2 = 0; s2 <= VFM_MAX_SEQS; ++s2) {
-        ti_few.cu[s2] = few;
-        if (s2 < segs.n && segs.kv_len(s2) > 0 && segs.kv_len(s2) <= kShortKeys) few += (segs.q_len(s2) + 31) / 32;
-      }
-      e = launch(bwd_short_delta_kernel<D, Segs>, dim3(few, n_heads), dim3(64), 0,
+    if (span.few_keys) {   // sequences with a handful of keys: Delta in its cancellation-free form
+      const TileIndex ti_few = make_few_key_index(segs);
+      e = launch(bwd_short_delta_kernel<D, Segs>, dim3(count_tiles(ti_few), n_heads), dim3(64), 0,
                  stream, qb, kb, vb, dob, lse, delta, segs, ti_few, total, n_heads, scale * kLog2eB);
       if (e != hipSuccess) return e;
     }

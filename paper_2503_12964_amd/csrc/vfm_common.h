@@ -240,6 +240,38 @@ __host__ __device__ __forceinline__ void locate_tile(const TileIndex& ti, int n,
   t = tile - ti.cu[lo];
 }
 
+// Sequences with at most this many keys have their Delta formed in its cancellation-free form (backward); the
+// tiles of 32 of their queries, none of the other sequences'.
+constexpr int kShortKeys = 32;
+template <class Segs>
+inline TileIndex make_few_key_index(const Segs& segs) {
+  TileIndex ti;
+  int tiles = 0;
+  for (int s = 0; s <= VFM_MAX_SEQS; ++s) {
+    ti.cu[s] = tiles;
+    if (s < segs.n && segs.kv_len(s) > 0 && segs.kv_len(s) <= kShortKeys) tiles += (segs.q_len(s) + 31) / 32;
+  }
+  return ti;
+}
+
+// What a run's backward is chosen by: its longest query range, its longest range of either kind, the query
+// tokens [tok0, tok_end) of all its sequences, and whether one with queries has few keys.
+struct RunSpan { int max_q, longest, tok0, tok_end; bool few_keys; };
+template <class Segs>
+inline RunSpan run_span(const Segs& segs) {
+  RunSpan r{0, 0, 0x7fffffff, 0, false};
+  for (int s = 0; s < segs.n; ++s) {
+    const int nq = segs.q_len(s), nk = segs.kv_len(s), q0 = segs.q_start(s);
+    if (nq > r.max_q) r.max_q = nq;
+    if (nq > r.longest || nk > r.longest) r.longest = nq > nk ? nq : nk;
+    if (nq == 0) continue;
+    if (q0 < r.tok0) r.tok0 = q0;
+    if (q0 + nq > r.tok_end) r.tok_end = q0 + nq;
+    r.few_keys |= nk > 0 && nk <= kShortKeys;
+  }
+  return r;
+}
+
 // Query rows per workgroup of the forward kernel for the sequences of one launch.  Few keys
 // per sequence (cross-attention on a text prompt, packs of images): a workgroup's loop is
 // short against its prologue and epilogue, so 128-row workgroups are used, two of which share

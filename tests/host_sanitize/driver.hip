@@ -41,6 +41,30 @@ static void check_segs(const Segs& segs, int total_q) {
   }
 }
 
+// What the backward derives from a run's sequences: the span of its queries, and the tiles of those with few
+// keys (every such tile found again by its index, no other).
+template <class Segs>
+static void check_run_span(const Segs& segs) {
+  const RunSpan r = run_span(segs);
+  const TileIndex ti = make_few_key_index(segs);
+  int tiles = 0, max_q = 0, longest = 0, lo = 0x7fffffff, hi = 0;
+  for (int s = 0; s < segs.n; ++s) {
+    max_q = std::max(max_q, segs.q_len(s));
+    longest = std::max({longest, segs.q_len(s), segs.kv_len(s)});
+    if (segs.q_len(s) == 0) continue;
+    lo = std::min(lo, segs.q_start(s));
+    hi = std::max(hi, segs.q_start(s) + segs.q_len(s));
+    if (segs.kv_len(s) > kShortKeys) continue;
+    for (int t = 0; t * 32 < segs.q_len(s); ++t) {
+      int seq = -1, tile = -1;
+      locate_tile(ti, segs.n, tiles++, seq, tile);
+      EXPECT(seq == s && tile == t);
+    }
+  }
+  EXPECT(count_tiles(ti) == tiles && r.few_keys == (tiles > 0));
+  EXPECT(r.max_q == max_q && r.longest == longest && r.tok0 == lo && r.tok_end == hi);
+}
+
 hipError_t launch_rope3d(void*, const RopeTable& tab, int, int, int, int, int, float, int, hipStream_t) {
   ++g_launches; check_rope_table(tab); return hipSuccess;
 }
@@ -126,7 +150,7 @@ template <class Segs>
 hipError_t launch_attn_bwd(const void*, const void*, const void*, const void*, const float*, const void*, const Segs& segs,
                            int total_q, int, int, float, void*, void*, void*, float*, float*, float*, float*, int total_kv,
                            int kv_lo, int kv_hi, hipStream_t) {
-  ++g_launches; check_segs(segs, total_q); EXPECT(kv_lo >= 0 && kv_lo <= kv_hi && kv_hi <= total_kv + (total_kv == 0 ? kv_hi : 0));
+  ++g_launches; check_segs(segs, total_q); check_run_span(segs); EXPECT(kv_lo >= 0 && kv_lo <= kv_hi && kv_hi <= total_kv + (total_kv == 0 ? kv_hi : 0));
   return hipSuccess;
 }
 template hipError_t launch_attn_fwd<SegTable>(const void*, const void*, const void*, const SegTable&, int, int, int, float,
