@@ -365,8 +365,9 @@ VFM_API int vfm_attn_fwd_fp8(const void* q8, const void* k8, const void* vT8, co
  * clips are never enumerated), clips longest first, and the (head, tile) units
  * are dealt to the grid so that the workgroups of one XCD (workgroup index mod
  * 8) take consecutive tiles of the same head.  The attention kernels use this
- * very mapping over query rows with rows_per_tile = 256 in the dQ kernel and
- * vfm_attn_fwd_tile_rows() in the forward, and over key rows with 128 (dK/dV).
+ * very mapping over query rows with rows_per_tile = 256 in the dQ kernel (128 at
+ * head_dim 64) and vfm_attn_fwd_tile_rows() in the forward, and over key rows
+ * with 128 (dK/dV).
  * (A backward launch at head_dim 128 whose sequences all have at most 1,024
  * rows deals both kinds of tile from one grid, per (head, sequence) the key
  * tiles and then the query tiles, with the same tile heights and XCD rule.)

@@ -197,6 +197,7 @@ void bwd_dkdv_unit(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   constexpr int SB = Cfg::kStageBytes;
   constexpr int TB = Cfg::kTileBytes;
   constexpr int RB = D * 2;
+  constexpr bool kAsm = D == 128;   // more than 256 registers (see mfma32_v)
 
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
@@ -300,10 +301,12 @@ void bwd_dkdv_unit(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
 
   // Every swizzled LDS address the loop uses, held in a register of its own (made opaque so
   // that the compiler keeps them instead of recomputing them between the MFMAs): set 0 for
-  // stages 0 and 1, set 1 for stage 2, whose tiles lie beyond the 64 KB an immediate reaches.
-  uint32_t rb[2][KS], tb[2][2][DB];
+  // stages 0 and 1, set 1 for stage 2, whose tiles lie beyond the 64 KB an immediate reaches (head_dim 64: one set
+  // reaches all three).
+  constexpr int SETS = kBwdRing * SB > 65536 ? 2 : 1;
+  uint32_t rb[SETS][KS], tb[SETS][2][DB];
 #pragma unroll
-  for (int hs = 0; hs < 2; ++hs) {
+  for (int hs = 0; hs < SETS; ++hs) {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       rb[hs][ks] = smem_addr + hs * 2 * SB + (rbase ^ (ks << 5));
@@ -329,7 +332,7 @@ void bwd_dkdv_unit(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   auto read_rows = [&](int stage, int ib, bf16x8 (&qa)[KS], bf16x8 (&da)[KS]) {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      const uint32_t a = rb[stage >> 1][ks] + (stage & 1) * SB + ib * 32 * RB;
+      const uint32_t a = rb[SETS == 2 ? stage >> 1 : 0][ks] + (SETS == 2 ? stage & 1 : stage) * SB + ib * 32 * RB;
       qa[ks] = lds_read_b128_at(a);
       da[ks] = lds_read_b128_at(a + TB);
     }
@@ -337,7 +340,10 @@ void bwd_dkdv_unit(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
 
   // ---- prologue: tiles 0 and 1 requested; S(0), dP(0); row operands of block 1
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) { to_agpr(kreg[ks]); to_agpr(vreg[ks]); }
+  for (int ks = 0; ks < KS; ++ks) {
+    if constexpr (kAsm) { to_agpr(kreg[ks]); to_agpr(vreg[ks]); }
+    else { settle(kreg[ks]); settle(vreg[ks]); }
+  }
   issue_tile(0); issue_tile(1);
   wait_vmcnt<0>();
   __syncthreads();
@@ -365,8 +371,13 @@ void bwd_dkdv_unit(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
     read_rows(0, 1, qa_n, da_n);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      mfma32_v(s_cur, q0r[ks], kreg[ks], ks == 0);
-      mfma32_v(dp_cur, d0r[ks], vreg[ks], ks == 0);
+      if constexpr (kAsm) {
+        mfma32_v(s_cur, q0r[ks], kreg[ks], ks == 0);
+        mfma32_v(dp_cur, d0r[ks], vreg[ks], ks == 0);
+      } else {
+        s_cur = mfma32(q0r[ks], kreg[ks], ks == 0 ? zero16 : s_cur);
+        dp_cur = mfma32(d0r[ks], vreg[ks], ks == 0 ? zero16 : dp_cur);
+      }
     }
   }
 
@@ -398,8 +409,13 @@ void bwd_dkdv_unit(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
 #pragma unroll
     for (int gi = 0; gi < NG; ++gi) {
       const int ks = gi >> 1;
-      if ((gi & 1) == 0) mfma32_v(s_next, qa_n[ks], kreg[ks], ks == 0, s_cur, p, pw);
-      else mfma32_v(dp_next, da_n[ks], vreg[ks], ks == 0, s_cur, p, pw);
+      if constexpr (kAsm) {
+        if ((gi & 1) == 0) mfma32_v(s_next, qa_n[ks], kreg[ks], ks == 0, s_cur, p, pw);
+        else mfma32_v(dp_next, da_n[ks], vreg[ks], ks == 0, s_cur, p, pw);
+      } else {
+        if ((gi & 1) == 0) s_next = mfma32(qa_n[ks], kreg[ks], ks == 0 ? zero16 : s_next);
+        else dp_next = mfma32(da_n[ks], vreg[ks], ks == 0 ? zero16 : dp_next);
+      }
       if (gi == 0) {
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) l4[q4] = *reinterpret_cast<const f32x4*>(lse_s + IB * 32 + 8 * q4 + 4 * g);
@@ -407,7 +423,7 @@ void bwd_dkdv_unit(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
 #pragma unroll
       for (int r = 2 * gi; r < 2 * gi + 2; ++r) {
         const int rr = r % (4 * DB), s2 = rr / (2 * DB), db = (rr >> 1) % DB, hi = rr & 1;
-        const uint32_t o = tb[ST_CUR >> 1][hi][db] + (ST_CUR & 1) * SB + (IB * 32 + 16 * s2) * RB;
+        const uint32_t o = tb[SETS == 2 ? ST_CUR >> 1 : 0][hi][db] + (SETS == 2 ? ST_CUR & 1 : ST_CUR) * SB + (IB * 32 + 16 * s2) * RB;
         if (r < 4 * DB) { if (hi) dhi[s2][db] = lds_read_tr_at(o + TB); else dlo[s2][db] = lds_read_tr_at(o + TB); }
         else { if (hi) qhi[s2][db] = lds_read_tr_at(o); else qlo[s2][db] = lds_read_tr_at(o); }
       }
@@ -521,8 +537,12 @@ void bwd_dkdv_unit(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   }
 }
 
+// head_dim 64: two workgroups per CU (252 registers, 51 KB of LDS each; one set of LDS addresses, every operand in a
+// VGPR), so that the exponentials of one meet the products of the other.  Against one workgroup with its operands in
+// AGPRs (272 registers), whole backward call: 32,768 tokens x 32 heads 27.7 -> 26.2 ms, 64 clips of 300 x 16
+// 170 -> 145 us, 2 x 4,096 x 16 456 -> 447; calls of fewer tiles than CUs lose 2% (2 x 2,048 x 2 62 -> 64).
 template <int D, class Segs, bool SPLIT>
-__global__ __launch_bounds__(kBwdWaves * 64, 1)
+__global__ __launch_bounds__(kBwdWaves * 64, D == 64 ? 2 : 1)
 void attn_bwd_dkdv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
                           const __bf16* __restrict__ v, const __bf16* __restrict__ dout,
                           const float* __restrict__ lse2, const float* __restrict__ delta,
@@ -564,8 +584,13 @@ struct DqCfg {
   static constexpr int kChunksPerThread = kDqBC * kChunksPerRow / (W * 64);
 };
 
+// Serves head_dim 64, where the exponentials weigh twice as much against the products as at 128: with 149 registers
+// three workgroups of four wavefronts share a CU, and half as many rows per workgroup spread small calls
+// over more CUs.  Against one workgroup of eight wavefronts per CU (whole backward call): 64 clips of 300 tokens x 16 heads
+// 176 -> 145 us, 2 x 2,048 tokens x 2 heads 74 -> 64, 8,192 x 12 692 -> 655, 32,768 x 32 26.9 -> 26.2 ms, 2 x 4,096 x
+// 16 440 -> 447; each K/V tile is staged twice as often.
 template <int D, int NI, int W, class Segs>
-__global__ __launch_bounds__(W * 64, (NI == 1 ? 2 : 1))
+__global__ __launch_bounds__(W * 64, NI == 1 ? 3 : 1)
 void attn_bwd_dq_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
                         const __bf16* __restrict__ v, const __bf16* __restrict__ dout,
                         const float* __restrict__ lse2g, const float* __restrict__ delta,
@@ -1647,7 +1672,7 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
                     scale * kLog2eB);
     } else {
       constexpr int NI = 1;
-      constexpr int W = 8;   // 256 query rows share each staged K/V tile
+      constexpr int W = 4;   // 128 query rows, three workgroups per CU (see the kernel)
       using Cfg = DqCfg<D, NI, W>;
       const TileIndex tq = make_tile_index<false>(segs, Cfg::kBR);
       const int n = count_tiles(tq);

@@ -93,6 +93,15 @@ def test_one_pass_backward_block_edges(head_dim, lengths):
     _assert_parity(wl, gpu, host, relative_maxabs=True)
 
 
+@pytest.mark.parametrize("lengths", [(257, 127), (383, 384, 385, 64), (640, 513, 33, 1)], ids=["257", "384", "640"])
+def test_two_pass_tile_edges_head_dim_64(lengths):
+    """Head_dim 64 beyond the one pass: 128-row query and key tiles with every kind of remainder (a row, a row
+    short, wavefronts without a row)."""
+    wl = W.Workload(f"d64_{lengths[0]}", tuple((1, 1, n) for n in lengths), 3, 64, (16, 24, 24), seed=640 + lengths[0])
+    gpu, host = _run_fwd_bwd(wl)
+    _assert_parity(wl, gpu, host, relative_maxabs=True)
+
+
 @pytest.mark.parametrize("head_dim", [64, 128])
 @pytest.mark.parametrize("lengths", [(64, 63, 33, 32, 31, 17, 5, 2, 1), (128, 127, 97, 65, 32, 16),
                                      (256, 255, 225, 193, 160, 129, 33, 8)], ids=["64", "128", "256"])
