@@ -371,6 +371,9 @@ VFM_API int vfm_attn_fwd_fp8(const void* q8, const void* k8, const void* vT8, co
  * (A backward launch at head_dim 128 whose sequences all have at most 1,024
  * rows deals both kinds of tile from one grid, per (head, sequence) the key
  * tiles and then the query tiles, with the same tile heights and XCD rule.)
+ * (With a number of heads that is no multiple of 8 and clips of unequal length,
+ * self-attention launches take the same tiles in another order: tile by tile,
+ * all heads of one tile before the next, workgroup b the b-th.)
  * (A backward run whose clips all have at most 256 tokens takes, but for small
  * runs, one workgroup per (clip, head), dealt round-robin over the XCDs.)
  * For workgroup b < *n_blocks: units[3b] = head (-1: the workgroup is grid

@@ -1654,7 +1654,7 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
     }
   }
   if (tiles == 0) return hipSuccess;
-  UnitMap um = make_unit_map(tiles, n_heads);
+  UnitMap um = make_unit_map(tiles, n_heads, unequal_units(segs));
   auto launch_dq = [&](auto stats_c) -> hipError_t {
     if constexpr (D == 128) {
       constexpr bool STATS = decltype(stats_c)::value != 0;
@@ -1662,7 +1662,7 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
       const TileIndex tq = make_tile_index<false>(segs, Cfg::kBR);
       const int n = count_tiles(tq);
       if (n == 0) return hipSuccess;
-      const UnitMap uq = make_unit_map(n, n_heads);
+      const UnitMap uq = make_unit_map(n, n_heads, unequal_units(segs));
       auto kern = attn_bwd_dq2_kernel<D, Segs, STATS>;
       hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::kLdsBytes);
@@ -1677,7 +1677,7 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
       const TileIndex tq = make_tile_index<false>(segs, Cfg::kBR);
       const int n = count_tiles(tq);
       if (n == 0) return hipSuccess;
-      const UnitMap uq = make_unit_map(n, n_heads);
+      const UnitMap uq = make_unit_map(n, n_heads, unequal_units(segs));
       auto kern = attn_bwd_dq_kernel<D, NI, W, Segs>;
       hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::kLdsBytes);
@@ -1723,7 +1723,7 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
       if (e != hipSuccess) return e;
       e = launch(fill_zero_f32x4_kernel, cgrid, dim3(256), 0, stream, acc_v, h4);
       if (e != hipSuccess) return e;
-      um = make_unit_map(tiles * q_split, n_heads);
+      um = make_unit_map(tiles * q_split, n_heads, unequal_units(segs));
       auto kern = attn_bwd_dkdv_kernel<D, Segs, true>;
       e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                               hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::kLdsBytes);

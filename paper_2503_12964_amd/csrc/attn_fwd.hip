@@ -377,7 +377,7 @@ static hipError_t launch_fwd_cfg(const void* q, const void* k, const void* v, co
   const TileIndex ti = make_tile_index<false>(segs, Cfg::kRows);
   const int tiles = count_tiles(ti);
   if (tiles == 0) return hipSuccess;
-  UnitMap um = make_unit_map(tiles, n_heads);
+  const UnitMap um = make_unit_map(tiles, n_heads, unequal_units(segs));
   const int grid = um.chunk * kNumXcd;
   auto kern = attn_fwd_kernel<D, W, Segs>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),

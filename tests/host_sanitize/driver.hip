@@ -204,6 +204,35 @@ static void check_dealt_units() {
         }
 }
 
+// The unit maps of the attention kernels: every (head, tile) exactly once; dealt out, no XCD has more tiles of any
+// clip than another but for one per head.
+static void check_unit_maps() {
+  for (int heads : {1, 2, 3, 4, 8, 12, 20, 33})
+    for (int tiles : {1, 2, 7, 58, 441})
+      for (bool unequal : {false, true}) {
+        const vfm::UnitMap um = vfm::make_unit_map(tiles, heads, unequal);
+        EXPECT((um.dealt_heads != 0) == (unequal && heads % vfm::kNumXcd != 0));
+        std::vector<int> seen(heads * tiles, 0), first(vfm::kNumXcd, 0);
+        for (int b = 0; b < um.chunk * vfm::kNumXcd; ++b) {
+          int head = -1, tile = -1;
+          if (!vfm::map_unit(um, b, head, tile)) continue;
+          EXPECT(head >= 0 && head < heads && tile >= 0 && tile < tiles);
+          ++seen[head * tiles + tile];
+          if (tile < (tiles + 1) / 2) ++first[b % vfm::kNumXcd];
+        }
+        for (int n : seen) EXPECT(n == 1);
+        const auto [lo, hi] = std::minmax_element(first.begin(), first.end());
+        if (um.dealt_heads) EXPECT(*hi - *lo <= 1);
+      }
+  vfm::SegTable t{};
+  EXPECT(!vfm::unequal_units(t));
+  t.n = 2;
+  t.len[0] = t.len[1] = 5;
+  EXPECT(!vfm::unequal_units(t));
+  t.len[1] = 4;
+  EXPECT(vfm::unequal_units(t));
+}
+
 // The one pass serves clips of up to 256 tokens; at head_dim 128 and more than 96 it needs more two-pass
 // workgroups than the chip has places for, short clips counting for their share.
 static void check_one_pass_rule() {
@@ -257,6 +286,7 @@ int main() {
   check_qk_bwd_split();
   check_bwd_order();
   check_dealt_units();
+  check_unit_maps();
   check_one_pass_rule();
   std::mt19937 rng(12345);
   void* const P = reinterpret_cast<void*>(0x10000);     // never dereferenced: the stubs launch nothing

@@ -103,6 +103,30 @@ def test_two_pass_tile_edges_head_dim_64(lengths):
 
 
 @pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("heads", [2, 12])
+def test_dealt_units_of_unequal_clips(heads, head_dim):
+    """Heads that do not divide by the XCDs and clips of unequal length: tiles are dealt out, and each clip gets
+    the bits that it gets in a call of its own."""
+    import torch
+    from paper_2503_12964_amd import binding as b
+    lens = (1301, 700, 700, 257, 5)
+    n = sum(lens)
+    gen = torch.Generator(device="cuda").manual_seed(heads + head_dim)
+    q, k, v, do = (torch.empty((n, heads, head_dim), device="cuda").normal_(generator=gen).to(torch.bfloat16) for _ in range(4))
+
+    def run(lo, hi, cu):
+        x = [t[lo:hi].contiguous() for t in (q, k, v, do)]
+        out, lse = b.vfm_attn_fwd(*x[:3], cu, 0.125)
+        return [out, lse.t().contiguous(), *b.vfm_attn_bwd(*x[:3], out, lse, x[3], cu, 0.125)]
+
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    whole = run(0, n, cu)
+    for lo, hi in zip(cu, cu[1:]):
+        for got, alone in zip(whole, run(lo, hi, np.asarray([0, hi - lo], dtype=np.int32))):
+            assert torch.equal(got[lo:hi].view(torch.uint8), alone.view(torch.uint8))
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
 @pytest.mark.parametrize("lengths", [(64, 63, 33, 32, 31, 17, 5, 2, 1), (128, 127, 97, 65, 32, 16),
                                      (256, 255, 225, 193, 160, 129, 33, 8)], ids=["64", "128", "256"])
 def test_a_clip_does_not_depend_on_its_pack_mates(head_dim, lengths):
