@@ -1228,8 +1228,11 @@ void attn_bwd_both_kernel(const __bf16* __restrict__ q, const __bf16* __restrict
 // that the five products of the backward are formed once (the two passes above form seven), every
 // operand comes from memory once and Delta needs no pass of its own.  What bounds such packs is the
 // memory path (eight tensors of the clip against 10 D flops per pair of few pairs).
-//   prologue: K into LDS, V rows into registers, Delta and lse in log2 units of all rows into LDS
-//             (out and dO straight from memory; dO is read again below while it is in L2)
+//   prologue: K into LDS, V rows into registers, lse in log2 units of all rows into LDS; Delta likewise
+//             (out and dO straight from memory; dO is read again below while it is in L2), but at head_dim 128
+//             with eight wavefronts, where no other workgroup's products hide those loads: there out rides in
+//             the ring and Delta(b+1) is formed in phase 2 of block b, behind a barrier that block b+1 has landed
+//             before (288 clips of 256 tokens x 32 heads: backward call 1,418 -> 1,368 us, 300 of 130 x 16 442 -> 419)
 //   per block b of 32 query rows (Q, dO in a ring of three LDS stages, requested two blocks ahead; two stages where that lets two
 //   workgroups share a CU):
 //     phase 1  dQ(b-1) = dS(b-1) K, every wavefront 32 columns over all keys, to memory;
@@ -1237,7 +1240,9 @@ void attn_bwd_both_kernel(const __bf16* __restrict__ q, const __bf16* __restrict
 //     barrier
 //     phase 2  dS(b) to LDS, key-major; dV^T += dO^T P, dK^T += Q^T dS
 //     barrier
-// dS is written in phase 2 and read in phase 1 only, so it needs no second copy.  Keys past the clip's end
+// dS is written in phase 2 and read in phase 1 only, so it needs no second copy.  At head_dim 64 there is room for one,
+// and with it the barrier between the phases goes (288 clips of 256 tokens x 32 heads 850 -> 810 us); at 128 it gave
+// 1% with eight wavefronts and does not fit two workgroups with four.  Keys past the clip's end
 // have dS = 0; query rows past it P = 0 (lse = +inf).  Four wavefronts serve 128 tokens in 73 KB of LDS (49 at
 // head_dim 64), so that two workgroups share a CU and one's loads and stores meet the other's products;
 // eight serve 256 tokens, at head_dim 128 one workgroup per CU.  Everything the loop could recompute it does
@@ -1250,11 +1255,17 @@ struct FusedCfg {
   static constexpr int kRows = NW * 32;                      // longest clip
   static constexpr int kBlockBytes = 32 * D * 2;             // 32 rows of one tensor
   static constexpr int kRing = D == 128 && NW == 4 ? 2 : 3;  // stages of (Q, dO) blocks
+  // out rides in the ring beside Q and dO, and Delta is formed block by block
+  static constexpr bool kStreamOut = D == 128 && NW == 8;
+  static constexpr int kStageTensors = kStreamOut ? 3 : 2;
+  static constexpr int kStageBytes = kStageTensors * kBlockBytes;
   static constexpr int kRingBase = kRows * D * 2;            // K first
-  static constexpr int kDsBase = kRingBase + kRing * 2 * kBlockBytes;
-  static constexpr int kStatBase = kDsBase + kRows * 64;     // dS: [key][32 queries] bf16; then lse2, Delta
+  static constexpr int kDsBase = kRingBase + kRing * kStageBytes;
+  static constexpr int kDsBufs = D == 128 ? 1 : 2;
+  static_assert(!kStreamOut || (kDsBufs == 1 && kRing == 3), "the barrier between the phases publishes the next block");
+  static constexpr int kStatBase = kDsBase + kDsBufs * kRows * 64;     // dS: [key][32 queries] bf16; then lse2, Delta
   static constexpr int kLdsBytes = kStatBase + 2 * kRows * 4;
-  static constexpr int kLoads = D / 8 / NW;                  // wave loads per block (Q and dO together)
+  static constexpr int kLoads = kStageBytes / 1024 / NW;     // wave loads per block (all tensors of a stage)
   // Neighbouring (clip, head) units per XCD: one at head_dim 128 (256 bytes of a row each; groups of 8 take 3%
   // longer), 8 at head_dim 64 (1 KB of a row; single units take 2 to 4% longer).
   static constexpr int kGroup = D == 128 ? 1 : 8;
@@ -1309,7 +1320,7 @@ void attn_bwd_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restric
     const int i = x * NW + wave;
     const int p = (i % (CPR / 2)) * 64 + lane;
     const int r = p / CPR;
-    src[x] = uniform_ptr((i < CPR / 2 ? q : dout) + clip_off);
+    src[x] = uniform_ptr((i < CPR / 2 ? q : i < CPR ? dout : out) + clip_off);
     st_row[x] = r;
     st_colb[x] = (uint32_t)(((p % CPR) ^ swz<D>(r)) * 16);
     st_lds[x] = __builtin_amdgcn_readfirstlane(smem_addr + Cfg::kRingBase + i * 1024);
@@ -1317,7 +1328,7 @@ void attn_bwd_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restric
   auto issue_block = [&](int stage) {   // strictly in order; blocks past the end re-read the last row
 #pragma unroll
     for (int x = 0; x < Cfg::kLoads; ++x) {
-      lds_dma16(src[x], (uint32_t)min(st_row[x], n - 1) * row_bytes + st_colb[x], st_lds[x] + stage * 2 * BB);
+      lds_dma16(src[x], (uint32_t)min(st_row[x], n - 1) * row_bytes + st_colb[x], st_lds[x] + stage * Cfg::kStageBytes);
       st_row[x] += 32;
     }
   };
@@ -1331,37 +1342,50 @@ void attn_bwd_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restric
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) vreg[ks] = *reinterpret_cast<const bf16x8*>(vp + ks * 16);
   }
-  // ---- statistics of all rows: CPR lanes per row, all loads in flight before the first sum
+  // ---- statistics: CPR lanes per row
   float* lse_s = reinterpret_cast<float*>(smem + Cfg::kStatBase);
   float* delta_s = lse_s + Cfg::kRows;
-  {
+  static_assert(Cfg::kRows <= NT, "one thread per row for lse");
+  const float lse_r = lse[(size_t)head * total + a + min(tid, n - 1)];
+  auto row_delta = [&](const u32x4& o8, const u32x4& d8) {   // this lane's 8 columns, then the row's CPR lanes
+    float s = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      s = __builtin_fmaf(__builtin_bit_cast(float, o8[e] << 16), __builtin_bit_cast(float, d8[e] << 16), s);
+      s = __builtin_fmaf(__builtin_bit_cast(float, o8[e] & 0xffff0000u), __builtin_bit_cast(float, d8[e] & 0xffff0000u), s);
+    }
+#pragma unroll
+    for (int o = CPR / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, CPR);
+    return s;
+  };
+  // Delta of the rows of one block, out and dO from its ring stage (both swizzled alike)
+  auto block_delta = [&](int blk, int stg) {
+    static_assert(!Cfg::kStreamOut || NT == 32 * CPR, "one chunk per thread");
+    int t = tid;
+    asm volatile("" : "+v"(t));
+    const char* dt = smem + Cfg::kRingBase + stg * Cfg::kStageBytes + BB + tile_off<D>(t / CPR, (t % CPR) * 8);
+    const float s = row_delta(*reinterpret_cast<const u32x4*>(dt + BB), *reinterpret_cast<const u32x4*>(dt));
+    const int r = blk * 32 + t / CPR;
+    if (t % CPR == 0) delta_s[r] = r < n ? s : 0.f;
+  };
+  if constexpr (!Cfg::kStreamOut) {   // of all rows at once, all loads in flight before the first sum
     constexpr int RP = NT / CPR, PASSES = Cfg::kRows / RP;
-    static_assert(Cfg::kRows <= NT, "one thread per row for lse");
     u32x4 oa[PASSES], da[PASSES];
     const int chunk = tid % CPR;
-    const float lse_r = lse[(size_t)head * total + a + min(tid, n - 1)];
 #pragma unroll
     for (int i = 0; i < PASSES; ++i) {   // (rows past the end: copies of the last one, no branch between the loads)
       const size_t off = clip_off + (size_t)min(i * RP + tid / CPR, n - 1) * row_stride + chunk * 8;
       oa[i] = *reinterpret_cast<const u32x4*>(out + off);
       da[i] = *reinterpret_cast<const u32x4*>(dout + off);
     }
-    if (tid < Cfg::kRows) lse_s[tid] = tid < n ? lse_r * kLog2eB : INFINITY;
 #pragma unroll
     for (int i = 0; i < PASSES; ++i) {
       const int r = i * RP + tid / CPR;
-      float s = 0.f;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        s = __builtin_fmaf(__builtin_bit_cast(float, oa[i][e] << 16), __builtin_bit_cast(float, da[i][e] << 16), s);
-        s = __builtin_fmaf(__builtin_bit_cast(float, oa[i][e] & 0xffff0000u),
-                           __builtin_bit_cast(float, da[i][e] & 0xffff0000u), s);
-      }
-#pragma unroll
-      for (int o = CPR / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, CPR);
+      const float s = row_delta(oa[i], da[i]);
       if (chunk == 0) delta_s[r] = r < n ? s : 0.f;
     }
   }
+  if (tid < Cfg::kRows) lse_s[tid] = tid < n ? lse_r * kLog2eB : INFINITY;
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) settle(vreg[ks]);
 
@@ -1379,6 +1403,7 @@ void attn_bwd_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restric
   const int col0 = (wave % (D / 32)) * 32, half0 = NROW == 2 ? 0 : wave / (D / 32);
   const bool dq_part = half0 < 2;                          // (head_dim 64 has two parts per half only)
   auto block_dq = [&](int blk, int rows_valid) {           // dQ of block blk, whose dS is in LDS -> memory
+    const int ds_buf = Cfg::kDsBufs == 2 ? (blk & 1) * (Cfg::kRows * 64) : 0;
     f32x4 acc[2][NROW];
 #pragma unroll
     for (int x = 0; x < 2; ++x)
@@ -1403,7 +1428,7 @@ void attn_bwd_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restric
     bf16x8 kf[2][2], df[2][NROW];
     auto read = [&](int kk, bf16x8 (&kr)[2], bf16x8 (&dr)[NROW]) {
       const char* kb = smem + kk * 32 * RB;
-      const char* db = smem + kk * 32 * 64;
+      const char* db = smem + ds_buf + kk * 32 * 64;
 #pragma unroll
       for (int x = 0; x < 2; ++x)
         kr[x] = join_tr(lds_read_tr(kb, ktr[0] ^ (x * 32)), lds_read_tr(kb, ktr[1] ^ (x * 32)));
@@ -1469,12 +1494,16 @@ void attn_bwd_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restric
   const bool late_dq = NW == 8 && wave >= 4;
   wait_vmcnt<0>();          // K, the first two blocks
   int stage = 0;            // b mod the ring's stages
+  if constexpr (Cfg::kStreamOut) {
+    __syncthreads();
+    block_delta(0, 0);
+  }
   for (int b = 0; b < n_blk; ++b) {
     // block b has landed (only block b+1's loads may be outstanding; dq stores only make the wait
     // stricter), everyone is done with block b-1, dS(b-1) is complete
-    wait_vmcnt<(Cfg::kRing - 2) * Cfg::kLoads>();
+    if constexpr (!Cfg::kStreamOut) wait_vmcnt<(Cfg::kRing - 2) * Cfg::kLoads>();
     __syncthreads();
-    const char* qt = smem + Cfg::kRingBase + stage * 2 * BB;
+    const char* qt = smem + Cfg::kRingBase + stage * Cfg::kStageBytes;
     if (Cfg::kRing == 3 || b > 0) issue_block(stage == 0 ? Cfg::kRing - 1 : stage - 1);
     stage = stage == Cfg::kRing - 1 ? 0 : stage + 1;
     if (b > 0 && !late_dq && dq_part) block_dq(b - 1, 32);
@@ -1534,11 +1563,15 @@ void attn_bwd_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restric
       }
     }
     if (b > 0 && late_dq && dq_part) block_dq(b - 1, 32);
-    __syncthreads();   // everyone has read dS(b-1)
+    if constexpr (Cfg::kStreamOut) wait_vmcnt<Cfg::kLoads>();   // block b+1 has landed
+    if constexpr (Cfg::kDsBufs == 1) __syncthreads();   // everyone has read dS(b-1)
+    if constexpr (Cfg::kStreamOut) {
+      if (b + 1 < n_blk) block_delta(b + 1, stage);
+    }
     if (active) {
       int j = jrow;
       asm volatile("" : "+v"(j));
-      char* ds_w = smem + Cfg::kDsBase + j * 64 + 8 * g;
+      char* ds_w = smem + Cfg::kDsBase + (Cfg::kDsBufs == 2 ? (b & 1) * (Cfg::kRows * 64) : 0) + j * 64 + 8 * g;
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
         const bf16x8 d = dsb[q4 >> 1];
