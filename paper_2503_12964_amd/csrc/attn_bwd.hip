@@ -826,10 +826,27 @@ struct Dq2Cfg {
   static constexpr int kBR = kDq2Waves * 64;                 // query rows per workgroup
   static constexpr int kTileBytes = kDqBC * D * 2;           // one K or V tile
   static constexpr int kStageBytes = 2 * kTileBytes;         // K tile, V tile
-  static constexpr int kLdsBytes = kDq2Ring * kStageBytes;
+  // a wavefront's 64 rows of Q and of dO on their way into registers: behind the ring's first stage
+  static constexpr int kOwnBase = kStageBytes;
+  static constexpr int kOwnBytes = 2 * 64 * D * 2;
+  static constexpr int kLdsBytes = kOwnBase + kDq2Waves * kOwnBytes;
+  static_assert(kLdsBytes >= kDq2Ring * kStageBytes && kLdsBytes <= 160 * 1024, "ring, LDS of one CU");
   static constexpr int kChunksPerRow = D / 8;
   static constexpr int kChunksPerThread = kDqBC * kChunksPerRow / (kDq2Waves * 64);
 };
+
+// Sum over a lane's row of 16 lanes, in every lane: v + the value 8, then 4, 2, 1 lanes away (rotations).
+__device__ __forceinline__ float row16_sum(float v) {
+  auto add = [&](auto ror) {
+    constexpr int kRor = 0x120 + decltype(ror)::value;   // row_ror
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), kRor, 0xf, 0xf, true));
+  };
+  add(IntC<8>{});
+  add(IntC<4>{});
+  add(IntC<2>{});
+  add(IntC<1>{});
+  return v;
+}
 
 // The work of one workgroup: query tile tq of sequence seq, one head.  STATS: form Delta and lse in log2
 // units of the tile's rows here, from `out` and `lse`, and leave them for the dK/dV pass (Delta of a sequence
@@ -869,53 +886,6 @@ void bwd_dq2_unit(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   const size_t head_off = (size_t)head * D;
   const __bf16* kbase = k + head_off;
   const __bf16* vbase = v + head_off;
-
-  // ---- Q and dO rows of the two query blocks as B operands (AGPRs); lse, Delta per lane
-  bf16x8 qreg[2][KS], doreg[2][KS];
-  float lse2[2], dlt[2];
-  int qrow[2];
-#pragma unroll
-  for (int ib = 0; ib < 2; ++ib) {
-    qrow[ib] = q0 + (wave * 2 + ib) * 32 + c;
-    const int r = min(qrow[ib], q_b - 1);
-    const size_t off = (size_t)r * row_stride + head_off + 8 * g;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      qreg[ib][ks] = *reinterpret_cast<const bf16x8*>(q + off + ks * 16);
-      doreg[ib][ks] = *reinterpret_cast<const bf16x8*>(dout + off + ks * 16);
-    }
-    const size_t stat = (size_t)head * total + r;
-    if constexpr (STATS) {
-      bf16x8 oreg[KS];
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) oreg[ks] = *reinterpret_cast<const bf16x8*>(out + off + ks * 16);
-      lse2[ib] = lse[stat] * kLog2eB;
-      // the order of bwd_prepare_kernel's sums (chunks of 8 columns, then pairs of chunks 8, 4, 2, 1 apart; the
-      // one-pass kernel's too), so that a clip's gradients do not depend, to the bit, on what else is in
-      // the pack
-      float s[KS];
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        s[ks] = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s[ks] = __builtin_fmaf((float)oreg[ks][e], (float)doreg[ib][ks][e], s[ks]);
-      }
-#pragma unroll
-      for (int o = KS / 2; o > 0; o >>= 1)
-#pragma unroll
-        for (int ks = 0; ks < o; ++ks) s[ks] += s[ks + o];
-      dlt[ib] = pair_sum(s[0]);
-      const bool few = segs.kv_len(seq) <= kShortKeys;
-      if (few) dlt[ib] = delta[stat];
-      if (g == 0 && qrow[ib] < q_b) {
-        lse2g[stat] = lse2[ib];
-        if (!few) delta[stat] = dlt[ib];
-      }
-    } else {
-      lse2[ib] = lse2g[stat];
-      dlt[ib] = delta[stat];
-    }
-  }
 
   // ---- K/V staging with direct global->LDS loads; tiles are requested in sequence
   const uint32_t row_bytes = (uint32_t)row_stride * 2u;
@@ -976,12 +946,6 @@ void bwd_dq2_unit(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   const int n_blocks = 2 * n_tiles;
   const int tail_rows = seg_b - seg_a - (n_tiles - 1) * kDqBC;   // valid rows of the last tile
 
-#pragma unroll
-  for (int ib = 0; ib < 2; ++ib)
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) { to_agpr(qreg[ib][ks]); to_agpr(doreg[ib][ks]); }
-#pragma unroll
-  for (int ib = 0; ib < 2; ++ib) asm volatile("" :: "v"(lse2[ib]), "v"(dlt[ib]));
   // A wavefront whose 64 query rows all lie past the end of the sequence (ragged last tile)
   // has nothing to compute.  It still fetches its share of every K/V tile, takes part in
   // zeroing the last tile's tail rows and meets every barrier, in the order of the loop
@@ -990,9 +954,9 @@ void bwd_dq2_unit(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   // around the zeroing; the epilogue's wait and barrier.
   if (q0 + wave * 64 >= q_b) {
     issue_tile(0);
-    issue_tile(1);
-    wait_vmcnt<2 * CPT>();
+    wait_vmcnt<0>();
     __syncthreads();
+    issue_tile(1);
     for (int t = 1; t < n_tiles; ++t) {
       wait_vmcnt<0>();
       __syncthreads();
@@ -1012,10 +976,94 @@ void bwd_dq2_unit(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
     return;
   }
 
+  // ---- this wavefront's Q and dO rows as B operands (AGPRs); lse, Delta per lane.  The rows come through LDS
+  // (direct loads of whole rows, four per instruction, chunk order as in a tile): loaded into registers
+  // as operands, 32 bytes of each of 32 rows per instruction, a workgroup of 512 keys spent a third of its life on
+  // them.  `out` comes in rows too.  (Backward call: 56,320 queries x 512 keys x 32 heads 1,781 -> 1,722 us, 8 x 1,000
+  // tokens x 8 heads 126 -> 123, 300 x 4 19.8 -> 18.4; level from 4,096 tokens on.)
+  const uint32_t own = smem_addr + Cfg::kOwnBase + wave * Cfg::kOwnBytes;   // Q rows, then dO rows
+  const int row_w = q0 + wave * 64;
+  {
+    const __bf16* qbase = q + head_off;
+    const __bf16* dobase = dout + head_off;
+    const uint32_t own_s = __builtin_amdgcn_readfirstlane(own);
+#pragma unroll
+    for (int x = 0; x < 16; ++x) {
+      const int r = x * 4 + (lane >> 4);
+      const uint32_t off = (uint32_t)min(row_w + r, q_b - 1) * row_bytes + (uint32_t)(((lane & 15) ^ swz<D>(r)) * 16);
+      lds_dma16(qbase, off, own_s + x * 1024);
+      lds_dma16(dobase, off, own_s + 64 * RB + x * 1024);
+    }
+  }
   issue_tile(0);
+  bf16x8 qreg[2][KS], doreg[2][KS];
+  float lse2[2], dlt[2];
+  int qrow[2];
+  size_t stat[2];
+#pragma unroll
+  for (int ib = 0; ib < 2; ++ib) {
+    qrow[ib] = row_w + ib * 32 + c;
+    stat[ib] = (size_t)head * total + min(qrow[ib], q_b - 1);
+  }
+  auto read_own = [&]() {
+#pragma unroll
+    for (int ib = 0; ib < 2; ++ib)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const uint32_t a = own + (tile_off<D>(c, 8 * g) ^ (ks << 5)) + ib * 32 * RB;
+        qreg[ib][ks] = lds_read_b128_at(a);
+        doreg[ib][ks] = lds_read_b128_at(a + 64 * RB);
+        to_agpr(qreg[ib][ks]);
+        to_agpr(doreg[ib][ks]);
+      }
+  };
+  if constexpr (STATS) {
+    bf16x8 orow[16];
+#pragma unroll
+    for (int x = 0; x < 16; ++x)
+      orow[x] = *reinterpret_cast<const bf16x8*>(out + (size_t)min(row_w + x * 4 + (lane >> 4), q_b - 1) * row_stride +
+                                                 head_off + (lane & 15) * 8);
+#pragma unroll
+    for (int ib = 0; ib < 2; ++ib) lse2[ib] = lse[stat[ib]] * kLog2eB;
+    wait_vmcnt<0>();
+    // the order of bwd_prepare_kernel's sums (chunks of 8 columns, then pairs of chunks 8, 4, 2, 1 apart; the
+    // one-pass kernel's too), so that a clip's gradients do not depend, to the bit, on what else is in
+    // the pack.  (Rotations by 8, 4, 2, 1 within a row's 16 lanes: after each the sums repeat with that period.)
+    float s[16];
+#pragma unroll
+    for (int x = 0; x < 16; ++x) {
+      const bf16x8 d = lds_read_b128_at(own + 64 * RB + tile_off<D>(x * 4 + (lane >> 4), (lane & 15) * 8));
+      s[x] = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s[x] = __builtin_fmaf((float)orow[x][e], (float)d[e], s[x]);
+      s[x] = row16_sum(s[x]);
+    }
+    read_own();
+    asm volatile("" ::: "memory");   // (the sums take the place of rows read above)
+    if ((lane & 15) == 0)
+#pragma unroll
+      for (int x = 0; x < 16; ++x)
+        *reinterpret_cast<__attribute__((address_space(3))) float*>(own + (x * 4 + (lane >> 4)) * 4) = s[x];
+    const bool few = segs.kv_len(seq) <= kShortKeys;
+#pragma unroll
+    for (int ib = 0; ib < 2; ++ib) {
+      dlt[ib] = *reinterpret_cast<const __attribute__((address_space(3))) float*>(own + (ib * 32 + c) * 4);
+      if (few) dlt[ib] = delta[stat[ib]];
+      if (g == 0 && qrow[ib] < q_b) {
+        lse2g[stat[ib]] = lse2[ib];
+        if (!few) delta[stat[ib]] = dlt[ib];
+      }
+    }
+  } else {
+#pragma unroll
+    for (int ib = 0; ib < 2; ++ib) { lse2[ib] = lse2g[stat[ib]]; dlt[ib] = delta[stat[ib]]; }
+    wait_vmcnt<0>();
+    read_own();
+  }
+#pragma unroll
+  for (int ib = 0; ib < 2; ++ib) asm volatile("" :: "v"(lse2[ib]), "v"(dlt[ib]));
+  __syncthreads();            // tile 0 has landed, everyone has its rows
   issue_tile(1);              // (re-requests the last rows when the clip has a single tile)
-  wait_vmcnt<2 * CPT>();      // tile 0 has landed
-  __syncthreads();
 
   // ---- state carried between half-steps
   f32x16 sacc[2], dpacc[2];   // S^T, dP^T of the current key block, per query block
