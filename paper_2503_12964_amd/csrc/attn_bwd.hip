@@ -175,6 +175,38 @@ struct BwdCfg {
   static constexpr int kLoadsPerWave = kBwdBQ * kChunksPerRow / (kBwdWaves * 64);  // per tile, per tensor
 };
 
+// Adds a wavefront's 32 x D fp32 tile (accumulator layout, see store_tile_rows) to rows of fp32 sums in memory.  Turned
+// through 32*D*4 bytes of LDS (16-byte chunk x of row r kept at chunk x ^ (r mod chunks-per-row)), so that an instruction
+// adds 64 neighbouring elements.  Straight from the accumulators, 4 bytes of each of 64 places, the additions took
+// as long as the products of a small call (whole backward, before -> now: 9,000 x 100 and 4,000 x 300 keys, 16 heads
+// 251 -> 131 us; 20,000 x 77, 8 heads 152 -> 87; 56,320 x 512, 32 heads 1,722 -> 1,650).
+template <int D>
+__device__ __forceinline__ void add_tile_rows(char* turn, const f32x16 (&acc)[D / 32], float mul, float* dst,
+                                              size_t row_stride, int rows_valid) {
+  constexpr int CPR = D / 4, RB = D * 4;
+  const int lane = threadIdx.x & 63, c = lane & 31, g = lane >> 5;
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      f32x4 a;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[e] = acc[db][q4 * 4 + e] * mul;
+      *reinterpret_cast<f32x4*>(turn + c * RB + (((db * 8 + q4 * 2 + g) ^ (c & (CPR - 1))) << 4)) = a;
+    }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  for (int r = 0; r < min(32, rows_valid); ++r)
+#pragma unroll
+    for (int x = 0; x < D; x += 64) {
+      const int col = x + lane;
+      const float w = *reinterpret_cast<const float*>(turn + r * RB + (((col >> 2) ^ (r & (CPR - 1))) << 4) + (col & 3) * 4);
+      __hip_atomic_fetch_add(dst + (size_t)r * row_stride + col, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // SPLIT: the sequence's query range is cut into q_split chunks, one workgroup each; partial
 // dK/dV are added to zeroed fp32 accumulators (dkv32: dK, then dV) with fp32 atomics and
 // converted afterwards.  Used when a few long key tiles would otherwise leave CUs idle.
@@ -359,7 +391,7 @@ void bwd_dkdv_unit(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
       issue_tile((t + 2) % kBwdRing);
     }
     wait_vmcnt<0>();
-    if constexpr (!SPLIT) __syncthreads();
+    __syncthreads();
     return;
   }
 
@@ -510,28 +542,16 @@ void bwd_dkdv_unit(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   }
   wait_vmcnt<0>();   // no load may still be writing LDS when the workgroup ends
 
-  // ---- epilogue: dK (scaled) and dV for this lane's key row
-  if (jvalid) {
-    if constexpr (SPLIT) {
-      float* dkp = dkv32 + ((size_t)jrow * n_heads + head) * D + 4 * g;
-      float* dvp = dkp + kv_elems;
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            __hip_atomic_fetch_add(dkp + db * 32 + q4 * 8 + e, dkacc[db][q4 * 4 + e] * scale, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_fetch_add(dvp + db * 32 + q4 * 8 + e, dvacc[db][q4 * 4 + e], __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-          }
-    }
-  }
-  if constexpr (!SPLIT) {
-    __syncthreads();   // the ring is free: each wavefront turns its tiles through a piece of it
+  // ---- epilogue: dK (scaled) and dV of this wavefront's key rows
+  __syncthreads();   // the ring is free: each wavefront turns its tiles through a piece of it
+  const int row0 = j0 + wave * 32;
+  if constexpr (SPLIT) {
+    char* turn = smem + wave * (32 * D * 4);
+    float* dkp = dkv32 + ((size_t)row0 * n_heads + head) * D;
+    add_tile_rows<D>(turn, dkacc, scale, dkp, row_stride, kv_b - row0);
+    add_tile_rows<D>(turn, dvacc, 1.0f, dkp + kv_elems, row_stride, kv_b - row0);
+  } else {
     char* turn = smem + wave * (32 * RB);
-    const int row0 = j0 + wave * 32;
     store_tile_rows<D>(turn, dkacc, scale, dk + (size_t)row0 * row_stride + head_off, row_stride, kv_b - row0);
     store_tile_rows<D>(turn, dvacc, 1.0f, dv + (size_t)row0 * row_stride + head_off, row_stride, kv_b - row0);
   }
@@ -561,15 +581,16 @@ void attn_bwd_dkdv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict
                                 scale_log2, dkv32, kv_elems, q_split, head, seq, tk, q_chunk);
 }
 
-// fp32 accumulators -> bf16 gradients (after a split dK/dV pass); also zeroes them beforehand
-__global__ void fill_zero_f32x4_kernel(f32x4* p, size_t n4) {
+// The fp32 sums of a split dK/dV pass, dK's and dV's in one launch each (blockIdx.y): zeroed before, -> bf16 after
+__global__ void fill_zero_f32x4_kernel(f32x4* p0, f32x4* p1, size_t n4) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-  if (i < n4) p[i] = z;
+  if (i < n4) (blockIdx.y ? p1 : p0)[i] = z;
 }
-__global__ void f32_to_bf16_kernel(const f32x4* __restrict__ src, bf16x4* __restrict__ dst, size_t n4) {
+__global__ void f32_to_bf16_kernel(const f32x4* __restrict__ src0, const f32x4* __restrict__ src1,
+                                   bf16x4* __restrict__ dst0, bf16x4* __restrict__ dst1, size_t n4) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n4) dst[i] = to_bf16x4(src[i]);
+  if (i < n4) (blockIdx.y ? dst1 : dst0)[i] = to_bf16x4((blockIdx.y ? src1 : src0)[i]);
 }
 
 // ---------------------------------------------------------------- dQ
@@ -1797,12 +1818,10 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
       // other runs of the same call own the rest of dk, dv
       const size_t kv_elems = (size_t)total_kv * n_heads * D;
       const size_t lo4 = (size_t)kv_lo * n_heads * D / 4, h4 = (size_t)(kv_hi - kv_lo) * n_heads * D / 4;
-      const dim3 cgrid((unsigned)((h4 + 255) / 256));
+      const dim3 cgrid((unsigned)((h4 + 255) / 256), 2);
       f32x4* acc_k = (f32x4*)dkv32 + lo4;
       f32x4* acc_v = (f32x4*)(dkv32 + kv_elems) + lo4;
-      e = launch(fill_zero_f32x4_kernel, cgrid, dim3(256), 0, stream, acc_k, h4);
-      if (e != hipSuccess) return e;
-      e = launch(fill_zero_f32x4_kernel, cgrid, dim3(256), 0, stream, acc_v, h4);
+      e = launch(fill_zero_f32x4_kernel, cgrid, dim3(256), 0, stream, acc_k, acc_v, h4);
       if (e != hipSuccess) return e;
       um = make_unit_map(tiles * q_split, n_heads, unequal_units(segs));
       auto kern = attn_bwd_dkdv_kernel<D, Segs, true>;
@@ -1813,9 +1832,8 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
                  lse2, delta, sentinel, (__bf16*)dk, (__bf16*)dv, segs, um, ti, total, n_heads, scale,
                  scale * kLog2eB, dkv32, kv_elems, q_split);
       if (e != hipSuccess) return e;
-      e = launch(f32_to_bf16_kernel, cgrid, dim3(256), 0, stream, (const f32x4*)acc_k, (bf16x4*)dk + lo4, h4);
-      if (e != hipSuccess) return e;
-      e = launch(f32_to_bf16_kernel, cgrid, dim3(256), 0, stream, (const f32x4*)acc_v, (bf16x4*)dv + lo4, h4);
+      e = launch(f32_to_bf16_kernel, cgrid, dim3(256), 0, stream, (const f32x4*)acc_k, (const f32x4*)acc_v,
+                 (bf16x4*)dk + lo4, (bf16x4*)dv + lo4, h4);
       if (e != hipSuccess) return e;
     } else {
       auto kern = attn_bwd_dkdv_kernel<D, Segs, false>;

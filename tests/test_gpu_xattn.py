@@ -72,6 +72,17 @@ def test_ragged_cross_attention_matches_oracle(name):
         assert not np.any(g_ref[1][77:90])
 
 
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("keys", [(1, 33), (77, 160), (129, 31, 200)], ids=str)
+def test_long_query_ranges_against_few_keys(hd, keys):
+    """Few key tiles and over 1,024 queries: dK, dV come from several workgroups' shares, added to fp32 sums
+    (key tiles with missing rows and wavefronts; shares of unequal size)."""
+    queries = (2100, 1030, 1601)[:len(keys)]
+    cu_q, cu_kv = (np.concatenate([[0], np.cumsum(x)]) for x in (queries, keys))
+    dev, gpu, scale = _run(_binding(), cu_q, cu_kv, 2, hd, seed=33 + hd + keys[0])
+    _assert(gpu, dev, cu_q, cu_kv, scale)
+
+
 def test_equal_ranges_are_bitwise_the_self_attention_result():
     b = _binding()
     cu = np.array([0, 300, 301, 301, 891])
