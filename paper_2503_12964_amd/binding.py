@@ -9,7 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
-from typing import Optional, Sequence, Tuple
+from typing import Sequence, Tuple
 
 import numpy as np
 
@@ -26,6 +26,7 @@ EXPORTS = ("vfm_rope3d", "vfm_qknorm_rope3d", "vfm_qknorm_rope3d_bwd", "vfm_attn
            "vfm_attn_fwd_tile_rows")
 
 _lib = None
+_torch = None                # set when the library is loaded
 
 
 class VfmError(RuntimeError):
@@ -36,7 +37,7 @@ class VfmError(RuntimeError):
 
 def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     """dlopen libvfm.so and declare the C signatures.  Raises if it is missing."""
-    global _lib
+    global _lib, _torch
     if _lib is not None and path == LIB_PATH:
         return _lib
     if not os.path.exists(path):
@@ -48,10 +49,11 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     # ships its own copy under that soname) loaded first, the dynamic linker gives the library
     # that copy.  Loaded the other way round, the library would bring in the system's copy as a
     # second runtime in the process, and a second runtime finds no device.
-    import torch  # noqa: F401
+    import torch
+    _torch = torch
     lib = ctypes.CDLL(path)
     c_int, c_float, c_void_p, c_size_t = ctypes.c_int, ctypes.c_float, ctypes.c_void_p, ctypes.c_size_t
-    p_i32 = ctypes.POINTER(ctypes.c_int32)
+    p_i32 = c_void_p          # host int32 arrays: passed as the address of their first element
     lib.vfm_rope3d.restype = c_int
     lib.vfm_rope3d.argtypes = [c_void_p, p_i32, p_i32, c_int, c_int, c_int, c_int, c_int, c_int, c_int,
                                c_float, c_int, c_int, c_void_p]
@@ -157,40 +159,51 @@ def vfm_attn_fwd_tile_rows(cu_seqlens, head_dim: int, run: int = 0) -> int:
     return rows.value
 
 
+# What a call costs here is what bounds the smallest steps: the argument handling of one call took 7 to 9 us beside the
+# 4 to 5 us of the native call and its launch (current_stream() alone 2.6 us, a ctypes pointer to an array 1.2), now 2 to 4.
+_I32 = np.dtype(np.int32)
+
+
 def _host_i32(a) -> np.ndarray:
+    if type(a) is np.ndarray and a.dtype is _I32 and a.ndim and a.flags.c_contiguous:
+        return a
     return np.ascontiguousarray(np.asarray(a, dtype=np.int32))
 
 
-def _i32_ptr(a: np.ndarray):
-    return a.ctypes.data_as(ctypes.POINTER(ctypes.c_int32))
+def _i32_ptr(a: np.ndarray) -> int:
+    """Address of the first element; the caller keeps the array alive over the native call."""
+    return a.__array_interface__["data"][0]
 
 
-def _stream_ptr(stream) -> Optional[int]:
+def _stream_ptr(stream) -> int:
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(int(getattr(stream, "cuda_stream", stream)))
+        try:
+            c = _torch._C
+            return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+        except AttributeError:      # another PyTorch: the public way, slower
+            stream = _torch.cuda.current_stream()
+    return int(getattr(stream, "cuda_stream", stream))
 
 
-def _dev(t, name: str) -> ctypes.c_void_p:
+def _dev(t, name: str) -> int:
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError(f"{name} must be a contiguous device tensor")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _dtype_code(t) -> int:
-    import torch
-    if t.dtype == torch.bfloat16:
+    dt = t.dtype
+    if dt is _torch.bfloat16:
         return VFM_BF16
-    if t.dtype == torch.float32:
+    if dt is _torch.float32:
         return VFM_F32
-    raise ValueError(f"unsupported dtype {t.dtype}")
+    raise ValueError(f"unsupported dtype {dt}")
 
 
 def vfm_rope3d(x, thw, cu_seqlens, dims: Sequence[int], theta: float = 10000.0,
                inverse: bool = False, stream=None):
     """In-place 3D RoPE on x[total, heads, head_dim] (device, bf16).  Returns x."""
-    lib = load_library()
+    lib = _lib or load_library()
     cu = _host_i32(cu_seqlens)
     g = _host_i32(thw).reshape(-1)
     total, heads, hd = x.shape
@@ -203,13 +216,13 @@ def vfm_rope3d(x, thw, cu_seqlens, dims: Sequence[int], theta: float = 10000.0,
 def vfm_qknorm_rope3d(x, gain, eps: float, thw, cu_seqlens, dims: Sequence[int], theta: float = 10000.0,
                       y=None, stream=None):
     """y = RoPE3D(gain * x / sqrt(mean_d x^2 + eps)) per (token, head); y=None works in place on x."""
-    lib = load_library()
+    lib = _lib or load_library()
     cu = _host_i32(cu_seqlens)
     g = _host_i32(thw).reshape(-1)
     total, heads, hd = x.shape
     y = x if y is None else y
     _check(lib.vfm_qknorm_rope3d(_dev(x, "x"), _dev(gain, "gain"), float(eps), _dev(y, "y"), _i32_ptr(g),
-                                 _i32_ptr(cu), int(cu.size - 1), int(total), int(heads), int(hd),
+                                 _i32_ptr(cu), cu.size - 1, total, heads, hd,
                                  int(dims[0]), int(dims[1]), int(dims[2]), float(theta), _dtype_code(x),
                                  _stream_ptr(stream)))
     return y
@@ -218,13 +231,12 @@ def vfm_qknorm_rope3d(x, gain, eps: float, thw, cu_seqlens, dims: Sequence[int],
 def vfm_qknorm_rope3d_bwd(x, gain, eps: float, dy, thw, cu_seqlens, dims: Sequence[int],
                           theta: float = 10000.0, dx=None, dgain=None, stream=None) -> Tuple:
     """dx (bf16, shape of x; may be dy itself) and dgain (fp32 [head_dim]) given the forward's input x."""
-    import torch
-    lib = load_library()
+    lib = _lib or load_library()
     cu = _host_i32(cu_seqlens)
     g = _host_i32(thw).reshape(-1)
     total, heads, hd = x.shape
-    dx = torch.empty_like(x) if dx is None else dx
-    dgain = torch.empty(hd, dtype=torch.float32, device=x.device) if dgain is None else dgain
+    dx = _torch.empty_like(x) if dx is None else dx
+    dgain = _torch.empty(hd, dtype=_torch.float32, device=x.device) if dgain is None else dgain
     _check(lib.vfm_qknorm_rope3d_bwd(_dev(x, "x"), _dev(gain, "gain"), float(eps), _dev(dy, "dy"), _dev(dx, "dx"),
                                      _dev(dgain, "dgain"), _i32_ptr(g), _i32_ptr(cu), int(cu.size - 1),
                                      int(total), int(heads), int(hd), int(dims[0]), int(dims[1]), int(dims[2]),
@@ -234,14 +246,13 @@ def vfm_qknorm_rope3d_bwd(x, gain, eps: float, dy, thw, cu_seqlens, dims: Sequen
 
 def vfm_attn_fwd(q, k, v, cu_seqlens, scale: float, out=None, lse=None, stream=None) -> Tuple:
     """out[total, heads, head_dim] (bf16) and lse[heads, total] (fp32) for packed q, k, v."""
-    import torch
-    lib = load_library()
+    lib = _lib or load_library()
     cu = _host_i32(cu_seqlens)
     total, heads, hd = q.shape
     if out is None:
-        out = torch.empty_like(q)
+        out = _torch.empty_like(q)
     if lse is None:
-        lse = torch.empty((heads, total), dtype=torch.float32, device=q.device)
+        lse = _torch.empty((heads, total), dtype=_torch.float32, device=q.device)
     _check(lib.vfm_attn_fwd(_dev(q, "q"), _dev(k, "k"), _dev(v, "v"), _i32_ptr(cu), int(cu.size - 1), int(total),
                             int(heads), int(hd), float(scale), _dev(out, "out"), _dev(lse, "lse"),
                             _dtype_code(q), _stream_ptr(stream)))
@@ -255,18 +266,17 @@ def vfm_attn_bwd_workspace_size(total_tokens: int, n_heads: int, head_dim: int) 
 def vfm_attn_bwd(q, k, v, out, lse, dout, cu_seqlens, scale: float, dq=None, dk=None, dv=None,
                  workspace=None, stream=None) -> Tuple:
     """dq, dk, dv (bf16, shape of q) given the forward's out and lse."""
-    import torch
-    lib = load_library()
+    lib = _lib or load_library()
     cu = _host_i32(cu_seqlens)
     total, heads, hd = q.shape
-    dq = torch.empty_like(q) if dq is None else dq
-    dk = torch.empty_like(k) if dk is None else dk
-    dv = torch.empty_like(v) if dv is None else dv
-    need = vfm_attn_bwd_workspace_size(total, heads, hd)
+    dq = _torch.empty_like(q) if dq is None else dq
+    dk = _torch.empty_like(k) if dk is None else dk
+    dv = _torch.empty_like(v) if dv is None else dv
     if workspace is None:
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
+        need = vfm_attn_bwd_workspace_size(total, heads, hd)
+        workspace = _torch.empty(max(need, 256), dtype=_torch.uint8, device=q.device)
     _check(lib.vfm_attn_bwd(_dev(q, "q"), _dev(k, "k"), _dev(v, "v"), _dev(out, "out"), _dev(lse, "lse"),
-                            _dev(dout, "dout"), _i32_ptr(cu), int(cu.size - 1), int(total), int(heads), int(hd),
+                            _dev(dout, "dout"), _i32_ptr(cu), cu.size - 1, total, heads, hd,
                             float(scale), _dev(dq, "dq"), _dev(dk, "dk"), _dev(dv, "dv"),
                             _dev(workspace, "workspace"), int(workspace.numel() * workspace.element_size()),
                             _dtype_code(q), _stream_ptr(stream)))
@@ -276,7 +286,7 @@ def vfm_attn_bwd(q, k, v, out, lse, dout, cu_seqlens, scale: float, dq=None, dk=
 def vfm_attn_bwd_noalloc(q, k, v, out, lse, dout, cu_seqlens, scale: float, dq, dk, dv, stream=None) -> Tuple:
     """vfm_attn_bwd without a workspace (the library's built-in scratch holds the statistics).
     The caller passes every output; nothing is allocated here or in the library."""
-    lib = load_library()
+    lib = _lib or load_library()
     cu = _host_i32(cu_seqlens)
     total, heads, hd = q.shape
     _check(lib.vfm_attn_bwd_noalloc(_dev(q, "q"), _dev(k, "k"), _dev(v, "v"), _dev(out, "out"), _dev(lse, "lse"),
@@ -288,17 +298,16 @@ def vfm_attn_bwd_noalloc(q, k, v, out, lse, dout, cu_seqlens, scale: float, dq, 
 
 def vfm_xattn_fwd(q, k, v, cu_seqlens_q, cu_seqlens_kv, scale: float, out=None, lse=None, stream=None) -> Tuple:
     """Cross-attention: out[total_q, heads, head_dim] (bf16), lse[heads, total_q] (fp32)."""
-    import torch
-    lib = load_library()
+    lib = _lib or load_library()
     cq, ck = _host_i32(cu_seqlens_q), _host_i32(cu_seqlens_kv)
     if cq.size != ck.size:
         raise ValueError("cu_seqlens_q and cu_seqlens_kv must have the same length")
     total_q, heads, hd = q.shape
     if out is None:
-        out = torch.empty_like(q)
+        out = _torch.empty_like(q)
     if lse is None:
-        lse = torch.empty((heads, total_q), dtype=torch.float32, device=q.device)
-    _check(lib.vfm_xattn_fwd(_dev(q, "q"), _dev(k, "k"), _dev(v, "v"), _i32_ptr(cq), _i32_ptr(ck), int(cq.size - 1),
+        lse = _torch.empty((heads, total_q), dtype=_torch.float32, device=q.device)
+    _check(lib.vfm_xattn_fwd(_dev(q, "q"), _dev(k, "k"), _dev(v, "v"), _i32_ptr(cq), _i32_ptr(ck), cq.size - 1,
                              int(total_q), int(k.shape[0]), int(heads), int(hd), float(scale), _dev(out, "out"),
                              _dev(lse, "lse"), _dtype_code(q), _stream_ptr(stream)))
     return out, lse
@@ -311,20 +320,19 @@ def vfm_xattn_bwd_workspace_size(total_q: int, total_kv: int, n_heads: int, head
 def vfm_xattn_bwd(q, k, v, out, lse, dout, cu_seqlens_q, cu_seqlens_kv, scale: float, dq=None, dk=None,
                   dv=None, workspace=None, stream=None) -> Tuple:
     """Cross-attention gradients: dq (shape of q), dk, dv (shape of k)."""
-    import torch
-    lib = load_library()
+    lib = _lib or load_library()
     cq, ck = _host_i32(cu_seqlens_q), _host_i32(cu_seqlens_kv)
     if cq.size != ck.size:
         raise ValueError("cu_seqlens_q and cu_seqlens_kv must have the same length")
     total_q, heads, hd = q.shape
-    dq = torch.empty_like(q) if dq is None else dq
-    dk = torch.empty_like(k) if dk is None else dk
-    dv = torch.empty_like(v) if dv is None else dv
-    need = vfm_xattn_bwd_workspace_size(total_q, int(k.shape[0]), heads, hd)
+    dq = _torch.empty_like(q) if dq is None else dq
+    dk = _torch.empty_like(k) if dk is None else dk
+    dv = _torch.empty_like(v) if dv is None else dv
     if workspace is None:
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
+        need = vfm_xattn_bwd_workspace_size(total_q, int(k.shape[0]), heads, hd)
+        workspace = _torch.empty(max(need, 256), dtype=_torch.uint8, device=q.device)
     _check(lib.vfm_xattn_bwd(_dev(q, "q"), _dev(k, "k"), _dev(v, "v"), _dev(out, "out"), _dev(lse, "lse"),
-                             _dev(dout, "dout"), _i32_ptr(cq), _i32_ptr(ck), int(cq.size - 1), int(total_q),
+                             _dev(dout, "dout"), _i32_ptr(cq), _i32_ptr(ck), cq.size - 1, int(total_q),
                              int(k.shape[0]), int(heads), int(hd), float(scale), _dev(dq, "dq"), _dev(dk, "dk"),
                              _dev(dv, "dv"), _dev(workspace, "workspace"),
                              int(workspace.numel() * workspace.element_size()), _dtype_code(q),
@@ -334,12 +342,11 @@ def vfm_xattn_bwd(q, k, v, out, lse, dout, cu_seqlens_q, cu_seqlens_kv, scale: f
 
 def vfm_tattn_fwd(q, k, v, thw, cu_seqlens, scale: float, out=None, stream=None):
     """Temporal attention (one sequence per pixel across a clip's frames): out, shape of q."""
-    import torch
-    lib = load_library()
+    lib = _lib or load_library()
     cu = _host_i32(cu_seqlens)
     g = _host_i32(thw).reshape(-1)
     total, heads, hd = q.shape
-    out = torch.empty_like(q) if out is None else out
+    out = _torch.empty_like(q) if out is None else out
     _check(lib.vfm_tattn_fwd(_dev(q, "q"), _dev(k, "k"), _dev(v, "v"), _i32_ptr(g), _i32_ptr(cu), int(cu.size - 1),
                              int(total), int(heads), int(hd), float(scale), _dev(out, "out"), _dtype_code(q),
                              _stream_ptr(stream)))
@@ -348,23 +355,22 @@ def vfm_tattn_fwd(q, k, v, thw, cu_seqlens, scale: float, out=None, stream=None)
 
 def vfm_tattn_bwd(q, k, v, dout, thw, cu_seqlens, scale: float, dq=None, dk=None, dv=None, stream=None) -> Tuple:
     """Temporal attention gradients dq, dk, dv (shape of q)."""
-    import torch
-    lib = load_library()
+    lib = _lib or load_library()
     cu = _host_i32(cu_seqlens)
     g = _host_i32(thw).reshape(-1)
     total, heads, hd = q.shape
-    dq = torch.empty_like(q) if dq is None else dq
-    dk = torch.empty_like(k) if dk is None else dk
-    dv = torch.empty_like(v) if dv is None else dv
+    dq = _torch.empty_like(q) if dq is None else dq
+    dk = _torch.empty_like(k) if dk is None else dk
+    dv = _torch.empty_like(v) if dv is None else dv
     _check(lib.vfm_tattn_bwd(_dev(q, "q"), _dev(k, "k"), _dev(v, "v"), _dev(dout, "dout"), _i32_ptr(g), _i32_ptr(cu),
-                             int(cu.size - 1), int(total), int(heads), int(hd), float(scale), _dev(dq, "dq"),
+                             cu.size - 1, total, heads, hd, float(scale), _dev(dq, "dq"),
                              _dev(dk, "dk"), _dev(dv, "dv"), _dtype_code(q), _stream_ptr(stream)))
     return dq, dk, dv
 
 
 def vfm_fp8_pack_sizes(cu_seqlens, n_heads: int, head_dim: int) -> Tuple[int, int, int, int]:
     """Bytes of the packed q8, k8, vT8 and scales buffers for these clips."""
-    lib = load_library()
+    lib = _lib or load_library()
     cu = _host_i32(cu_seqlens)
     a, b, c, d = ctypes.c_size_t(), ctypes.c_size_t(), ctypes.c_size_t(), ctypes.c_size_t()
     _check(lib.vfm_fp8_pack_sizes(_i32_ptr(cu), int(cu.size - 1), int(cu[-1]), int(n_heads), int(head_dim),
@@ -376,15 +382,14 @@ def vfm_fp8_pack(q, k, v, cu_seqlens, scale: float, q8=None, k8=None, vT8=None, 
     """Quantise bf16 q, k, v to E4M3 tiles with power-of-two scales, in the packed layout
     vfm_attn_fwd_fp8 reads (uint8 device buffers q8, k8, vT8 and the scales buffer).  q also
     carries scale * log2(e) (scale = softmax scale)."""
-    import torch
-    lib = load_library()
+    lib = _lib or load_library()
     cu = _host_i32(cu_seqlens)
     total, heads, hd = q.shape
     nq, nk, nv, ns = vfm_fp8_pack_sizes(cu, heads, hd)
-    q8 = torch.empty(max(nq, 16), dtype=torch.uint8, device=q.device) if q8 is None else q8
-    k8 = torch.empty(max(nk, 16), dtype=torch.uint8, device=q.device) if k8 is None else k8
-    vT8 = torch.empty(max(nv, 16), dtype=torch.uint8, device=q.device) if vT8 is None else vT8
-    scales = torch.empty(max(ns, 16), dtype=torch.uint8, device=q.device) if scales is None else scales
+    q8 = _torch.empty(max(nq, 16), dtype=_torch.uint8, device=q.device) if q8 is None else q8
+    k8 = _torch.empty(max(nk, 16), dtype=_torch.uint8, device=q.device) if k8 is None else k8
+    vT8 = _torch.empty(max(nv, 16), dtype=_torch.uint8, device=q.device) if vT8 is None else vT8
+    scales = _torch.empty(max(ns, 16), dtype=_torch.uint8, device=q.device) if scales is None else scales
     _check(lib.vfm_fp8_pack(_dev(q, "q"), _dev(k, "k"), _dev(v, "v"), _i32_ptr(cu), int(cu.size - 1), int(total),
                             int(heads), int(hd), float(scale), _dev(q8, "q8"), _dev(k8, "k8"), _dev(vT8, "vT8"),
                             _dev(scales, "scales"), _dtype_code(q), _stream_ptr(stream)))
@@ -394,14 +399,13 @@ def vfm_fp8_pack(q, k, v, cu_seqlens, scale: float, q8=None, k8=None, vT8=None, 
 def vfm_attn_fwd_fp8(q8, k8, vT8, scales, cu_seqlens, n_heads: int, head_dim: int, out=None, lse=None,
                      stream=None) -> Tuple:
     """FP8 attention forward on packed operands: out (bf16 [total, heads, head_dim]) and lse (fp32)."""
-    import torch
-    lib = load_library()
+    lib = _lib or load_library()
     cu = _host_i32(cu_seqlens)
     total = int(cu[-1])
     if out is None:
-        out = torch.empty((total, n_heads, head_dim), dtype=torch.bfloat16, device=q8.device)
+        out = _torch.empty((total, n_heads, head_dim), dtype=_torch.bfloat16, device=q8.device)
     if lse is None:
-        lse = torch.empty((n_heads, total), dtype=torch.float32, device=q8.device)
+        lse = _torch.empty((n_heads, total), dtype=_torch.float32, device=q8.device)
     _check(lib.vfm_attn_fwd_fp8(_dev(q8, "q8"), _dev(k8, "k8"), _dev(vT8, "vT8"), _dev(scales, "scales"), _i32_ptr(cu),
                                 int(cu.size - 1), total, int(n_heads), int(head_dim), _dev(out, "out"),
                                 _dev(lse, "lse"), _stream_ptr(stream)))

@@ -1686,8 +1686,7 @@ static hipError_t launch_bwd_fused(const __bf16* q, const __bf16* k, const __bf1
   constexpr int lds = FusedCfg<D, NW>::kLdsBytes;
   static_assert(lds <= 160 * 1024, "LDS of one CU");
   auto kern = attn_bwd_fused_kernel<D, NW>;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  hipError_t e = allow_lds(kern, lds);
   if (e != hipSuccess) return e;
   return launch(kern, dim3(dealt_grid(segs.n * n_heads, FusedCfg<D, NW>::kGroup)), dim3(NW * 64), lds, stream, q, k, v,
                 out, lse, dout, dq, dk, dv, segs, total, n_heads, scale, scale * kLog2eB);
@@ -1766,8 +1765,7 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
       if (n == 0) return hipSuccess;
       const UnitMap uq = make_unit_map(n, n_heads, unequal_units(segs));
       auto kern = attn_bwd_dq2_kernel<D, Segs, STATS>;
-      hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::kLdsBytes);
+      hipError_t err = allow_lds(kern, Cfg::kLdsBytes);
       if (err != hipSuccess) return err;
       return launch(kern, dim3(uq.chunk * kNumXcd), dim3(kDq2Waves * 64), Cfg::kLdsBytes, stream, qb, kb, vb, dob,
                     (const __bf16*)out, lse, lse2, delta, sentinel, (__bf16*)dq, segs, uq, tq, total, n_heads, scale,
@@ -1781,8 +1779,7 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
       if (n == 0) return hipSuccess;
       const UnitMap uq = make_unit_map(n, n_heads, unequal_units(segs));
       auto kern = attn_bwd_dq_kernel<D, NI, W, Segs>;
-      hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::kLdsBytes);
+      hipError_t err = allow_lds(kern, Cfg::kLdsBytes);
       if (err != hipSuccess) return err;
       return launch(kern, dim3(uq.chunk * kNumXcd), dim3(W * 64), Cfg::kLdsBytes, stream, qb, kb, vb, dob, lse2,
                     delta, (__bf16*)dq, segs, uq, tq, total, n_heads, scale, scale * kLog2eB);
@@ -1806,7 +1803,7 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
         um = make_unit_map(n_both, n_heads);
         constexpr int lds = Cfg::kLdsBytes > Dq2Cfg<D>::kLdsBytes ? Cfg::kLdsBytes : Dq2Cfg<D>::kLdsBytes;
         auto kern = attn_bwd_both_kernel<D, Segs>;
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        e = allow_lds(kern, lds);
         if (e != hipSuccess) return e;
         return launch(kern, dim3(um.chunk * kNumXcd), dim3(kBwdWaves * 64), lds, stream, qb, kb, vb, dob, lse2,
                       delta, sentinel, (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, segs, um, tb, total, n_heads, scale,
@@ -1825,8 +1822,7 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
       if (e != hipSuccess) return e;
       um = make_unit_map(tiles * q_split, n_heads, unequal_units(segs));
       auto kern = attn_bwd_dkdv_kernel<D, Segs, true>;
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::kLdsBytes);
+      e = allow_lds(kern, Cfg::kLdsBytes);
       if (e != hipSuccess) return e;
       e = launch(kern, dim3(um.chunk * kNumXcd), dim3(kBwdWaves * 64), Cfg::kLdsBytes, stream, qb, kb, vb, dob,
                  lse2, delta, sentinel, (__bf16*)dk, (__bf16*)dv, segs, um, ti, total, n_heads, scale,
@@ -1837,8 +1833,7 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
       if (e != hipSuccess) return e;
     } else {
       auto kern = attn_bwd_dkdv_kernel<D, Segs, false>;
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::kLdsBytes);
+      e = allow_lds(kern, Cfg::kLdsBytes);
       if (e != hipSuccess) return e;
       e = launch(kern, dim3(um.chunk * kNumXcd), dim3(kBwdWaves * 64), Cfg::kLdsBytes, stream, qb, kb, vb, dob,
                  lse2, delta, sentinel, (__bf16*)dk, (__bf16*)dv, segs, um, ti, total, n_heads, scale,

@@ -506,8 +506,7 @@ static hipError_t fwd_fp8_d(const void* q8, const void* k8, const void* vT8, con
   UnitMap um = make_unit_map(tiles, n_heads);
   constexpr int lds = kF8Ring * 2 * kF8Unit * D + kF8Ring * 16;
   auto kern = attn_fwd_fp8_kernel<D>;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  hipError_t e = allow_lds(kern, lds);
   if (e != hipSuccess) return e;
   const unsigned char* q_exp = static_cast<const unsigned char*>(scales);
   const uint32_t* us = reinterpret_cast<const uint32_t*>(q_exp + unit_scale_offset(total, n_heads));

@@ -380,8 +380,7 @@ static hipError_t launch_fwd_cfg(const void* q, const void* k, const void* v, co
   const UnitMap um = make_unit_map(tiles, n_heads, unequal_units(segs));
   const int grid = um.chunk * kNumXcd;
   auto kern = attn_fwd_kernel<D, W, Segs>;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::kLdsBytes);
+  hipError_t e = allow_lds(kern, Cfg::kLdsBytes);
   if (e != hipSuccess) return e;
   return launch(kern, dim3(grid), dim3(W * 64), Cfg::kLdsBytes, stream, (const __bf16*)q, (const __bf16*)k,
                 (const __bf16*)v, (__bf16*)out, lse, segs, um, ti, total, n_heads, scale * kLog2e);

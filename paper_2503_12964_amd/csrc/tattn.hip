@@ -679,14 +679,14 @@ static hipError_t launch_blocks(const void* q, const void* k, const void* v, con
   if (!dout) {
     constexpr int lds = 3 * NB * TB;
     auto kern = tattnB_fwd_kernel<D, NB>;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    hipError_t e = allow_lds(kern, lds);
     if (e != hipSuccess) return e;
     return launch(kern, grid, block, lds, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (__bf16*)o0,
                   tab, n_heads, scale_log2);
   }
   constexpr int lds = 4 * NB * TB + 2 * NB * kT2Rows * 4;
   auto kern = tattnB_bwd_kernel<D, NB>;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  hipError_t e = allow_lds(kern, lds);
   if (e != hipSuccess) return e;
   return launch(kern, grid, block, lds, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v,
                 (const __bf16*)dout, (__bf16*)o0, (__bf16*)o1, (__bf16*)o2, tab, n_heads, scale, scale_log2);
@@ -1056,23 +1056,23 @@ static hipError_t launch_long(const void* q, const void* k, const void* v, const
   hipError_t e;
   if (!dout) {
     auto kern = tattnL_fwd_kernel<D, false>;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    e = allow_lds(kern, lds);
     if (e != hipSuccess) return e;
     return launch(kern, grid, block, lds, stream, qb, kb, vb, dob, (__bf16*)o0, lt, n_heads, scale_log2);
   }
   auto stats = tattnL_fwd_kernel<D, true>;
-  e = hipFuncSetAttribute(reinterpret_cast<const void*>(stats), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  e = allow_lds(stats, lds);
   if (e != hipSuccess) return e;
   e = launch(stats, grid, block, lds, stream, qb, kb, vb, dob, (__bf16*)o0, lt, n_heads, scale_log2);   // o0 = dq
   if (e != hipSuccess) return e;
   auto dkdv = tattnL_dkdv_kernel<D>;
-  e = hipFuncSetAttribute(reinterpret_cast<const void*>(dkdv), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  e = allow_lds(dkdv, lds);
   if (e != hipSuccess) return e;
   e = launch(dkdv, grid, block, lds, stream, qb, kb, vb, dob, (__bf16*)o0, (__bf16*)o1, (__bf16*)o2, lt, n_heads, scale,
              scale_log2);
   if (e != hipSuccess) return e;
   auto dqk = tattnL_dq_kernel<D>;
-  e = hipFuncSetAttribute(reinterpret_cast<const void*>(dqk), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  e = allow_lds(dqk, lds);
   if (e != hipSuccess) return e;
   return launch(dqk, grid, block, lds, stream, qb, kb, vb, dob, (__bf16*)o0, lt, n_heads, scale, scale_log2);
 }
@@ -1087,15 +1087,13 @@ static hipError_t launch_waves(const void* q, const void* k, const void* v, cons
   const int lds = kTWaves * (dout ? 4 : 3) * TCfg<D>::kTileBytes;
   if (!dout) {
     auto kern = tattn_fwd_kernel<D>;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    hipError_t e = allow_lds(kern, lds);
     if (e != hipSuccess) return e;
     return launch(kern, grid, block, lds, stream, (const __bf16*)q, (const __bf16*)k,
                   (const __bf16*)v, (__bf16*)o0, tab, n_heads, scale * kLog2eT);
   }
   auto kern = tattn_bwd_kernel<D>;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  hipError_t e = allow_lds(kern, lds);
   if (e != hipSuccess) return e;
   return launch(kern, grid, block, lds, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v,
                 (const __bf16*)dout, (__bf16*)o0, (__bf16*)o1, (__bf16*)o2, tab, n_heads, scale, scale * kLog2eT);
