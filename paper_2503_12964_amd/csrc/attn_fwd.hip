@@ -38,7 +38,10 @@ template <int D, int W>
 struct FwdCfg {
   static constexpr int kRows = W * 32;                              // query rows per workgroup
   static constexpr int kUnitBytes = kFwdU * D * 2;                  // one K or V unit
-  static constexpr int kLdsBytes = 2 * kFwdRing * kUnitBytes;       // K ring + V ring
+  // The workgroup's Q rows on their way into registers: over the V ring's last two slots, which fill after the prologue
+  static constexpr int kQBase = (2 * kFwdRing - 2) * kUnitBytes;
+  static constexpr int kLdsBytes = kQBase + kRows * D * 2;          // K ring, V ring, the rest of the Q rows
+  static_assert(kRows * D * 2 >= 2 * kUnitBytes && kLdsBytes <= 160 * 1024, "rings, LDS of one CU");
   static constexpr int kChunksPerRow = D / 8;
   static constexpr int kLoadsPerWave = kFwdU * kChunksPerRow / (W * 64);  // per unit, per tensor
 };
@@ -47,7 +50,7 @@ struct FwdCfg {
 constexpr int kSgValu = 0x002, kSgMfma = 0x008, kSgDsRead = 0x100;
 
 template <int D, int W, class Segs>
-__global__ __launch_bounds__(W * 64, 2)
+__global__ __launch_bounds__(W * 64, D == 64 ? 3 : 2)
 void attn_fwd_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
                      const __bf16* __restrict__ v, __bf16* __restrict__ out,
                      float* __restrict__ lse, const Segs segs, const UnitMap um, const TileIndex ti,
@@ -82,15 +85,7 @@ void attn_fwd_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   const __bf16* kbase = k + (size_t)head * D;
   const __bf16* vbase = v + (size_t)head * D;
 
-  // ---- Q operands (B operand of S^T): lane holds row i = c, columns ks*16 + 8g..+7
-  bf16x8 qreg[KS];
   const int qrow = q0 + wave * 32 + c;
-  {
-    const int r = min(qrow, q_b - 1);
-    const __bf16* qp = q + (size_t)r * row_stride + (size_t)head * D + 8 * g;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qreg[ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
-  }
 
   // ---- K/V staging with direct global->LDS loads.  One wave instruction fills 64
   // consecutive 16-byte chunks of a unit; lane L of instruction (x, wave) owns chunk
@@ -185,12 +180,30 @@ void attn_fwd_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
     return;
   }
 
-  // ---- prologue: K units 0..3 and V units 0..1 requested; S(0); operands of K(1)
+  // ---- prologue: Q rows, K units 0..3 and V units 0..1 requested; Q operands (B operand of S^T: lane holds row
+  // i = c, columns ks*16 + 8g..+7); S(0); operands of K(1).  Q comes through LDS in whole rows like the units;
+  // straight into registers it was 32 bytes of each of 32 rows per instruction (56,320 queries x 512 keys x 32 heads
+  // 528 -> 520 us, 288 clips of 256 tokens x 32 537 -> 529, 40 of 700 x 16 197 -> 194; level from 3,520 keys on)
+  const uint32_t q_lds = lds_addr_of(smem) + Cfg::kQBase + wave * (32 * RB);   // this wavefront's 32 rows
+  {
+    const __bf16* qbase = q + (size_t)head * D;
+    const uint32_t q_s = __builtin_amdgcn_readfirstlane(q_lds);
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) settle(qreg[ks]);
+    for (int x = 0; x < 32 * RB / 1024; ++x) {
+      const int p = x * 64 + lane, r = p / Cfg::kChunksPerRow;
+      lds_dma16(qbase, (uint32_t)min(q0 + wave * 32 + r, q_b - 1) * row_bytes +
+                           (uint32_t)(((p % Cfg::kChunksPerRow) ^ swz<D>(r)) * 16), q_s + x * 1024);
+    }
+  }
   issue_k(0); issue_k(1); issue_k(2); issue_k(3);
   issue_v(0); issue_v(1);
   wait_vmcnt<0>();
+  bf16x8 qreg[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    qreg[ks] = lds_read_b128_at(q_lds + (kbase_off ^ (ks << 5)));
+    settle(qreg[ks]);
+  }
   __syncthreads();
 
   bf16x8 ka[KS];
