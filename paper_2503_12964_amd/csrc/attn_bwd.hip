@@ -170,7 +170,12 @@ struct BwdCfg {
   static constexpr int kStatBytes = 4 * kBwdBQ * 4;                      // lse2, Delta (+ spare) of one stage
   // tiles first (two stages span exactly 64 KB at head_dim 128: immediate LDS offsets), statistics behind them
   static constexpr int kStatBase = kBwdRing * kStageBytes;
-  static constexpr int kLdsBytes = kStatBase + kBwdRing * kStatBytes;
+  // the workgroup's K rows on their way into registers: over the ring's last stage, which fills after the prologue;
+  // V rows: behind the statistics
+  static constexpr int kOwnK = 2 * kStageBytes;
+  static constexpr int kOwnV = kStatBase + kBwdRing * kStatBytes;
+  static constexpr int kLdsBytes = kOwnV + kBwdBC * D * 2;
+  static_assert(kBwdBC * D * 2 <= kStageBytes && kOwnV % 1024 == 0, "K rows fit a stage");
   static constexpr int kChunksPerRow = D / 8;
   static constexpr int kLoadsPerWave = kBwdBQ * kChunksPerRow / (kBwdWaves * 64);  // per tile, per tensor
 };
@@ -268,15 +273,6 @@ void bwd_dkdv_unit(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
     }
     return;
   }
-  bf16x8 kreg[KS], vreg[KS];
-  {
-    const size_t off = (size_t)min(jrow, kv_b - 1) * row_stride + head_off + 8 * g;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      kreg[ks] = *reinterpret_cast<const bf16x8*>(k + off + ks * 16);
-      vreg[ks] = *reinterpret_cast<const bf16x8*>(v + off + ks * 16);
-    }
-  }
 
   // ---- tile requests (direct global->LDS).  Lane L of wave instruction (x, wave) owns
   // LDS chunk P = (x*waves + wave)*64 + L of the tile (row P / chunks_per_row, physical
@@ -370,14 +366,34 @@ void bwd_dkdv_unit(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
     }
   };
 
-  // ---- prologue: tiles 0 and 1 requested; S(0), dP(0); row operands of block 1
+  // ---- prologue: K, V rows, tiles 0 and 1 requested; S(0), dP(0); row operands of block 1.  K and V come through LDS
+  // in whole rows like the tiles, not as operands (32 bytes of each of 32 rows per
+  // instruction): whole backward call 1.5% less for 40 clips of 700 tokens x 16 heads, 1% for 100 of 512, level from
+  // 4,096 tokens on
+  const uint32_t own = smem_addr + wave * (32 * RB);   // this wavefront's rows, from kOwnK and kOwnV on
+  {
+    const __bf16* kbase = k + head_off;
+    const __bf16* vbase = v + head_off;
+    const uint32_t own_s = __builtin_amdgcn_readfirstlane(own);
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    if constexpr (kAsm) { to_agpr(kreg[ks]); to_agpr(vreg[ks]); }
-    else { settle(kreg[ks]); settle(vreg[ks]); }
+    for (int x = 0; x < 32 * RB / 1024; ++x) {
+      const int p = x * 64 + lane, r = p / Cfg::kChunksPerRow;
+      const uint32_t off = (uint32_t)min(j0 + wave * 32 + r, kv_b - 1) * row_bytes +
+                           (uint32_t)(((p % Cfg::kChunksPerRow) ^ swz<D>(r)) * 16);
+      lds_dma16(kbase, off, own_s + Cfg::kOwnK + x * 1024);
+      lds_dma16(vbase, off, own_s + Cfg::kOwnV + x * 1024);
+    }
   }
   issue_tile(0); issue_tile(1);
   wait_vmcnt<0>();
+  bf16x8 kreg[KS], vreg[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    kreg[ks] = lds_read_b128_at(own + Cfg::kOwnK + (rbase ^ (ks << 5)));
+    vreg[ks] = lds_read_b128_at(own + Cfg::kOwnV + (rbase ^ (ks << 5)));
+    if constexpr (kAsm) { to_agpr(kreg[ks]); to_agpr(vreg[ks]); }
+    else { settle(kreg[ks]); settle(vreg[ks]); }
+  }
   __syncthreads();
 
   // A wavefront whose 32 key rows all lie past the end of the sequence (ragged last tile) has
