@@ -42,7 +42,9 @@ namespace {
 constexpr int kF8Unit = 64;
 constexpr int kF8Waves = 8;
 constexpr int kF8Rows = kF8Waves * 32;   // query rows per workgroup
-constexpr int kF8Ring = 4;
+// Units from one workgroup barrier to the next, and LDS slots of (K unit, V^T unit) (see the unit loop)
+constexpr int f8_meet(int head_dim) { return head_dim == 64 ? 2 : 1; }
+constexpr int f8_ring(int head_dim) { return 4 * f8_meet(head_dim); }
 constexpr float kF8Ln2 = 0.6931471805599453f;
 constexpr float kF8PShift = 6.0f;        // P is stored as 2^6 P
 constexpr float kF8SafeSum = 448.0f;     // largest finite E4M3: bounds every scaled P of the unit
@@ -242,6 +244,7 @@ void attn_fwd_fp8_kernel(const unsigned char* __restrict__ q8, const unsigned ch
   constexpr int kLoadWaves = UB / 1024; // waves that take part in staging a unit (1 KB each)
 
   extern __shared__ __attribute__((aligned(16))) char smem[];   // ring of (K unit, V^T unit), then the units' scale words
+  constexpr int kMeet = f8_meet(D), kF8Ring = f8_ring(D);
   constexpr int kScaleBase = kF8Ring * 2 * UB;                  // one 16-byte cell per ring slot
 
   int head, tile;
@@ -401,24 +404,32 @@ void attn_fwd_fp8_kernel(const unsigned char* __restrict__ q8, const unsigned ch
     for (int db = 0; db < DB; ++db) oacc[db] = mfma_f8<1, 0>(va[db], pb, oacc[db], us, kScaleOne);
   };
 
-  // ---- the unit loop.  A workgroup barrier per unit keeps the two wavefronts of a SIMD in step,
+  // ---- the unit loop.  Workgroup barriers keep the two wavefronts of a SIMD in step,
   // so if both ran the stages in the same order they would want the matrix pipe at the same
   // time and the VALU at the same time (measured: the two add up).  Instead waves 0-3
   // ("leaders") and 4-7 ("followers", the other wave of each SIMD) run them in opposite phase
   // between two barriers:
   //     leader  :  PV(u-1), S(u)   [matrix pipe]   then   softmax(u)       [VALU]
   //     follower:  softmax(u-1)    [VALU]          then   PV(u-1), S(u)    [matrix pipe]
-  // Both read K(u) and V(u-1) in interval u; the loads issued there bring unit u+2 into the
-  // slot of unit u-2 (ring of four).  SLOT = u % 4 is a compile-time constant so that every
-  // LDS offset is an immediate.
-  static_assert(kF8Ring == 4, "the unit loop is unrolled over the ring");
+  // Both read K(u) and V(u-1) in interval u.  With a barrier before every unit (head_dim 128) the loads issued there
+  // bring unit u+2 into the slot of unit u-2 (ring of four).  With one before every second unit (head_dim 64,
+  // whose units are half as long: 20,000 tokens x 8 heads 701 -> 618 us, 3,000 x 16 49 -> 45; at 128, in
+  // 128 KB of slots, 56,320 x 32 23.1 -> 24.7 ms) they bring units u+2 and u+3, and unit u-1 is still read: ring of eight.
+  // SLOT = u % kF8Ring is a compile-time constant so that every LDS offset is an immediate.
   auto interval = [&](auto slot_c, auto lead_c, auto first_c, int u) {
     constexpr int SLOT = decltype(slot_c)::value;
     constexpr bool LEAD = decltype(lead_c)::value != 0;
     constexpr bool FIRST = decltype(first_c)::value != 0;
-    wait_vmcnt<2>();          // unit u has landed (unit u+1 may still be in flight) ...
-    __syncthreads();          // ... for every wave, and every wave is done with unit u-2
-    issue_unit(u + 2, (SLOT + 2) % kF8Ring);
+    if constexpr (kMeet == 1) {
+      wait_vmcnt<2>();          // unit u has landed (unit u+1 may still be in flight) ...
+      __syncthreads();          // ... for every wave, and every wave is done with unit u-2
+      issue_unit(u + 2, (SLOT + 2) % kF8Ring);
+    } else if constexpr (SLOT % 2 == 0) {
+      wait_vmcnt<0>();          // units u and u+1 have landed ...
+      __syncthreads();          // ... for every wave, and every wave is done with units u-2 and earlier
+      issue_unit(u + 2, (SLOT + 2) % kF8Ring);
+      issue_unit(u + 3, (SLOT + 3) % kF8Ring);
+    }
     const char* kt = smem + SLOT * 2 * UB;
     const char* vt_prev = smem + ((SLOT + kF8Ring - 1) % kF8Ring) * 2 * UB + UB;
     const int us = *reinterpret_cast<const int*>(smem + kScaleBase + SLOT * 16);   // unit u's scale word
@@ -441,11 +452,17 @@ void attn_fwd_fp8_kernel(const unsigned char* __restrict__ q8, const unsigned ch
   };
   auto run = [&](auto lead_c) {
     interval(IntC<0>{}, lead_c, IntC<1>{}, 0);
-    for (int u = 1; u < n_u; u += 4) {
+    for (int u = 1; u < n_u; u += kF8Ring) {
       interval(IntC<1>{}, lead_c, IntC<0>{}, u);
       if (u + 1 < n_u) interval(IntC<2>{}, lead_c, IntC<0>{}, u + 1);
       if (u + 2 < n_u) interval(IntC<3>{}, lead_c, IntC<0>{}, u + 2);
-      if (u + 3 < n_u) interval(IntC<0>{}, lead_c, IntC<0>{}, u + 3);
+      if constexpr (kF8Ring == 8) {
+        if (u + 3 < n_u) interval(IntC<4>{}, lead_c, IntC<0>{}, u + 3);
+        if (u + 4 < n_u) interval(IntC<5>{}, lead_c, IntC<0>{}, u + 4);
+        if (u + 5 < n_u) interval(IntC<6>{}, lead_c, IntC<0>{}, u + 5);
+        if (u + 6 < n_u) interval(IntC<7>{}, lead_c, IntC<0>{}, u + 6);
+      }
+      if (u + kF8Ring - 1 < n_u) interval(IntC<0>{}, lead_c, IntC<0>{}, u + kF8Ring - 1);
     }
     // drain: the last unit's remaining stages (its V unit is still in its slot)
     if constexpr (decltype(lead_c)::value == 0) softmax(n_u - 1);
@@ -504,7 +521,7 @@ static hipError_t fwd_fp8_d(const void* q8, const void* k8, const void* vT8, con
   const int tiles = count_tiles(ti);
   if (tiles == 0) return hipSuccess;
   UnitMap um = make_unit_map(tiles, n_heads);
-  constexpr int lds = kF8Ring * 2 * kF8Unit * D + kF8Ring * 16;
+  constexpr int lds = f8_ring(D) * 2 * kF8Unit * D + f8_ring(D) * 16;
   auto kern = attn_fwd_fp8_kernel<D>;
   hipError_t e = allow_lds(kern, lds);
   if (e != hipSuccess) return e;

@@ -164,6 +164,14 @@ def test_pack_is_bit_exact_and_attention_matches_oracle(name):
     assert U.rel_rms(o, o_true) <= 2 * TOL_FP8_OUT_RELRMS
 
 
+def test_every_end_of_the_unit_loop_head_dim_64():
+    # clips of 1 to 10 and of 17 and 18 key units, whole and partial last units: the loop over units is unrolled eight
+    # times after its first unit and its waves meet before every second one
+    lens = [64 * n - (13 * n % 64 if n % 3 else 0) for n in (*range(1, 11), 17, 18)]
+    wl = _custom("units64", [(1, 1, n) for n in lens], 2, 64, (16, 24, 24), 22)
+    _check_pack_and_attention(_binding(), wl, W.make_inputs(wl, tensors=("q", "k", "v")))
+
+
 def test_tiles_of_very_different_magnitude_keep_their_precision():
     # Clips whose k is 2^-5 to 2^5 and whose v is 2^-12 to 2^10 times unit variance (q carries the
     # inverse of the k factor, so the scores stay ordinary).  With a scale per tile every tile uses
