@@ -626,11 +626,14 @@ struct DqCfg {
 // over more CUs.  Against one workgroup of eight wavefronts per CU (whole backward call): 64 clips of 300 tokens x 16 heads
 // 176 -> 145 us, 2 x 2,048 tokens x 2 heads 74 -> 64, 8,192 x 12 692 -> 655, 32,768 x 32 26.9 -> 26.2 ms, 2 x 4,096 x
 // 16 440 -> 447; each K/V tile is staged twice as often.
-template <int D, int NI, int W, class Segs>
+// STATS: as in bwd_dq2_unit (the pass runs first and leaves Delta, lse in log2 units and the sentinels for the
+// dK/dV pass; figures at bwd_order).
+template <int D, int NI, int W, class Segs, bool STATS>
 __global__ __launch_bounds__(W * 64, NI == 1 ? 3 : 1)
 void attn_bwd_dq_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
                         const __bf16* __restrict__ v, const __bf16* __restrict__ dout,
-                        const float* __restrict__ lse2g, const float* __restrict__ delta,
+                        const __bf16* __restrict__ out, const float* __restrict__ lse,
+                        float* __restrict__ lse2g, float* __restrict__ delta, float* __restrict__ sentinel,
                         __bf16* __restrict__ dq, const Segs segs, const UnitMap um, const TileIndex ti,
                         int total, int n_heads, float scale, float scale_log2) {
   using Cfg = DqCfg<D, NI, W>;
@@ -644,6 +647,10 @@ void attn_bwd_dq_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__
 
   int head, tile;
   if (!map_unit(um, blockIdx.x, head, tile)) return;
+  if (STATS && blockIdx.x == 0 && threadIdx.x == 0) {   // the dK/dV pass' statistics of rows past a clip's end
+    sentinel[0] = INFINITY;
+    sentinel[1] = 0.f;
+  }
   // query rows of the range [.., q_b); keys and values are rows [seg_a, seg_b) of k, v
   int seq, tq;
   locate_tile(ti, segs.n, tile, seq, tq);
@@ -676,8 +683,35 @@ void attn_bwd_dq_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__
       qreg[ib][ks] = *reinterpret_cast<const bf16x8*>(q + off + ks * 16);
       doreg[ib][ks] = *reinterpret_cast<const bf16x8*>(dout + off + ks * 16);
     }
-    lse2[ib] = lse2g[(size_t)head * total + r];
-    dlt[ib] = delta[(size_t)head * total + r];
+    const size_t stat = (size_t)head * total + r;
+    if constexpr (STATS) {
+      bf16x8 oreg[KS];
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) oreg[ks] = *reinterpret_cast<const bf16x8*>(out + off + ks * 16);
+      lse2[ib] = lse[stat] * kLog2eB;
+      // the order of bwd_prepare_kernel's sums (chunks of 8 columns, then pairs of chunks D/16, .., 2, 1 apart)
+      float s[KS];
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        s[ks] = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s[ks] = __builtin_fmaf((float)oreg[ks][e], (float)doreg[ib][ks][e], s[ks]);
+      }
+#pragma unroll
+      for (int o = KS / 2; o > 0; o >>= 1)
+#pragma unroll
+        for (int ks = 0; ks < o; ++ks) s[ks] += s[ks + o];
+      dlt[ib] = pair_sum(s[0]);
+      const bool few = segs.kv_len(seq) <= kShortKeys;   // (already in place)
+      if (few) dlt[ib] = delta[stat];
+      if (g == 0 && qrow[ib] < q_b) {
+        lse2g[stat] = lse2[ib];
+        if (!few) delta[stat] = dlt[ib];
+      }
+    } else {
+      lse2[ib] = lse2g[stat];
+      dlt[ib] = delta[stat];
+    }
   }
 
   // ---- K/V staging with direct global->LDS loads (same scheme as the forward kernel)
@@ -1773,8 +1807,8 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
   if (tiles == 0) return hipSuccess;
   UnitMap um = make_unit_map(tiles, n_heads, unequal_units(segs));
   auto launch_dq = [&](auto stats_c) -> hipError_t {
+    constexpr bool STATS = decltype(stats_c)::value != 0;
     if constexpr (D == 128) {
-      constexpr bool STATS = decltype(stats_c)::value != 0;
       using Cfg = Dq2Cfg<D>;
       const TileIndex tq = make_tile_index<false>(segs, Cfg::kBR);
       const int n = count_tiles(tq);
@@ -1794,11 +1828,11 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
       const int n = count_tiles(tq);
       if (n == 0) return hipSuccess;
       const UnitMap uq = make_unit_map(n, n_heads, unequal_units(segs));
-      auto kern = attn_bwd_dq_kernel<D, NI, W, Segs>;
+      auto kern = attn_bwd_dq_kernel<D, NI, W, Segs, STATS>;
       hipError_t err = allow_lds(kern, Cfg::kLdsBytes);
       if (err != hipSuccess) return err;
-      return launch(kern, dim3(uq.chunk * kNumXcd), dim3(W * 64), Cfg::kLdsBytes, stream, qb, kb, vb, dob, lse2,
-                    delta, (__bf16*)dq, segs, uq, tq, total, n_heads, scale, scale * kLog2eB);
+      return launch(kern, dim3(uq.chunk * kNumXcd), dim3(W * 64), Cfg::kLdsBytes, stream, qb, kb, vb, dob,
+                    (const __bf16*)out, lse, lse2, delta, sentinel, (__bf16*)dq, segs, uq, tq, total, n_heads, scale, scale * kLog2eB);
     }
   };
   if (dq_first) {

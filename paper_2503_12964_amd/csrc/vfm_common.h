@@ -329,17 +329,18 @@ inline bool bwd_one_pass(const SegTable& segs, int n_heads, int head_dim, int cu
 }
 
 // The passes of a run that does not take the one-pass backward.  both: dK/dV and dQ units from one grid,
-// where no sequence has more than this many rows (queries or keys).  dq_first: the dQ pass runs before
-// the dK/dV pass and forms the statistics on the way (backward call at head_dim 128, separate pass ->
-// here: 20,000 queries x 300 keys x 16 heads 413 -> 403 us, 2 x 4,096 tokens x 16 heads 785 -> 775, 12,000
-// tokens x 4 heads level).  Without dq_first the statistics come from a pass of their own, without either
-// (head_dim 64) dQ comes last.  The dK/dV workgroups of a sequence read all of its q and dout rows: where dq takes the place
+// where no sequence has more than this many rows (queries or keys), head_dim 128.  dq_first: the dQ pass runs before
+// the dK/dV pass and forms the statistics on the way (backward call, separate pass ->
+// here: head_dim 128, 20,000 queries x 300 keys x 16 heads 413 -> 403 us, 2 x 4,096 tokens x 16 heads 785 -> 775, 12,000
+// tokens x 4 heads level; head_dim 64, 300 tokens x 4 20.1 -> 18.2 us, 64 clips of 300 x 16 144 -> 138, 8,192 x
+// 12 655 -> 630).  With neither the statistics come from a pass of their own and dQ
+// comes last.  The dK/dV workgroups of a sequence read all of its q and dout rows: where dq takes the place
 // of either it has to be written after all of them are done, so neither of the first two will do.
 constexpr int kBothMaxRows = 1024;
 struct BwdOrder { bool both, dq_first; };
 inline BwdOrder bwd_order(int head_dim, int q_split, int longest, bool dq_over_input) {
-  if (head_dim != 128 || dq_over_input) return {false, false};
-  const bool both = q_split == 1 && longest <= kBothMaxRows;
+  if (dq_over_input) return {false, false};
+  const bool both = head_dim == 128 && q_split == 1 && longest <= kBothMaxRows;
   return {both, !both};
 }
 
