@@ -573,7 +573,7 @@ void bwd_dkdv_unit(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   }
 }
 
-// head_dim 64: two workgroups per CU (252 registers, 51 KB of LDS each; one set of LDS addresses, every operand in a
+// head_dim 64: two workgroups per CU (252 registers, 67 KB of LDS each; one set of LDS addresses, every operand in a
 // VGPR), so that the exponentials of one meet the products of the other.  Against one workgroup with its operands in
 // AGPRs (272 registers), whole backward call: 32,768 tokens x 32 heads 27.7 -> 26.2 ms, 64 clips of 300 x 16
 // 170 -> 145 us, 2 x 4,096 x 16 456 -> 447; calls of fewer tiles than CUs lose 2% (2 x 2,048 x 2 62 -> 64).
@@ -849,22 +849,13 @@ void attn_bwd_dq_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__
     if (t + 1 < n_tiles) tile_body(IntC<1>{}, t + 1);
   }
 
-  // ---- epilogue: dq = bf16(scale * dQ^T)
+  // ---- epilogue: dq = bf16(scale * dQ^T), whole rows per store; every wave is past the ring (the loop's last
+  // barrier), each turns its tiles through a piece of it
 #pragma unroll
   for (int ib = 0; ib < NI; ++ib) {
-    const int i = qrow[ib];
-    if (i < q_b) {
-      __bf16* op = dq + (size_t)i * row_stride + head_off + 4 * g;
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          f32x4 o;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) o[e] = dqacc[ib][db][q4 * 4 + e] * scale;
-          *reinterpret_cast<bf16x4*>(op + db * 32 + q4 * 8) = to_bf16x4(o);
-        }
-    }
+    const int row0 = q0 + (wave * NI + ib) * 32;
+    store_tile_rows<D>(smem + wave * (32 * RB), dqacc[ib], scale, dq + (size_t)row0 * row_stride + head_off, row_stride,
+                       q_b - row0);
   }
 }
 
