@@ -309,9 +309,11 @@ inline int fwd_tile_rows(const Segs& segs, int head_dim) {
 }
 
 // Whether a run of clips (longest first) takes the one-pass backward, which forms its own statistics: one
-// workgroup per (clip, head), clips of at most 256 tokens.  At head_dim 64 it is level or faster from the
-// first unit on (2 units: 64 tokens 6.7 us against 11.0, 128 tokens 10.1 against 13.9, 256 tokens 19.9 against
-// 19.4; 256 units of 256 tokens 27 against 39), at head_dim 128 up to 96 tokens too (2 units of 64 and 96
+// workgroup per (clip, head), clips of at most 256 tokens.  At head_dim 64 it is faster up to
+// 224 tokens (2 and 256 units, two passes, one pass: 64 tokens 11.5, 8.4 and 13.2, 8.7 us; 128 tokens 12.0, 9.6 and
+// 16.3, 12.6; 192 tokens 13.3, 13.8 and 23.7, 16.9) and beyond for 160 units and more (256 tokens 15.3, 18.4 at 2
+// units, 19.4, 20.5 at 128, 25.5, 22.1 at 160, 28.8, 24.2 at 256); smaller runs of 225 to 256 tokens lose 1 to 3 us to
+// it and take it all the same, one rule for every run of short clips.  At head_dim 128 up to 96 tokens too (2 units of 64 and 96
 // tokens 10.1 and 12.0 against 10.4 and 12.2; 256 units 12.6 and 16 against 22 and 28).  Beyond, its lone
 // workgroup takes longer than the two-pass kernel's, which spreads a (clip, head) over up to three, so a run
 // whose two-pass workgroups fit the chip at once stays there (two passes, one pass: 128 tokens x 64 units
