@@ -362,20 +362,23 @@ VFM_API int vfm_attn_fwd_fp8(const void* q8, const void* k8, const void* vT8, co
  * The tile scheduler, on the host (nothing is launched): which rows each
  * workgroup of a launch takes.  Section 3.1's packed clips are cut into tiles of
  * rows_per_tile rows that never straddle a clip (so blocks between different
- * clips are never enumerated), clips longest first, and the (head, tile) units
- * are dealt to the grid so that the workgroups of one XCD (workgroup index mod
- * 8) take consecutive tiles of the same head.  The attention kernels use this
- * very mapping over query rows with rows_per_tile = 256 in the dQ kernel (128 at
- * head_dim 64) and vfm_attn_fwd_tile_rows() in the forward, and over key rows
- * with 128 (dK/dV).
- * (A backward launch at head_dim 128 whose sequences all have at most 1,024
- * rows deals both kinds of tile from one grid, per (head, sequence) the key
- * tiles and then the query tiles, with the same tile heights and XCD rule.)
- * (With a number of heads that is no multiple of 8 and clips of unequal length,
- * self-attention launches take the same tiles in another order: tile by tile,
- * all heads of one tile before the next, workgroup b the b-th.)
- * (A backward run whose clips all have at most 256 tokens takes, but for small
- * runs, one workgroup per (clip, head), dealt round-robin over the XCDs.)
+ * clips are never enumerated), clips longest first.  The (head, tile) units go to
+ * the grid in one of two orders.  Contiguous: head by head, one run of units per
+ * XCD (workgroup index mod 8), so that its workgroups take consecutive tiles of
+ * the same head.  Dealt, where the number of heads is no multiple of 8 and the
+ * clips differ in length: tile by tile, all heads of one tile before the next,
+ * workgroup b the b-th unit.
+ * This is the very mapping of these bf16 self-attention launches: the forward
+ * over query rows (rows_per_tile = vfm_attn_fwd_tile_rows()), the backward's dQ
+ * pass over query rows (256; 128 at head_dim 64) and its dK/dV pass over key
+ * rows (128).  Others differ:
+ *  - cross-attention and the FP8 forward are always contiguous (the latter with
+ *    256 rows and runs of 128 clips);
+ *  - a backward launch at head_dim 128 whose sequences all have at most 1,024
+ *    rows takes both kinds of tile from one contiguous grid, per (head,
+ *    sequence) the key tiles and then the query tiles;
+ *  - a backward run whose clips all have at most 256 tokens takes, but for small
+ *    runs, one workgroup per (clip, head), dealt round-robin over the XCDs.
  * For workgroup b < *n_blocks: units[3b] = head (-1: the workgroup is grid
  * padding and exits), units[3b+1] = first packed row, units[3b+2] = rows
  * (1..rows_per_tile).  With more than VFM_MAX_SEQS clips the call is one launch

@@ -352,15 +352,15 @@ int vfm_schedule_units(const int32_t* cu_seqlens, int n_seqs, int total_tokens, 
   if (n_seqs < 0 || total_tokens < 0 || n_heads < 1 || n_heads > 65535 || rows_per_tile < 1 || capacity < 0)
     return VFM_ERR_SHAPE;
   if (int st = check_cu(cu_seqlens, n_seqs, total_tokens)) return st;
-  // exactly what the launchers and kernels do, run after run: count the tiles, build the unit
-  // map, and ask the kernels' own mapping which unit each workgroup of the grid takes
+  // what the launchers and kernels of the header's list do, run after run: count the tiles, build the
+  // unit map (contiguous or dealt), and ask the kernels' own mapping which unit each workgroup takes
   for (int pass = 0; pass < 2; ++pass) {
     int at = 0;
     for (int s0 = 0; s0 < n_seqs || s0 == 0; s0 += VFM_MAX_SEQS) {
       SegTable segs;
       build_seg_table(cu_seqlens + s0, std::min(VFM_MAX_SEQS, n_seqs - s0), &segs);
       const vfm::TileIndex ti = vfm::make_tile_index<false>(segs, rows_per_tile);
-      const vfm::UnitMap um = vfm::make_unit_map(vfm::count_tiles(ti), n_heads);
+      const vfm::UnitMap um = vfm::make_unit_map(vfm::count_tiles(ti), n_heads, vfm::unequal_units(segs));
       const int grid = um.chunk * vfm::kNumXcd;
       if (pass == 1)
         for (int b = 0; b < grid; ++b) {

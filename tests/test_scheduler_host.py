@@ -1,8 +1,8 @@
 """The tile scheduler on the host (no GPU): vfm_schedule_units runs the launchers' unit map and
 the kernels' own block -> (head, tile) -> rows mapping on the CPU.  Checked here: every (head,
 token) is handed out exactly once, no tile straddles a clip (cross-clip blocks are never
-enumerated), clips go longest first, each XCD gets one contiguous run of units, and the grid
-is padded by fewer than 8 idle workgroups."""
+enumerated), clips go longest first, the grid is padded by fewer than 8 idle workgroups, and
+each XCD gets one contiguous run of units, or, where units are dealt out, its share of every clip."""
 import numpy as np
 import pytest
 
@@ -13,10 +13,16 @@ XCDS = 8
 
 def _units_in_order(units):
     """Workgroup b belongs to XCD b % 8 and is that XCD's (b // 8)-th: list the live units in
-    the order XCD 0's run, XCD 1's run, ... (the head-major unit numbering)."""
+    the order XCD 0's run, XCD 1's run, ... (the head-major unit numbering of a contiguous map)."""
     chunk = len(units) // XCDS
     order = [units[x + XCDS * i] for x in range(XCDS) for i in range(chunk)]
     return [tuple(int(v) for v in u) for u in order]
+
+
+def _is_dealt(lens, heads):
+    """Whether a launch over clips of these lengths deals its units out."""
+    live = [n for n in lens if n > 0]
+    return heads % XCDS != 0 and len(set(live)) > 1
 
 
 def _check(cu, heads, rows, units=None):
@@ -34,7 +40,8 @@ def _check(cu, heads, rows, units=None):
     n_tiles = int(sum((n + rows - 1) // rows for n in lens))
     assert len(units) % XCDS == 0
     assert len(units) == XCDS * ((n_tiles * heads + XCDS - 1) // XCDS)
-    ordered = _units_in_order(units)
+    dealt = _is_dealt(lens, heads)
+    ordered = [tuple(int(v) for v in u) for u in units] if dealt else _units_in_order(units)
     live = [u for u in ordered if u[0] >= 0]
     assert len(live) == n_tiles * heads and len(units) - len(live) < XCDS
     # idle workgroups only at the end of the numbering (the last XCD's run is the short one)
@@ -47,9 +54,19 @@ def _check(cu, heads, rows, units=None):
         assert (first - cu[clip_of[first]]) % rows == 0, "tiles start on the clip's own tile grid"
         cover[head, first:first + n] += 1
     assert np.all(cover == 1), "every (head, token) exactly once"
-    # head-major, and within a head the clips come longest first (ties in packed order)
+    # contiguous: head-major; dealt: all heads of one tile before the next; either way the clips of a
+    # head come longest first (ties in packed order)
     heads_seen = [u[0] for u in live]
-    assert heads_seen == sorted(heads_seen)
+    if dealt:
+        assert heads_seen == list(range(heads)) * n_tiles
+        assert all(u[1:] == live[i - i % heads][1:] for i, u in enumerate(live))
+        for c in range(len(lens)):      # no XCD has more tiles of a clip than another, but for one
+            share = [0] * XCDS
+            for i, u in enumerate(live):
+                share[i % XCDS] += clip_of[u[1]] == c
+            assert max(share) - min(share) <= 1
+    else:
+        assert heads_seen == sorted(heads_seen)
     for h in range(heads):
         clips = [int(clip_of[first]) for head, first, _ in live if head == h]
         runs = [c for i, c in enumerate(clips) if i == 0 or c != clips[i - 1]]
@@ -81,6 +98,18 @@ def test_random_clip_mixes(seed):
         lens[0] = 5
         cu = np.concatenate([[0], np.cumsum(lens)])
     _check(cu, int(rng.integers(1, 7)), int(rng.choice([32, 64, 128, 256])))
+
+
+def test_unequal_clips_are_dealt_where_heads_do_not_divide_by_the_xcds():
+    # 5,000 + 1,200 + 700 + 300 tokens: cut contiguously, every second XCD would hold 35 of the longest
+    # clip's tiles of 12 heads and the others 25
+    cu = np.cumsum([0, 300, 5000, 700, 1200])
+    units = _check(cu, 12, 256)
+    assert [int(u[0]) for u in units[:24]] == list(range(12)) * 2 and int(units[0][1]) == 300
+    longest = [sum(1 for u in units[x::XCDS] if u[0] >= 0 and 300 <= u[1] < 5300) for x in range(XCDS)]
+    assert longest == [30] * XCDS
+    heads = [int(u[0]) for u in _units_in_order(_check(cu, 16, 256)) if u[0] >= 0]
+    assert heads == sorted(heads)
 
 
 def test_equal_lengths_keep_packed_order_and_empty_input_has_no_workgroups():
