@@ -365,9 +365,10 @@ VFM_API int vfm_attn_fwd_fp8(const void* q8, const void* k8, const void* vT8, co
  * clips are never enumerated), clips longest first.  The (head, tile) units go to
  * the grid in one of two orders.  Contiguous: head by head, one run of units per
  * XCD (workgroup index mod 8), so that its workgroups take consecutive tiles of
- * the same head.  Dealt, where the number of heads is no multiple of 8 and the
- * clips differ in length: tile by tile, all heads of one tile before the next,
- * workgroup b the b-th unit.
+ * the same head.  Dealt, where the number of heads is no multiple of 8, the
+ * clips differ in length and the contiguous order would leave some XCDs over 3%
+ * longer at work: tile by tile, all heads of one tile before the next, workgroup
+ * b the b-th unit.
  * This is the very mapping of these bf16 self-attention launches: the forward
  * over query rows (rows_per_tile = vfm_attn_fwd_tile_rows()), the backward's dQ
  * pass over query rows (256; 128 at head_dim 64) and its dK/dV pass over key

@@ -1796,7 +1796,6 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
     }
   }
   if (tiles == 0) return hipSuccess;
-  UnitMap um = make_unit_map(tiles, n_heads, unequal_units(segs));
   auto launch_dq = [&](auto stats_c) -> hipError_t {
     constexpr bool STATS = decltype(stats_c)::value != 0;
     if constexpr (D == 128) {
@@ -1804,7 +1803,7 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
       const TileIndex tq = make_tile_index<false>(segs, Cfg::kBR);
       const int n = count_tiles(tq);
       if (n == 0) return hipSuccess;
-      const UnitMap uq = make_unit_map(n, n_heads, unequal_units(segs));
+      const UnitMap uq = make_unit_map(segs, tq, Cfg::kBR, n_heads);
       auto kern = attn_bwd_dq2_kernel<D, Segs, STATS>;
       hipError_t err = allow_lds(kern, Cfg::kLdsBytes);
       if (err != hipSuccess) return err;
@@ -1818,7 +1817,7 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
       const TileIndex tq = make_tile_index<false>(segs, Cfg::kBR);
       const int n = count_tiles(tq);
       if (n == 0) return hipSuccess;
-      const UnitMap uq = make_unit_map(n, n_heads, unequal_units(segs));
+      const UnitMap uq = make_unit_map(segs, tq, Cfg::kBR, n_heads);
       auto kern = attn_bwd_dq_kernel<D, NI, W, Segs, STATS>;
       hipError_t err = allow_lds(kern, Cfg::kLdsBytes);
       if (err != hipSuccess) return err;
@@ -1841,7 +1840,7 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
           if (s2 < segs.n)
             n_both += (segs.kv_len(s2) + kBwdBC - 1) / kBwdBC + (segs.q_len(s2) + Dq2Cfg<D>::kBR - 1) / Dq2Cfg<D>::kBR;
         }
-        um = make_unit_map(n_both, n_heads);
+        const UnitMap um = make_unit_map(n_both, n_heads);
         constexpr int lds = Cfg::kLdsBytes > Dq2Cfg<D>::kLdsBytes ? Cfg::kLdsBytes : Dq2Cfg<D>::kLdsBytes;
         auto kern = attn_bwd_both_kernel<D, Segs>;
         e = allow_lds(kern, lds);
@@ -1861,7 +1860,7 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
       f32x4* acc_v = (f32x4*)(dkv32 + kv_elems) + lo4;
       e = launch(fill_zero_f32x4_kernel, cgrid, dim3(256), 0, stream, acc_k, acc_v, h4);
       if (e != hipSuccess) return e;
-      um = make_unit_map(tiles * q_split, n_heads, unequal_units(segs));
+      const UnitMap um = make_unit_map(tiles * q_split, n_heads);
       auto kern = attn_bwd_dkdv_kernel<D, Segs, true>;
       e = allow_lds(kern, Cfg::kLdsBytes);
       if (e != hipSuccess) return e;
@@ -1873,6 +1872,7 @@ static hipError_t launch_bwd_d(const void* q, const void* k, const void* v, cons
                  (bf16x4*)dk + lo4, (bf16x4*)dv + lo4, h4);
       if (e != hipSuccess) return e;
     } else {
+      const UnitMap um = make_unit_map(segs, ti, kBwdBC, n_heads);
       auto kern = attn_bwd_dkdv_kernel<D, Segs, false>;
       e = allow_lds(kern, Cfg::kLdsBytes);
       if (e != hipSuccess) return e;

@@ -390,7 +390,7 @@ static hipError_t launch_fwd_cfg(const void* q, const void* k, const void* v, co
   const TileIndex ti = make_tile_index<false>(segs, Cfg::kRows);
   const int tiles = count_tiles(ti);
   if (tiles == 0) return hipSuccess;
-  const UnitMap um = make_unit_map(tiles, n_heads, unequal_units(segs));
+  const UnitMap um = make_unit_map(segs, ti, Cfg::kRows, n_heads);
   const int grid = um.chunk * kNumXcd;
   auto kern = attn_fwd_kernel<D, W, Segs>;
   hipError_t e = allow_lds(kern, Cfg::kLdsBytes);

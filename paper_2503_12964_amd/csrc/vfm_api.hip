@@ -360,7 +360,7 @@ int vfm_schedule_units(const int32_t* cu_seqlens, int n_seqs, int total_tokens, 
       SegTable segs;
       build_seg_table(cu_seqlens + s0, std::min(VFM_MAX_SEQS, n_seqs - s0), &segs);
       const vfm::TileIndex ti = vfm::make_tile_index<false>(segs, rows_per_tile);
-      const vfm::UnitMap um = vfm::make_unit_map(vfm::count_tiles(ti), n_heads, vfm::unequal_units(segs));
+      const vfm::UnitMap um = vfm::make_unit_map(segs, ti, rows_per_tile, n_heads);
       const int grid = um.chunk * vfm::kNumXcd;
       if (pass == 1)
         for (int b = 0; b < grid; ++b) {

@@ -182,26 +182,16 @@ struct UnitMap {
 // b % kNumXcd and takes unit (b % kNumXcd) * chunk + b / kNumXcd, so that the workgroups
 // sharing an L2 walk neighbouring tiles of the same head.  Grid = chunk * kNumXcd.
 //
-// Dealt units: tile-major, u = tile * n_heads + head, workgroup b takes unit b.  Where the heads do not divide by
-// the XCDs a contiguous chunk holds pieces of heads, and with clips of unequal length (longest first) some XCDs get
-// the long clips of such a head and others the short ones.  Dealt out, every XCD gets its share of every clip
-// (head_dim 128, 12 heads, 5,000 + 1,200 + 700 + 300 tokens, contiguous -> dealt: forward 240 -> 173 us, backward
-// 661 -> 525; 9,000 + 7,000 + 1,100 tokens 863 -> 718 and 2,547 -> 2,268; 4 x 1,500 + 8 x 300, 4 heads, backward
-// 121 -> 92; level where two heads have enough XCDs each).  An XCD then walks n_heads / gcd(n_heads, kNumXcd) heads at
-// a time instead of one or two, so equal clips keep their chunks.  Where the long units are just more than
-// the CUs, short ones first can be the luckier order (4 x 1,500 + 8 x 300, 12 heads, forward: 79 -> 87).
-__host__ inline UnitMap make_unit_map(int tiles_per_head, int n_heads, bool unequal = false) {
+// Dealt units: tile-major, u = tile * n_heads + head, workgroup b takes unit b: every XCD gets its share of every
+// clip (see deal_units for when).
+__host__ inline UnitMap make_unit_map(int tiles_per_head, int n_heads, bool dealt = false) {
   UnitMap um;
   um.tiles_per_head = tiles_per_head;
   um.n_units = tiles_per_head * n_heads;
   um.chunk = (um.n_units + kNumXcd - 1) / kNumXcd;
-  um.dealt_heads = unequal && n_heads % kNumXcd != 0 ? n_heads : 0;
+  um.dealt_heads = dealt ? n_heads : 0;
   return um;
 }
-// Whether the units of a self-attention launch differ in length.  (Cross-attention tables are ordered by pairs, not by
-// the range that a unit walks: dealt out in that order long units may come last.)
-inline bool unequal_units(const SegTable& segs) { return segs.n > 0 && segs.len[segs.n - 1] != segs.len[0]; }
-inline bool unequal_units(const XSegTable&) { return false; }
 
 __host__ __device__ __forceinline__ bool map_unit(const UnitMap& um, int block, int& head, int& tile) {
   if (um.dealt_heads) {
@@ -259,6 +249,101 @@ __host__ __device__ __forceinline__ void locate_tile(const TileIndex& ti, int n,
   }
   s = lo;
   t = tile - ti.cu[lo];
+}
+
+// When a self-attention launch deals its units out (make_unit_map).  Where the heads do not divide by the XCDs a contiguous
+// chunk holds pieces of heads, and with clips of unequal length (longest first) some XCDs get the long clips of such a
+// head and others the short ones.  Dealt out, every XCD gets its share, but walks n_heads / gcd(n_heads, kNumXcd) heads
+// at a time instead of one or two, which costs where there is nothing to even out (head_dim 128, contiguous -> dealt:
+// 4,096 + 4,095 tokens, forward, 12 heads 213 -> 215 us, 13 219 -> 225, 33 586 -> 594; 8,192 + 8,190 + 8,100, 33 heads,
+// backward 9.6 -> 10.1 ms).  So both orders are weighed here: their units are handed in order to the 32 CUs of an
+// XCD, a unit taking its clip's length, a little less for a tile with few rows (a quarter of the time goes with them),
+// and units are dealt where the contiguous order ends over 3% later.  Measured over 312 forward and backward calls (2 to
+// 33 heads, 2 to 48 clips of 260 to 20,000 tokens, both head_dims), against contiguous throughout: 0.934 of the time in
+// the geometric mean, at worst 1.04 (24 us) and then 1.02; dealing every unequal call 0.936, at worst 1.09.
+// Gains: 12 heads, 5,000 + 1,200 + 700 + 300 tokens, forward 245 -> 176 us, backward 666 -> 533;
+// 9,000 + 7,000 + 1,100 tokens 886 -> 730 and 2,616 -> 2,302; 4 x 1,500 + 8 x 300, 4 heads, backward 120 -> 91.
+// Left contiguous: 4 x 1,500 + 8 x 300, 12 heads, forward 81 (dealt 89), 5,697 + 1,143, 12 heads, 281 (294).
+// Up to one unit per CU the orders end together.  Beyond kDealWeighed units per CU a launch ends when its
+// heaviest XCD has done its work, whose sum takes no walk over the units (which costs the host 2 to 5 us, with an odd
+// number of heads up to 12).
+constexpr int kXcdCus = 32;
+constexpr int kDealWeighed = 2;
+struct XcdClock {   // when the CUs of one XCD are done: a heap, the first to be done on top
+  float done[kXcdCus] = {}, last = 0.f;
+  void take(float cost) {
+    const float t = done[0] + cost;
+    int i = 0;
+    for (int c; (c = 2 * i + 1) < kXcdCus; i = c) {
+      c += c + 1 < kXcdCus && done[c + 1] < done[c];
+      if (done[c] >= t) break;
+      done[i] = done[c];
+    }
+    done[i] = t;
+    last = t > last ? t : last;
+  }
+};
+inline bool deal_units(const SegTable& segs, const TileIndex& ti, int rows_per_tile, int n_heads) {
+  if (n_heads % kNumXcd == 0 || segs.n == 0 || segs.len[segs.n - 1] == segs.len[0]) return false;
+  const int tiles = count_tiles(ti);
+  const long long units = (long long)tiles * n_heads, chunk = (units + kNumXcd - 1) / kNumXcd;
+  if (chunk <= kXcdCus) return false;
+  constexpr float kMargin = 1.03f;
+  auto tile_cost = [&](int s, int t) {
+    const int left = segs.len[s] - t * rows_per_tile;
+    return (long long)segs.len[s] * (3LL * rows_per_tile + (left < rows_per_tile ? left : rows_per_tile));
+  };
+  if (chunk > kDealWeighed * kXcdCus) {
+    auto tiles_cost = [&](int end) {   // of a head's tiles [0, end)
+      long long sum = 0;
+      for (int s = 0; s < segs.n && ti.cu[s] < end; ++s) {
+        const int last = (ti.cu[s + 1] < end ? ti.cu[s + 1] : end) - ti.cu[s] - 1;
+        sum += last * tile_cost(s, 0) + tile_cost(s, last);
+      }
+      return sum;
+    };
+    const long long head = tiles_cost(tiles);
+    auto units_cost = [&](long long end) { return end / tiles * head + tiles_cost((int)(end % tiles)); };
+    for (int x = 0; x < kNumXcd; ++x) {
+      const long long a = x * chunk, b = a + chunk;
+      if (a < units && (float)(units_cost(b < units ? b : units) - units_cost(a)) * kNumXcd > kMargin * head * n_heads) return true;
+    }
+    return false;
+  }
+  struct Cursor { int tile, s; };   // (tiles are asked for in order)
+  auto cost_at = [&](Cursor& at, int tile) {
+    if (tile < at.tile) at.s = 0;
+    at.tile = tile;
+    while (ti.cu[at.s + 1] <= tile) ++at.s;
+    return (float)tile_cost(at.s, tile - ti.cu[at.s]);
+  };
+  XcdClock dealt;   // XCD 0 has the first, longest unit of every eight
+  Cursor at{0, 0};
+  for (int u = 0; u < (int)units; u += kNumXcd) dealt.take(cost_at(at, u / n_heads));
+  int first[kNumXcd];
+  for (int x = 0; x < kNumXcd; ++x) {
+    const int a = x * (int)chunk, b = (int)(a + chunk < units ? a + chunk : units);
+    first[x] = a % tiles;
+    bool seen = false;   // an XCD that starts at the same tile has done as much
+    for (int y = 0; y < x; ++y) seen |= first[y] == first[x];
+    if (seen) continue;
+    XcdClock c;
+    for (int u = a, tile = first[x]; u < b; ++u) {
+      c.take(cost_at(at, tile));
+      tile = tile + 1 < tiles ? tile + 1 : 0;
+    }
+    if (c.last > kMargin * dealt.last) return true;
+  }
+  return false;
+}
+// (Cross-attention tables are ordered by pairs, not by the range that a unit walks: dealt out in that order long units
+// may come last.)
+inline bool deal_units(const XSegTable&, const TileIndex&, int, int) { return false; }
+
+// The unit map of an attention launch over the tiles of ti, rows_per_tile rows each.
+template <class Segs>
+inline UnitMap make_unit_map(const Segs& segs, const TileIndex& ti, int rows_per_tile, int n_heads) {
+  return make_unit_map(count_tiles(ti), n_heads, deal_units(segs, ti, rows_per_tile, n_heads));
 }
 
 // Sequences with at most this many keys have their Delta formed in its cancellation-free form (backward); the

@@ -205,32 +205,67 @@ static void check_dealt_units() {
 }
 
 // The unit maps of the attention kernels: every (head, tile) exactly once; dealt out, no XCD has more tiles of any
-// clip than another but for one per head.
+// range of tiles than another, but for one.
 static void check_unit_maps() {
   for (int heads : {1, 2, 3, 4, 8, 12, 20, 33})
     for (int tiles : {1, 2, 7, 58, 441})
-      for (bool unequal : {false, true}) {
-        const vfm::UnitMap um = vfm::make_unit_map(tiles, heads, unequal);
-        EXPECT((um.dealt_heads != 0) == (unequal && heads % vfm::kNumXcd != 0));
-        std::vector<int> seen(heads * tiles, 0), first(vfm::kNumXcd, 0);
+      for (bool dealt : {false, true}) {
+        const vfm::UnitMap um = vfm::make_unit_map(tiles, heads, dealt);
+        EXPECT((um.dealt_heads != 0) == dealt);
+        std::vector<int> seen(heads * tiles, 0);
+        std::vector<std::vector<int>> upto(vfm::kNumXcd, std::vector<int>(tiles + 1, 0));   // tiles [0, t) of an XCD
         for (int b = 0; b < um.chunk * vfm::kNumXcd; ++b) {
           int head = -1, tile = -1;
           if (!vfm::map_unit(um, b, head, tile)) continue;
           EXPECT(head >= 0 && head < heads && tile >= 0 && tile < tiles);
           ++seen[head * tiles + tile];
-          if (tile < (tiles + 1) / 2) ++first[b % vfm::kNumXcd];
+          ++upto[b % vfm::kNumXcd][tile + 1];
         }
         for (int n : seen) EXPECT(n == 1);
-        const auto [lo, hi] = std::minmax_element(first.begin(), first.end());
-        if (um.dealt_heads) EXPECT(*hi - *lo <= 1);
+        if (!dealt) continue;
+        for (auto& u : upto)
+          for (int t = 0; t < tiles; ++t) u[t + 1] += u[t];
+        for (int a = 0; a < tiles; ++a)
+          for (int t = a + 1; t <= tiles; ++t) {
+            int lo = seen.size(), hi = 0;
+            for (const auto& u : upto) lo = std::min(lo, u[t] - u[a]), hi = std::max(hi, u[t] - u[a]);
+            EXPECT(hi - lo <= 1);
+          }
       }
-  vfm::SegTable t{};
-  EXPECT(!vfm::unequal_units(t));
-  t.n = 2;
-  t.len[0] = t.len[1] = 5;
-  EXPECT(!vfm::unequal_units(t));
-  t.len[1] = 4;
-  EXPECT(vfm::unequal_units(t));
+}
+
+// Which launches are dealt (the rule's choice by itself is checked against a model of its own in the scheduler's
+// tests): never one whose heads divide by the XCDs, whose clips are all alike or which has a unit per CU at most; every
+// table of random clips is walked without a read past its end.
+static void check_deal_rule() {
+  auto table = [](std::vector<int> lens) {
+    std::sort(lens.rbegin(), lens.rend());
+    vfm::SegTable t{};
+    t.n = (int)lens.size();
+    for (int s = 0, at = 0; s < t.n; at += lens[s++]) { t.len[s] = lens[s]; t.start[s] = at; }
+    return t;
+  };
+  auto deal = [](const vfm::SegTable& t, int rows, int heads) {
+    return vfm::deal_units(t, vfm::make_tile_index<false>(t, rows), rows, heads);
+  };
+  EXPECT(!deal(table({}), 256, 12));
+  for (int rows : {128, 256}) {
+    EXPECT(deal(table({5000, 1200, 700, 300}), rows, 12) && !deal(table({5000, 1200, 700, 300}), rows, 16));
+    EXPECT(!deal(table(std::vector<int>(64, 3000)), rows, 12) && !deal(table({3000, 100}), rows, 4));
+    EXPECT(!deal(table({33554432}), rows, 1) && !deal(table({33554431, 1}), rows, 1));
+  }
+  std::mt19937 rng(7);
+  for (int trial = 0; trial < 2000; ++trial) {
+    const int n = 1 + (int)(rng() % (trial % 5 ? 12 : VFM_MAX_SEQS)), most = 1 << (rng() % 15);
+    std::vector<int> lens(n);
+    for (int& l : lens) l = 1 + (int)(rng() % most);
+    const vfm::SegTable t = table(lens);
+    const int heads = 1 + (int)(rng() % 33), rows = rng() & 1 ? 128 : 256;
+    const vfm::TileIndex ti = vfm::make_tile_index<false>(t, rows);
+    const bool dealt = deal(t, rows, heads);
+    if (dealt) EXPECT(heads % vfm::kNumXcd != 0 && t.len[0] != t.len[n - 1] && vfm::count_tiles(ti) * heads > 256);
+    EXPECT((vfm::make_unit_map(t, ti, rows, heads).dealt_heads == heads) == dealt);
+  }
 }
 
 // The one pass serves clips of up to 256 tokens; at head_dim 128 and more than 96 it needs more two-pass
@@ -287,6 +322,7 @@ int main() {
   check_bwd_order();
   check_dealt_units();
   check_unit_maps();
+  check_deal_rule();
   check_one_pass_rule();
   std::mt19937 rng(12345);
   void* const P = reinterpret_cast<void*>(0x10000);     // never dereferenced: the stubs launch nothing

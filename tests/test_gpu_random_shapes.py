@@ -103,13 +103,16 @@ def test_two_pass_tile_edges_head_dim_64(lengths):
 
 
 @pytest.mark.parametrize("head_dim", [64, 128])
-@pytest.mark.parametrize("heads", [2, 12])
-def test_dealt_units_of_unequal_clips(heads, head_dim):
-    """Heads that do not divide by the XCDs and clips of unequal length: tiles are dealt out, and each clip gets
-    the bits that it gets in a call of its own."""
+@pytest.mark.parametrize("heads, lens, dealt_rows", [(2, (1301, 700, 700, 257, 5), ()), (12, (1301, 700, 700, 257, 5), (128,)),
+                                                     (12, (5000, 1200, 700, 300), (128, 256)), (13, (4467, 490), (256,))], ids=str)
+def test_dealt_units_of_unequal_clips(heads, lens, dealt_rows, head_dim):
+    """Heads that do not divide by the XCDs and clips of unequal length: whether the tiles of a pass (of 128 or 256
+    rows) are dealt out or not, each clip gets the bits that it gets in a call of its own."""
     import torch
     from paper_2503_12964_amd import binding as b
-    lens = (1301, 700, 700, 257, 5)
+    for rows in (128, 256):      # dealt: the second workgroup has the first tile's next head
+        second = b.vfm_schedule_units(np.concatenate([[0], np.cumsum(lens)]), heads, rows)[1].tolist()
+        assert (second == [1, 0, rows]) == (rows in dealt_rows)
     n = sum(lens)
     gen = torch.Generator(device="cuda").manual_seed(heads + head_dim)
     q, k, v, do = (torch.empty((n, heads, head_dim), device="cuda").normal_(generator=gen).to(torch.bfloat16) for _ in range(4))

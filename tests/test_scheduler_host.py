@@ -3,6 +3,8 @@ the kernels' own block -> (head, tile) -> rows mapping on the CPU.  Checked here
 token) is handed out exactly once, no tile straddles a clip (cross-clip blocks are never
 enumerated), clips go longest first, the grid is padded by fewer than 8 idle workgroups, and
 each XCD gets one contiguous run of units, or, where units are dealt out, its share of every clip."""
+import heapq
+
 import numpy as np
 import pytest
 
@@ -19,10 +21,30 @@ def _units_in_order(units):
     return [tuple(int(v) for v in u) for u in order]
 
 
-def _is_dealt(lens, heads):
-    """Whether a launch over clips of these lengths deals its units out."""
-    live = [n for n in lens if n > 0]
-    return heads % XCDS != 0 and len(set(live)) > 1
+def _dealing_gain(lens, heads, rows):
+    """How much later the contiguous order of these clips' units ends than the dealt one: units handed in
+    order to the 32 CUs of an XCD, each taking its clip's length, a quarter of that by its rows.  None: every
+    CU has at most one unit, or there is nothing to even out.  Beyond two units per CU: the heaviest XCD's
+    work against the mean."""
+    live = sorted((int(n) for n in lens if n > 0), reverse=True)
+    if heads % XCDS == 0 or len(set(live)) < 2:
+        return None
+    tiles = [n * (0.75 + 0.25 * min(rows, n - t) / rows) for n in live for t in range(0, n, rows)]
+    chunk = -(-len(tiles) * heads // XCDS)
+    if chunk <= 32:
+        return None
+    whole = tiles * heads
+    parts = [whole[x * chunk:(x + 1) * chunk] for x in range(XCDS)]
+    if chunk > 64:
+        return max(map(sum, parts)) * XCDS / sum(whole)
+
+    def end(units):
+        cus = [0.0] * 32
+        for u in units:
+            heapq.heapreplace(cus, cus[0] + u)
+        return max(cus)
+
+    return max(map(end, parts)) / end([t for t in tiles for _ in range(heads)][::XCDS])
 
 
 def _check(cu, heads, rows, units=None):
@@ -40,7 +62,11 @@ def _check(cu, heads, rows, units=None):
     n_tiles = int(sum((n + rows - 1) // rows for n in lens))
     assert len(units) % XCDS == 0
     assert len(units) == XCDS * ((n_tiles * heads + XCDS - 1) // XCDS)
-    dealt = _is_dealt(lens, heads)
+    gain = _dealing_gain(lens, heads, rows)
+    # the order is told by the second workgroup: the first tile's next head, or the second XCD's run
+    dealt = gain is not None and [int(v) for v in units[1]] == [1 % heads, *(int(v) for v in units[0][1:])]
+    if gain is not None and abs(gain - 1.03) > 1e-3:
+        assert dealt == (gain > 1.03)
     ordered = [tuple(int(v) for v in u) for u in units] if dealt else _units_in_order(units)
     live = [u for u in ordered if u[0] >= 0]
     assert len(live) == n_tiles * heads and len(units) - len(live) < XCDS
@@ -110,6 +136,21 @@ def test_unequal_clips_are_dealt_where_heads_do_not_divide_by_the_xcds():
     assert longest == [30] * XCDS
     heads = [int(u[0]) for u in _units_in_order(_check(cu, 16, 256)) if u[0] >= 0]
     assert heads == sorted(heads)
+
+
+@pytest.mark.parametrize("lens, heads, rows, dealt", [
+    ((4096, 4095), 12, 256, False), ((4096, 4095), 13, 128, False), ((4096, 4095), 33, 256, False),
+    ((8192, 8190, 8100), 33, 256, False),                        # nothing to even out, only heads to mix
+    ((1500,) * 4 + (300,) * 8, 12, 256, False),                  # both orders need two rounds of long units
+    ((1500,) * 4 + (300,) * 8, 4, 128, True),                    # two rounds against one
+    ((5412, 440), 12, 256, True),                                # the second round is tiles of 36 rows, if dealt
+    ((9000, 7000, 1100), 12, 256, True), ((4467, 490), 13, 256, True),
+    ((700, 300), 12, 128, False),                                # one unit per CU at most
+    ((20000, 15000), 13, 256, True), ((20000, 19900), 13, 256, False),
+])
+def test_units_are_dealt_where_the_contiguous_order_ends_later(lens, heads, rows, dealt):
+    units = _check(np.concatenate([[0], np.cumsum(lens)]), heads, rows)
+    assert (int(units[1][0]) == 1 and int(units[1][1]) == int(units[0][1])) == dealt
 
 
 def test_equal_lengths_keep_packed_order_and_empty_input_has_no_workgroups():
