@@ -394,11 +394,15 @@ inline int fwd_tile_rows(const Segs& segs, int head_dim) {
 }
 
 // Whether a run of clips (longest first) takes the one-pass backward, which forms its own statistics: one
-// workgroup per (clip, head), clips of at most 256 tokens.  At head_dim 64 it is faster up to
-// 224 tokens (2 and 256 units, two passes, one pass: 64 tokens 11.5, 8.4 and 13.2, 8.7 us; 128 tokens 12.0, 9.6 and
-// 16.3, 12.6; 192 tokens 13.3, 13.8 and 23.7, 16.9) and beyond for 160 units and more (256 tokens 15.3, 18.4 at 2
-// units, 19.4, 20.5 at 128, 25.5, 22.1 at 160, 28.8, 24.2 at 256); smaller runs of 225 to 256 tokens lose 1 to 3 us to
-// it and take it all the same, one rule for every run of short clips.  At head_dim 128 up to 96 tokens too (2 units of 64 and 96
+// workgroup per (clip, head), clips of at most 256 tokens.  At head_dim 64 it is faster to about 190 tokens at any
+// number of units, and to 224 level with few of them (two passes, one pass: 2 and 256 units of 64 tokens 11.5, 8.4 and
+// 13.2, 8.7 us; 160 tokens 13.5, 11.7 and 21.8, 15.1; 192 tokens 13.3, 13.6 and 22.5, 17.4; 224 tokens 15.2, 15.9 and
+// 26.4, 21.4).  Beyond, its lone workgroup takes longer than the two passes as long as each CU has at most one of their
+// dK/dV workgroups, two to a clip of more than 128 tokens (225 tokens x 128 units 18.3, 20.1, x 136 23.7, 20.6; 256 tokens
+// x 2 15.2, 18.2, x 64 16.9, 19.4, x 128 18.5, 20.4, x 136 24.0, 21.1, x 256 28.2, 24.6, x 9,216 934, 827; units of 256 and
+// of 64 tokens, 16 and 112 16.2, 19.5, 16 and 496 24.4, 21.1).  (Where a second round of lone
+// workgroups has just begun the lead is gone: 320 units of 225 to 256 tokens 37 to 42, 41.)
+// At head_dim 128 it is level or faster up to 96 tokens (2 units of 64 and 96
 // tokens 10.1 and 12.0 against 10.4 and 12.2; 256 units 12.6 and 16 against 22 and 28).  Beyond, its lone
 // workgroup takes longer than the two-pass kernel's, which spreads a (clip, head) over up to three, so a run
 // whose two-pass workgroups fit the chip at once stays there (two passes, one pass: 128 tokens x 64 units
@@ -409,7 +413,12 @@ constexpr int kOnePassMaxRows = 256;
 inline bool bwd_one_pass(const SegTable& segs, int n_heads, int head_dim, int cus) {
   const int longest = segs.len[0];
   if (longest > kOnePassMaxRows) return false;
-  if (head_dim == 64 || longest <= 96) return true;
+  if (longest <= (head_dim == 64 ? 224 : 96)) return true;
+  if (head_dim == 64) {
+    long long tiles = 0;   // of 128 keys
+    for (int s = 0; s < segs.n; ++s) tiles += segs.len[s] > 128 ? 2 : 1;
+    return tiles * n_heads > cus;
+  }
   long long rows = 0;   // two-pass workgroups (tiles of 128 keys, of 256 queries), each as the rows of its clip
   for (int s = 0; s < segs.n; ++s) rows += (segs.len[s] > 128 ? 3 : 2) * (segs.len[s] > 64 ? segs.len[s] : 64);
   return rows * n_heads > (long long)cus * longest;

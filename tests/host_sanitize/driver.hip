@@ -269,7 +269,8 @@ static void check_deal_rule() {
 }
 
 // The one pass serves clips of up to 256 tokens; at head_dim 128 and more than 96 it needs more two-pass
-// workgroups than the chip has places for, short clips counting for their share.
+// workgroups than the chip has places for, short clips counting for their share; at head_dim 64 and more than 224
+// more dK/dV workgroups than CUs.
 static void check_one_pass_rule() {
   auto run = [](int n, int len, int m, int other) {
     vfm::SegTable t{};
@@ -278,7 +279,13 @@ static void check_one_pass_rule() {
     return t;
   };
   EXPECT(!vfm::bwd_one_pass(run(1, 257, 255, 1), 32, 64, 256) && !vfm::bwd_one_pass(run(1, 257, 255, 1), 32, 128, 256));
-  EXPECT(vfm::bwd_one_pass(run(1, 256, 0, 0), 1, 64, 256) && vfm::bwd_one_pass(run(1, 96, 0, 0), 1, 128, 256));
+  EXPECT(vfm::bwd_one_pass(run(1, 224, 0, 0), 1, 64, 256) && vfm::bwd_one_pass(run(1, 96, 0, 0), 1, 128, 256));
+  for (int len : {225, 256}) {
+    EXPECT(!vfm::bwd_one_pass(run(1, len, 0, 0), 1, 64, 256) && !vfm::bwd_one_pass(run(8, len, 0, 0), 16, 64, 256));
+    EXPECT(vfm::bwd_one_pass(run(1, len, 0, 0), 129, 64, 256) && vfm::bwd_one_pass(run(256, len, 0, 0), 65535, 64, 256));
+    EXPECT(!vfm::bwd_one_pass(run(1, len, 14, 128), 16, 64, 256) && vfm::bwd_one_pass(run(1, len, 15, 128), 16, 64, 256));
+    EXPECT(vfm::bwd_one_pass(run(1, len, 14, 129), 16, 64, 256));
+  }
   EXPECT(!vfm::bwd_one_pass(run(1, 256, 0, 0), 85, 128, 256) && vfm::bwd_one_pass(run(1, 256, 0, 0), 86, 128, 256));
   EXPECT(!vfm::bwd_one_pass(run(1, 128, 0, 0), 128, 128, 256) && vfm::bwd_one_pass(run(1, 128, 0, 0), 129, 128, 256));
   EXPECT(!vfm::bwd_one_pass(run(1, 256, 7, 64), 16, 128, 256) && vfm::bwd_one_pass(run(1, 256, 31, 64), 16, 128, 256));
