@@ -45,6 +45,21 @@ def test_header_compiles_as_c_and_cxx(tmp_path):
         assert res.returncode == 0 and not res.stderr.strip(), res.stderr
 
 
+def test_host_arrays_are_taken_as_int32_only(lib):
+    """A 64-bit clip table (numpy's default integers) or a bare address would be read as int32: refused."""
+    wide = np.array([0, 5, 9])
+    rows = ctypes.c_int(0)
+    for bad in (wide.ctypes.data_as(ctypes.POINTER(ctypes.c_int64)), wide.ctypes.data, b"\0" * 12):
+        with pytest.raises(ctypes.ArgumentError):
+            lib.vfm_attn_fwd_tile_rows(bad, 2, 9, 128, 0, ctypes.byref(rows))
+    good = wide.astype(np.int32)
+    assert lib.vfm_attn_fwd_tile_rows(good.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)), 2, 9, 128, 0, ctypes.byref(rows)) == 0
+    assert rows.value == binding.vfm_attn_fwd_tile_rows(wide, 128) == 128
+    no_tables = {"vfm_strerror", "vfm_last_hip_error", "vfm_attn_bwd_workspace_size", "vfm_xattn_bwd_workspace_size"}
+    for name in binding.EXPORTS:
+        assert (ctypes.POINTER(ctypes.c_int32) in getattr(lib, name).argtypes) == (name not in no_tables), name
+
+
 def test_strerror_texts(lib):
     assert lib.vfm_strerror(0) == b"ok"
     texts = {lib.vfm_strerror(i) for i in range(11)}
