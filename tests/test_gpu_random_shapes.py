@@ -183,14 +183,16 @@ def test_one_pass_backward_under_graph_replay_and_without_workspace():
         assert all(torch.equal(a.view(torch.int16), c.view(torch.int16)) for a, c in zip(got, want))
 
 
+@pytest.mark.parametrize("head_dim", [64, 128])
 @pytest.mark.parametrize("lengths", [(1100, 700, 20, 1), (1025, 257, 33)], ids=["few_keys", "tails"])
-def test_statistics_from_the_dq_pass(lengths):
-    """Packs with a clip of more than 1,024 tokens at head_dim 128: the dQ pass forms Delta (not that of
-    clips of at most 32 keys) and the dK/dV pass reads it; with dq written over dout both come from
+def test_statistics_from_the_dq_pass(lengths, head_dim):
+    """Packs with a clip of more than 1,024 tokens (at head_dim 64: more than 256): the dQ pass forms Delta (not
+    that of clips of at most 32 keys) and the dK/dV pass reads it; with dq written over dout both come from
     the separate pass and the gradients are the same bits."""
     import torch
     from paper_2503_12964_amd import binding as b
-    wl = W.Workload("dq_first", tuple((1, 1, n) for n in lengths), 3, 128, (32, 48, 48), seed=31)
+    dims = (16, 24, 24) if head_dim == 64 else (32, 48, 48)
+    wl = W.Workload("dq_first", tuple((1, 1, n) for n in lengths), 3, head_dim, dims, seed=31)
     gpu, host = _run_fwd_bwd(wl)
     _assert_parity(wl, gpu, host, relative_maxabs=True)
     q, k, v, do = (U.to_device(W.make_inputs(wl)[n]) for n in ("q", "k", "v", "dout"))
