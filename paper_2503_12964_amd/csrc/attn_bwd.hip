@@ -621,7 +621,7 @@ struct DqCfg {
   static constexpr int kChunksPerThread = kDqBC * kChunksPerRow / (W * 64);
 };
 
-// Serves head_dim 64, where the exponentials weigh twice as much against the products as at 128: with 149 registers
+// Serves head_dim 64, where the exponentials weigh twice as much against the products as at 128: with 154 registers
 // three workgroups of four wavefronts share a CU, and half as many rows per workgroup spread small calls
 // over more CUs.  Against one workgroup of eight wavefronts per CU (whole backward call): 64 clips of 300 tokens x 16 heads
 // 176 -> 145 us, 2 x 2,048 tokens x 2 heads 74 -> 64, 8,192 x 12 692 -> 655, 32,768 x 32 26.9 -> 26.2 ms, 2 x 4,096 x
@@ -912,8 +912,8 @@ __device__ __forceinline__ float row16_sum(float v) {
 
 // The work of one workgroup: query tile tq of sequence seq, one head.  STATS: form Delta and lse in log2
 // units of the tile's rows here, from `out` and `lse`, and leave them for the dK/dV pass (Delta of a sequence
-// with few keys is already in place).  The rows of dO are in registers anyway, so this costs the reads of
-// `out`, where the separate pass reads dO as well and is one more launch.
+// with few keys is already in place).  The rows of dO are in LDS on their way into registers, so this costs the
+// reads of `out`, where the separate pass reads dO as well and is one more launch.
 template <int D, class Segs, bool STATS>
 __device__ __forceinline__
 void bwd_dq2_unit(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
@@ -1342,7 +1342,9 @@ void attn_bwd_both_kernel(const __bf16* __restrict__ q, const __bf16* __restrict
 //             (out and dO straight from memory; dO is read again below while it is in L2), but at head_dim 128
 //             with eight wavefronts, where no other workgroup's products hide those loads: there out rides in
 //             the ring and Delta(b+1) is formed in phase 2 of block b, behind a barrier that block b+1 has landed
-//             before (288 clips of 256 tokens x 32 heads: backward call 1,418 -> 1,368 us, 300 of 130 x 16 442 -> 419)
+//             before (288 clips of 256 tokens x 32 heads: backward call 1,418 -> 1,368 us, 300 of 130 x 16 442 -> 419).
+//             Eight wavefronts have a CU to themselves at head_dim 64 too; there the barrier that would publish the
+//             block is the one that the second dS removes (below), and Delta by blocks has not been tried
 //   per block b of 32 query rows (Q, dO in a ring of three LDS stages, requested two blocks ahead; two stages where that lets two
 //   workgroups share a CU):
 //     phase 1  dQ(b-1) = dS(b-1) K, every wavefront 32 columns over all keys, to memory;
@@ -1353,13 +1355,14 @@ void attn_bwd_both_kernel(const __bf16* __restrict__ q, const __bf16* __restrict
 // dS is written in phase 2 and read in phase 1 only, so it needs no second copy.  At head_dim 64 there is room for one,
 // and with it the barrier between the phases goes (288 clips of 256 tokens x 32 heads 850 -> 810 us); at 128 it gave
 // 1% with eight wavefronts and does not fit two workgroups with four.  Keys past the clip's end
-// have dS = 0; query rows past it P = 0 (lse = +inf).  Four wavefronts serve 128 tokens in 73 KB of LDS (49 at
+// have dS = 0; query rows past it P = 0 (lse = +inf).  Four wavefronts serve 128 tokens in 73 KB of LDS (57 at
 // head_dim 64), so that two workgroups share a CU and one's loads and stores meet the other's products;
-// eight serve 256 tokens, at head_dim 128 one workgroup per CU.  Everything the loop could recompute it does
+// eight serve 256 tokens, one workgroup per CU (154 KB; 90 KB at head_dim 64, where 174 registers allow two wavefronts
+// per SIMD, which is this one workgroup).  Everything the loop could recompute it does
 // (opaque offsets): one spilled register tuple read back in the loop waits for the loads in flight.
-// Whole backward call, statistics pass included, 256 clips x 32 heads, two-pass kernels -> this one:
-// 256 tokens 1653 -> 1266 us (3.4 TB/s of the eight tensors), 128 tokens 801 -> 443, 64 tokens 557 -> 230,
-// 16 tokens 739 -> 140; head_dim 64, 256 tokens 1067 -> 757, 128 tokens 506 -> 240.
+// Whole backward call, statistics included, 256 clips x 32 heads, two-pass kernels -> this one:
+// 256 tokens 1,558 -> 1,203 us (3.6 TB/s of the eight tensors), 128 tokens 810 -> 439, 64 tokens 528 -> 223,
+// 16 tokens 448 -> 128; head_dim 64, 256 tokens 769 -> 721, 128 tokens 340 -> 228, 64 tokens 195 -> 138.
 template <int D, int NW>
 struct FusedCfg {
   static constexpr int kRows = NW * 32;                      // longest clip
