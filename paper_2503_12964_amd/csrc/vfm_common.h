@@ -291,24 +291,23 @@ inline bool deal_units(const SegTable& segs, const TileIndex& ti, int rows_per_t
   constexpr float kMargin = 1.03f;
   auto tile_cost = [&](int s, int t) {
     const int left = segs.len[s] - t * rows_per_tile;
-    return (long long)segs.len[s] * (3LL * rows_per_tile + (left < rows_per_tile ? left : rows_per_tile));
+    return segs.len[s] * (0.75f + 0.25f * (left < rows_per_tile ? left : rows_per_tile) / rows_per_tile);
   };
   if (chunk > kDealWeighed * kXcdCus) {
     auto tiles_cost = [&](int end) {   // of a head's tiles [0, end)
-      long long sum = 0;
+      double sum = 0.0;
       for (int s = 0; s < segs.n && ti.cu[s] < end; ++s) {
         const int last = (ti.cu[s + 1] < end ? ti.cu[s + 1] : end) - ti.cu[s] - 1;
-        sum += last * tile_cost(s, 0) + tile_cost(s, last);
+        sum += (double)last * tile_cost(s, 0) + tile_cost(s, last);
       }
       return sum;
     };
-    const long long head = tiles_cost(tiles);
-    auto units_cost = [&](long long end) { return end / tiles * head + tiles_cost((int)(end % tiles)); };
+    const double head = tiles_cost(tiles);
+    auto units_cost = [&](long long end) { return (double)(end / tiles) * head + tiles_cost((int)(end % tiles)); };
     for (int x = 0; x < kNumXcd; ++x) {
       const long long a = x * chunk, b = a + chunk;
       if (a >= units) break;
-      const long long share = units_cost(b < units ? b : units) - units_cost(a);
-      if ((float)share * kNumXcd > kMargin * head * n_heads) return true;
+      if ((units_cost(b < units ? b : units) - units_cost(a)) * kNumXcd > kMargin * head * n_heads) return true;
     }
     return false;
   }
@@ -317,7 +316,7 @@ inline bool deal_units(const SegTable& segs, const TileIndex& ti, int rows_per_t
     if (tile < at.tile) at.s = 0;
     at.tile = tile;
     while (ti.cu[at.s + 1] <= tile) ++at.s;
-    return (float)tile_cost(at.s, tile - ti.cu[at.s]);
+    return tile_cost(at.s, tile - ti.cu[at.s]);
   };
   XcdClock dealt;   // XCD 0 has the first, longest unit of every eight
   Cursor at{0, 0};
