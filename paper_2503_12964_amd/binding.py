@@ -27,7 +27,8 @@ EXPORTS = ("vfm_rope3d", "vfm_qknorm_rope3d", "vfm_qknorm_rope3d_bwd", "vfm_attn
            "vfm_attn_fwd_tile_rows")
 
 _lib = None
-_torch = None                # set when the library is loaded
+_calls = None                # the library's functions as the wrappers call them (load_library)
+_torch = None                # both set when the library is loaded
 
 
 class VfmError(RuntimeError):
@@ -38,7 +39,7 @@ class VfmError(RuntimeError):
 
 def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     """dlopen libvfm.so and declare the C signatures.  Raises if it is missing."""
-    global _lib, _torch
+    global _lib, _calls, _torch
     if _lib is not None and path == LIB_PATH:
         return _lib
     if not os.path.exists(path):
@@ -118,7 +119,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
         fn.restype, fn.argtypes = typed.restype, [c_void_p if t is p_i32 else t for t in typed.argtypes]
         setattr(lib.by_address, name, fn)
     if path == LIB_PATH:
-        _lib = lib
+        _lib, _calls = lib, lib.by_address
     return lib
 
 
@@ -211,7 +212,7 @@ def _dtype_code(t) -> int:
 def vfm_rope3d(x, thw, cu_seqlens, dims: Sequence[int], theta: float = 10000.0,
                inverse: bool = False, stream=None):
     """In-place 3D RoPE on x[total, heads, head_dim] (device, bf16).  Returns x."""
-    lib = (_lib or load_library()).by_address
+    lib = _calls or load_library().by_address
     cu = _host_i32(cu_seqlens)
     g = _host_i32(thw).reshape(-1)
     total, heads, hd = x.shape
@@ -224,7 +225,7 @@ def vfm_rope3d(x, thw, cu_seqlens, dims: Sequence[int], theta: float = 10000.0,
 def vfm_qknorm_rope3d(x, gain, eps: float, thw, cu_seqlens, dims: Sequence[int], theta: float = 10000.0,
                       y=None, stream=None):
     """y = RoPE3D(gain * x / sqrt(mean_d x^2 + eps)) per (token, head); y=None works in place on x."""
-    lib = (_lib or load_library()).by_address
+    lib = _calls or load_library().by_address
     cu = _host_i32(cu_seqlens)
     g = _host_i32(thw).reshape(-1)
     total, heads, hd = x.shape
@@ -239,7 +240,7 @@ def vfm_qknorm_rope3d(x, gain, eps: float, thw, cu_seqlens, dims: Sequence[int],
 def vfm_qknorm_rope3d_bwd(x, gain, eps: float, dy, thw, cu_seqlens, dims: Sequence[int],
                           theta: float = 10000.0, dx=None, dgain=None, stream=None) -> Tuple:
     """dx (bf16, shape of x; may be dy itself) and dgain (fp32 [head_dim]) given the forward's input x."""
-    lib = (_lib or load_library()).by_address
+    lib = _calls or load_library().by_address
     cu = _host_i32(cu_seqlens)
     g = _host_i32(thw).reshape(-1)
     total, heads, hd = x.shape
@@ -254,7 +255,7 @@ def vfm_qknorm_rope3d_bwd(x, gain, eps: float, dy, thw, cu_seqlens, dims: Sequen
 
 def vfm_attn_fwd(q, k, v, cu_seqlens, scale: float, out=None, lse=None, stream=None) -> Tuple:
     """out[total, heads, head_dim] (bf16) and lse[heads, total] (fp32) for packed q, k, v."""
-    lib = (_lib or load_library()).by_address
+    lib = _calls or load_library().by_address
     cu = _host_i32(cu_seqlens)
     total, heads, hd = q.shape
     if out is None:
@@ -274,7 +275,7 @@ def vfm_attn_bwd_workspace_size(total_tokens: int, n_heads: int, head_dim: int) 
 def vfm_attn_bwd(q, k, v, out, lse, dout, cu_seqlens, scale: float, dq=None, dk=None, dv=None,
                  workspace=None, stream=None) -> Tuple:
     """dq, dk, dv (bf16, shape of q) given the forward's out and lse."""
-    lib = (_lib or load_library()).by_address
+    lib = _calls or load_library().by_address
     cu = _host_i32(cu_seqlens)
     total, heads, hd = q.shape
     dq = _torch.empty_like(q) if dq is None else dq
@@ -294,7 +295,7 @@ def vfm_attn_bwd(q, k, v, out, lse, dout, cu_seqlens, scale: float, dq=None, dk=
 def vfm_attn_bwd_noalloc(q, k, v, out, lse, dout, cu_seqlens, scale: float, dq, dk, dv, stream=None) -> Tuple:
     """vfm_attn_bwd without a workspace (the library's built-in scratch holds the statistics).
     The caller passes every output; nothing is allocated here or in the library."""
-    lib = (_lib or load_library()).by_address
+    lib = _calls or load_library().by_address
     cu = _host_i32(cu_seqlens)
     total, heads, hd = q.shape
     _check(lib.vfm_attn_bwd_noalloc(_dev(q, "q"), _dev(k, "k"), _dev(v, "v"), _dev(out, "out"), _dev(lse, "lse"),
@@ -306,7 +307,7 @@ def vfm_attn_bwd_noalloc(q, k, v, out, lse, dout, cu_seqlens, scale: float, dq, 
 
 def vfm_xattn_fwd(q, k, v, cu_seqlens_q, cu_seqlens_kv, scale: float, out=None, lse=None, stream=None) -> Tuple:
     """Cross-attention: out[total_q, heads, head_dim] (bf16), lse[heads, total_q] (fp32)."""
-    lib = (_lib or load_library()).by_address
+    lib = _calls or load_library().by_address
     cq, ck = _host_i32(cu_seqlens_q), _host_i32(cu_seqlens_kv)
     if cq.size != ck.size:
         raise ValueError("cu_seqlens_q and cu_seqlens_kv must have the same length")
@@ -328,7 +329,7 @@ def vfm_xattn_bwd_workspace_size(total_q: int, total_kv: int, n_heads: int, head
 def vfm_xattn_bwd(q, k, v, out, lse, dout, cu_seqlens_q, cu_seqlens_kv, scale: float, dq=None, dk=None,
                   dv=None, workspace=None, stream=None) -> Tuple:
     """Cross-attention gradients: dq (shape of q), dk, dv (shape of k)."""
-    lib = (_lib or load_library()).by_address
+    lib = _calls or load_library().by_address
     cq, ck = _host_i32(cu_seqlens_q), _host_i32(cu_seqlens_kv)
     if cq.size != ck.size:
         raise ValueError("cu_seqlens_q and cu_seqlens_kv must have the same length")
@@ -350,7 +351,7 @@ def vfm_xattn_bwd(q, k, v, out, lse, dout, cu_seqlens_q, cu_seqlens_kv, scale: f
 
 def vfm_tattn_fwd(q, k, v, thw, cu_seqlens, scale: float, out=None, stream=None):
     """Temporal attention (one sequence per pixel across a clip's frames): out, shape of q."""
-    lib = (_lib or load_library()).by_address
+    lib = _calls or load_library().by_address
     cu = _host_i32(cu_seqlens)
     g = _host_i32(thw).reshape(-1)
     total, heads, hd = q.shape
@@ -363,7 +364,7 @@ def vfm_tattn_fwd(q, k, v, thw, cu_seqlens, scale: float, out=None, stream=None)
 
 def vfm_tattn_bwd(q, k, v, dout, thw, cu_seqlens, scale: float, dq=None, dk=None, dv=None, stream=None) -> Tuple:
     """Temporal attention gradients dq, dk, dv (shape of q)."""
-    lib = (_lib or load_library()).by_address
+    lib = _calls or load_library().by_address
     cu = _host_i32(cu_seqlens)
     g = _host_i32(thw).reshape(-1)
     total, heads, hd = q.shape
@@ -378,7 +379,7 @@ def vfm_tattn_bwd(q, k, v, dout, thw, cu_seqlens, scale: float, dq=None, dk=None
 
 def vfm_fp8_pack_sizes(cu_seqlens, n_heads: int, head_dim: int) -> Tuple[int, int, int, int]:
     """Bytes of the packed q8, k8, vT8 and scales buffers for these clips."""
-    lib = (_lib or load_library()).by_address
+    lib = _calls or load_library().by_address
     cu = _host_i32(cu_seqlens)
     a, b, c, d = ctypes.c_size_t(), ctypes.c_size_t(), ctypes.c_size_t(), ctypes.c_size_t()
     _check(lib.vfm_fp8_pack_sizes(_i32_ptr(cu), int(cu.size - 1), int(cu[-1]), int(n_heads), int(head_dim),
@@ -390,7 +391,7 @@ def vfm_fp8_pack(q, k, v, cu_seqlens, scale: float, q8=None, k8=None, vT8=None, 
     """Quantise bf16 q, k, v to E4M3 tiles with power-of-two scales, in the packed layout
     vfm_attn_fwd_fp8 reads (uint8 device buffers q8, k8, vT8 and the scales buffer).  q also
     carries scale * log2(e) (scale = softmax scale)."""
-    lib = (_lib or load_library()).by_address
+    lib = _calls or load_library().by_address
     cu = _host_i32(cu_seqlens)
     total, heads, hd = q.shape
     nq, nk, nv, ns = vfm_fp8_pack_sizes(cu, heads, hd)
@@ -407,7 +408,7 @@ def vfm_fp8_pack(q, k, v, cu_seqlens, scale: float, q8=None, k8=None, vT8=None, 
 def vfm_attn_fwd_fp8(q8, k8, vT8, scales, cu_seqlens, n_heads: int, head_dim: int, out=None, lse=None,
                      stream=None) -> Tuple:
     """FP8 attention forward on packed operands: out (bf16 [total, heads, head_dim]) and lse (fp32)."""
-    lib = (_lib or load_library()).by_address
+    lib = _calls or load_library().by_address
     cu = _host_i32(cu_seqlens)
     total = int(cu[-1])
     if out is None:
